@@ -445,6 +445,10 @@ struct EvolveBufs {
   unsigned long long *cross_count = nullptr;
   void *cross_tmp = nullptr;
   size_t cross_tmp_bytes = 0;
+  // the buffers that hold nothing between two steps (the interface lists, and
+  // the records, partial sums and tile boxes of the receivers), contiguous
+  void *idle = nullptr;
+  size_t idle_bytes = 0;
 };
 
 static EvolveBufs evolve_layout(const EvolvePlan &p, const fga_receivers *r, int64_t cap, Arena &ar)
@@ -455,21 +459,26 @@ static EvolveBufs evolve_layout(const EvolvePlan &p, const fga_receivers *r, int
   b.blk_extra = ar.take<int64_t>(nblk_all);
   b.blk_off = ar.take<int64_t>(nblk_all);
   b.total = ar.take<int64_t>(1);
+  const size_t idle0 = Arena::need(ar.used);
   b.cross_list = ar.take<int32_t>(cap + 1);
   b.cross_sorted = ar.take<int32_t>(cap + 1);
   b.cross_count = ar.take<unsigned long long>(1);
   b.cross_tmp_bytes = cross_sort_bytes(cap);
   b.cross_tmp = ar.take<char>(b.cross_tmp_bytes);
+  size_t idle_end = ar.used;
   if (r) {
     const int m = (p.chunk + r->stride - 1) / r->stride + 1;
     b.emit = ar.take<double>((size_t)m * 12 * p.batch);
     const int64_t nblk = (p.batch + p.bpb - 1) / p.bpb;
     b.partial = ar.take<double>((size_t)nblk * m * r->n * 6);
     b.box = ar.take<double>((size_t)m * ((p.batch + 63) / 64) * 6);
+    idle_end = ar.used;
     b.xs = ar.take<double>((size_t)3 * r->n + 1);
     b.perm = ar.take<int32_t>((size_t)r->n + 1);
     if (r->coords == FGA_COORDS_SPHERICAL) b.xc = ar.take<double>((size_t)3 * r->n + 1);
   }
+  b.idle = b.cross_list;
+  b.idle_bytes = idle_end - idle0;
   return b;
 }
 
@@ -493,7 +502,7 @@ size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_
   if (p.resort > 0) {
     Arena sa(nullptr, 0);
     size_t ns = 0;
-    sort_beams_spatial(&bb, sa, nullptr, true, &ns);
+    sort_beams_spatial(&bb, sa, nullptr, 0, nullptr, true, &ns);
     need = need > base + ns ? need : base + ns;
   }
   if (opts && opts->compact) {
@@ -565,7 +574,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
       if (p.resort > 0 && (last_sort < 0 || s0 - last_sort >= p.resort)) {
         Arena sa(static_cast<char *>(workspace) + sort_base, sub_bytes);
         size_t need = 0;
-        if ((s = sort_beams_spatial(beams, sa, st, false, &need)) != FGA_OK) return s;
+        if ((s = sort_beams_spatial(beams, sa, wb.idle, wb.idle_bytes, st, false, &need)) != FGA_OK) return s;
         last_sort = s0;
       }
       const int64_t n = beams->count;
@@ -652,7 +661,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
     if (p.resort > 0 && (last_sort < 0 || s0 - last_sort >= p.resort)) {
       Arena sa(static_cast<char *>(workspace) + sort_base, sub_bytes);
       size_t need = 0;
-      if ((s = sort_beams_spatial(beams, sa, st, false, &need)) != FGA_OK) return s;
+      if ((s = sort_beams_spatial(beams, sa, wb.idle, wb.idle_bytes, st, false, &need)) != FGA_OK) return s;
       last_sort = s0;
     }
     const int64_t n = beams->count;

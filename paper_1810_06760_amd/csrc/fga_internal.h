@@ -190,8 +190,11 @@ hipError_t collect_crossers(const int32_t *flags, int64_t n, int32_t *list, int3
 // exclusive scan of n int64 values (one workgroup); total = sum
 hipError_t launch_scan(const int64_t *in, int64_t *out, int64_t n, int64_t *total, hipStream_t st);
 
-// Morton-order the beam set by Q (dead beams dropped; count updated; synchronises st)
-fga_status sort_beams_spatial(fga_beams *b, Arena &ar, hipStream_t st, bool size_only, size_t *need);
+// Morton-order the beam set by Q (dead beams dropped; count updated; synchronises st).
+// scratch (256-byte aligned, may be NULL): memory free during the call beside the
+// arena's; the more planes it holds the fewer launches the re-ordering takes
+fga_status sort_beams_spatial(fga_beams *b, Arena &ar, void *scratch, size_t scratch_bytes, hipStream_t st,
+                              bool size_only, size_t *need);
 
 // stable compaction of the beam set by FLAGS & ALIVE
 fga_status compact_beams(fga_beams *b, Arena &ar, hipStream_t st, bool size_only, size_t *need);

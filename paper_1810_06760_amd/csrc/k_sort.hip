@@ -106,12 +106,101 @@ __global__ __launch_bounds__(256) void k_count_alive(const uint32_t *__restrict_
   if (live && next_dead) *out = i + 1;
 }
 
-template <class T>
-__global__ __launch_bounds__(256) void k_gather(const T *__restrict__ src, const int32_t *__restrict__ perm,
-                                                int64_t n, T *__restrict__ dst)
+// All planes of a beam set by one number: the FGA_NF64 double planes, the
+// lineage, then the FGA_NI32 int32 planes.
+constexpr int NPLANE = FGA_NF64 + 1 + FGA_NI32;
+constexpr int NWIDE = FGA_NF64 + 1;  // planes of 8-byte entries
+
+struct PlaneSet {
+  double *f64;
+  int32_t *i32;
+  int64_t *lineage;
+  int64_t cap;
+};
+
+// Scratch slots of one plane each (8-byte stride), in two separate regions.
+struct Slots {
+  uint64_t *a, *b;
+  int na, nb;
+  int64_t stride;  // entries
+  __host__ __device__ uint64_t *at(int s) const { return s < na ? a + s * stride : b + (s - na) * stride; }
+};
+
+__device__ __forceinline__ void *plane_ptr(const PlaneSet &p, int id)
+{
+  if (id < FGA_NF64) return p.f64 + (int64_t)id * p.cap;
+  if (id == FGA_NF64) return p.lineage;
+  return p.i32 + (int64_t)(id - NWIDE) * p.cap;
+}
+
+// Re-orders planes through scratch: planes [g0, g1) are gathered,
+// slot[gs + p - g0][i] = plane p[perm[i]], and the slots of the planes
+// [c0, c1), gathered by the launch before, are copied back to their planes.
+// blockIdx.y takes G planes.  The planes of a large set stream through the
+// 256 MB last-level cache one or two at a time, which serves the scattered reads
+// of the first ordering (33 M beams: 22.8 ms for one and two planes per block,
+// 29.9 ms for eight; one plane per launch and a copy kernel, 23.6 ms; 66 k
+// beams: 28 us against 116 launches of 3 us each).
+constexpr int G = 2;
+__global__ __launch_bounds__(256) void k_permute(PlaneSet ps, const int32_t *__restrict__ perm, int64_t n,
+                                                 Slots sl, int g0, int g1, int gs, int c0, int c1, int cs)
 {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) dst[i] = src[perm[i]];
+  if (i >= n) return;
+  const int ng = (g1 - g0 + G - 1) / G;
+  const bool gather = (int)blockIdx.y < ng;
+  const int y = gather ? blockIdx.y : blockIdx.y - ng;
+  const int b = gather ? g0 : c0, e = gather ? g1 : c1, s0 = gather ? gs : cs;
+  const int64_t src = gather ? perm[i] : i;
+  uint64_t v[G];
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    const int p = b + y * G + k;
+    v[k] = 0;
+    if (p < e) {
+      const void *from = gather ? plane_ptr(ps, p) : sl.at(s0 + p - b);
+      v[k] = p < NWIDE ? static_cast<const uint64_t *>(from)[src] : static_cast<const uint32_t *>(from)[src];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    const int p = b + y * G + k;
+    if (p < e) {
+      void *to = gather ? sl.at(s0 + p - b) : plane_ptr(ps, p);
+      if (p < NWIDE) static_cast<uint64_t *>(to)[i] = v[k];
+      else static_cast<uint32_t *>(to)[i] = (uint32_t)v[k];
+    }
+  }
+}
+
+// The permutation of all planes in as few launches as the scratch allows:
+// with NPLANE slots one gather and one copy; with fewer, groups of half the
+// slots, each launch gathering one group while it copies the group before
+// back (a single slot alternates).
+hipError_t permute_planes(const PlaneSet &ps, const int32_t *perm, int64_t n, const Slots &sl, hipStream_t st)
+{
+  const int slots = sl.na + sl.nb;
+  if (slots < 1) return hipErrorInvalidValue;
+  const int per = slots >= NPLANE ? NPLANE : (slots >= 2 ? slots / 2 : 1);
+  const unsigned nblk = (unsigned)((n + 255) / 256);
+  auto launch = [&](int g0, int g1, int gs, int c0, int c1, int cs) {
+    const int y = (g1 - g0 + G - 1) / G + (c1 - c0 + G - 1) / G;
+    hipLaunchKernelGGL(k_permute, dim3(nblk, (unsigned)y), 256, 0, st, ps, perm, n, sl, g0, g1, gs, c0, c1, cs);
+    return hipGetLastError();
+  };
+  const bool overlap = slots >= 2 * per;
+  int prev0 = 0, prev1 = 0, prevs = 0;
+  for (int g0 = 0, k = 0; g0 < NPLANE; g0 += per, ++k) {
+    const int g1 = g0 + per < NPLANE ? g0 + per : NPLANE;
+    const int gs = overlap ? (k & 1) * per : 0;
+    hipError_t e;
+    if (!overlap && prev1 > prev0 && (e = launch(0, 0, 0, prev0, prev1, prevs)) != hipSuccess) return e;
+    if ((e = overlap ? launch(g0, g1, gs, prev0, prev1, prevs) : launch(g0, g1, gs, 0, 0, 0)) != hipSuccess) return e;
+    prev0 = g0;
+    prev1 = g1;
+    prevs = gs;
+  }
+  return launch(0, 0, 0, prev0, prev1, prevs);
 }
 
 struct SortBufs {
@@ -121,31 +210,35 @@ struct SortBufs {
   int64_t *alive;
   void *sort_tmp;
   size_t sort_bytes;
+  size_t free_bytes;  // from k1 on: free once the keys are sorted and the live beams counted
 };
 
 SortBufs sort_layout(int64_t n, Arena &ar)
 {
   SortBufs b{};
   const int64_t nblk = (n + 255) / 256;
-  b.k1 = ar.take<uint32_t>(n + 1);
-  b.k2 = ar.take<uint32_t>(n + 1);
-  b.v1 = ar.take<int32_t>(n + 1);
   b.v2 = ar.take<int32_t>(n + 1);
   b.part = ar.take<double>(6 * nblk + 6);
   b.box = ar.take<double>(6);
-  b.tmp = ar.take<double>(n + 1);
   b.alive = ar.take<int64_t>(1);
+  const size_t keep = Arena::need(ar.used);
+  b.k1 = ar.take<uint32_t>(n + 1);
+  b.k2 = ar.take<uint32_t>(n + 1);
+  b.v1 = ar.take<int32_t>(n + 1);
+  b.tmp = ar.take<double>(n + 1);
   b.sort_bytes = 0;
   // size query only (no device work): the bytes come back in sort_bytes
   (void)hipcub::DeviceRadixSort::SortPairs(nullptr, b.sort_bytes, b.k1, b.k2, b.v1, b.v2, (int)(n > 0 ? n : 1), 0,
                                            32);
   b.sort_tmp = ar.take<char>(b.sort_bytes + 1);
+  b.free_bytes = ar.used - keep;
   return b;
 }
 
 }  // namespace
 
-fga_status sort_beams_spatial(fga_beams *b, Arena &ar, hipStream_t st, bool size_only, size_t *need)
+fga_status sort_beams_spatial(fga_beams *b, Arena &ar, void *scratch, size_t scratch_bytes, hipStream_t st,
+                              bool size_only, size_t *need)
 {
   const int64_t n = b->count;
   SortBufs s = sort_layout(n, ar);
@@ -171,19 +264,15 @@ fga_status sort_beams_spatial(fga_beams *b, Arena &ar, hipStream_t st, bool size
   FGA_HIP(hipMemsetAsync(s.alive, 0, sizeof(int64_t), st));
   hipLaunchKernelGGL(k_count_alive, (unsigned)nblk, 256, 0, st, s.k2, n, s.alive);
   FGA_LAUNCH_CHECK();
-  for (int p = 0; p < FGA_NF64; ++p) {
-    double *pl = b->f64 + (int64_t)p * cap;
-    hipLaunchKernelGGL(k_gather<double>, (unsigned)nblk, 256, 0, st, pl, s.v2, n, s.tmp);
-    FGA_HIP(hipMemcpyAsync(pl, s.tmp, n * sizeof(double), hipMemcpyDeviceToDevice, st));
-  }
-  for (int p = 0; p < FGA_NI32; ++p) {
-    int32_t *pl = b->i32 + (int64_t)p * cap;
-    hipLaunchKernelGGL(k_gather<int32_t>, (unsigned)nblk, 256, 0, st, pl, s.v2, n, (int32_t *)s.tmp);
-    FGA_HIP(hipMemcpyAsync(pl, s.tmp, n * sizeof(int32_t), hipMemcpyDeviceToDevice, st));
-  }
-  hipLaunchKernelGGL(k_gather<int64_t>, (unsigned)nblk, 256, 0, st, b->lineage, s.v2, n, (int64_t *)s.tmp);
-  FGA_HIP(hipMemcpyAsync(b->lineage, s.tmp, n * sizeof(int64_t), hipMemcpyDeviceToDevice, st));
-  FGA_LAUNCH_CHECK();
+  Slots sl{};
+  sl.stride = (n + 31) & ~(int64_t)31;
+  const size_t slot_bytes = (size_t)sl.stride * 8;
+  auto slots_in = [&](size_t bytes) { return (int)(bytes / slot_bytes < NPLANE ? bytes / slot_bytes : NPLANE); };
+  sl.a = static_cast<uint64_t *>(scratch);
+  sl.na = scratch ? slots_in(scratch_bytes) : 0;
+  sl.b = reinterpret_cast<uint64_t *>(s.k1);
+  sl.nb = slots_in(s.free_bytes);
+  FGA_HIP(permute_planes(PlaneSet{b->f64, b->i32, b->lineage, cap}, s.v2, n, sl, st));
   int64_t alive = 0;
   FGA_HIP(hipMemcpyAsync(&alive, s.alive, sizeof alive, hipMemcpyDeviceToHost, st));
   FGA_HIP(hipStreamSynchronize(st));
