@@ -52,8 +52,8 @@ HBM_PEAK = 8.0e12
 # scaled by a 1 GiB copy calibration; valid only while the kernel's source is
 # unchanged (sha256 prefix) and the beam set is the one profiled, else null
 TRAFFIC = {
-    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "262f9ec0539f99f6",
-                   "beams": 33044152, "bytes_per_launch": 2.3741e10},
+    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "0c7a0571f27155e8",
+                   "beams": 33044152, "bytes_per_launch": 2.1412e10},
     "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "b905efd85e76b798",
                   "beams": 33044152, "bytes_per_launch": 9.9295e9},
 }

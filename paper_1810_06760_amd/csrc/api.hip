@@ -427,7 +427,7 @@ EvolvePlan evolve_plan(const fga_beams *b, int nsteps, const fga_evolve_opts *o,
   p.batch = (o && o->batch > 0) ? o->batch : ((int64_t)1 << 22);
   if (p.batch > b->capacity) p.batch = b->capacity > 0 ? b->capacity : 1;
   p.nsamp = r ? nsteps / r->stride : 0;
-  p.bpb = r ? points_beams_per_block(p.batch, r->n, (p.chunk + r->stride - 1) / r->stride + 1) : 1024;
+  p.bpb = r ? points_beams_per_block(p.batch, r->n, (p.chunk + r->stride - 1) / r->stride + 1, 1024) : 1024;
   // with receivers: every 32 steps for large sets (the sort's cost wins over
   // lost locality: 36.0 -> 35.6 s on the 49 M-beam workload), every 16 for
   // small ones (serving requests of 0.1-2.5 M beams)
@@ -744,7 +744,7 @@ size_t fga_reconstruct_points_workspace_bytes(const fga_beams *beams, int64_t n)
   Arena ar(nullptr, 0);
   ar.take<unsigned long long>(1);
   ar.take<double>((size_t)12 * batch);
-  const int bpb = points_beams_per_block(batch, n, 1);
+  const int bpb = points_beams_per_block(batch, n, 1, 64);
   ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
   ar.take<double>((size_t)((batch + 63) / 64) * 6);
   ar.take<double>((size_t)3 * n + 1);
@@ -768,7 +768,7 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
   Arena ar(workspace, workspace_bytes);
   unsigned long long *ctr = ar.take<unsigned long long>(1);
   double *emit = ar.take<double>((size_t)12 * batch);
-  const int bpb = points_beams_per_block(batch, n, 1);
+  const int bpb = points_beams_per_block(batch, n, 1, 64);
   double *partial = ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
   double *box = ar.take<double>((size_t)((batch + 63) / 64) * 6);
   double *xs = ar.take<double>((size_t)3 * n + 1);
@@ -776,7 +776,7 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
   if (!ctr || !emit || !partial || !box || !xs || !perm)
     return fail(FGA_ENOMEM, "reconstruct workspace too small (%zu bytes given, %zu needed)", workspace_bytes, ar.used);
   if (n > 0x7fffffff) return fail(FGA_EUNSUPPORTED, "more than 2^31 points");
-  FGA_HIP(hipMemsetAsync(ctr, 0, sizeof(unsigned long long), st));
+  if (evals) FGA_HIP(hipMemsetAsync(ctr, 0, sizeof(unsigned long long), st));
   if (n > 0 && (s = sort_points(xyz, n, xs, perm, st)) != FGA_OK) return s;
   if (nb == 0) FGA_HIP(launch_reduce_points(partial, 0, 1, n, nullptr, out, 1, 0, 0, st));
   for (int64_t b0 = 0; b0 < nb; b0 += batch) {
@@ -792,7 +792,7 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
     pa.tau = tau;
     pa.partial = partial;
     pa.beams_per_block = bpb;
-    pa.evals = ctr;
+    pa.evals = evals ? ctr : nullptr;
     pa.tile_box = box;
     pa.ntiles = (pa.nb + 63) / 64;
     pa.boxes_ready = 1;
@@ -858,7 +858,7 @@ size_t noalloc_bytes(int64_t batch, int64_t n)
   Arena ar(nullptr, 0);
   ar.take<unsigned long long>(1);
   ar.take<double>((size_t)12 * batch);
-  const int bpb = points_beams_per_block(batch, n, 1);
+  const int bpb = points_beams_per_block(batch, n, 1, 64);
   ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
   ar.take<double>((size_t)((batch + 63) / 64) * 6);
   return ar.used;
@@ -896,12 +896,14 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
   Arena ar(base, kNoAllocScratchBytes);
   unsigned long long *ctr = ar.take<unsigned long long>(1);
   double *emit = ar.take<double>((size_t)12 * batch);
-  const int bpb = points_beams_per_block(batch, n, 1);
+  const int bpb = points_beams_per_block(batch, n, 1, 64);
   double *partial = ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
   double *box = ar.take<double>((size_t)((batch + 63) / 64) * 6);
   if (!ctr || !emit || !partial || !box) return fail(FGA_ENOMEM, "scratch layout does not fit");
-  hipLaunchKernelGGL(k_zero_u64, 1, 64, 0, st, ctr, 1);
-  FGA_HIP(hipGetLastError());
+  if (evals) {
+    hipLaunchKernelGGL(k_zero_u64, 1, 64, 0, st, ctr, 1);
+    FGA_HIP(hipGetLastError());
+  }
   if (nb == 0) FGA_HIP(launch_reduce_points(partial, 0, 1, n, nullptr, out, 1, 0, 0, st));
   for (int64_t b0 = 0; b0 < nb; b0 += batch) {
     const int64_t b1 = b0 + batch < nb ? b0 + batch : nb;
@@ -916,7 +918,7 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
     pa.tau = tau;
     pa.partial = partial;
     pa.beams_per_block = bpb;
-    pa.evals = ctr;
+    pa.evals = evals ? ctr : nullptr;
     pa.tile_box = box;
     pa.ntiles = (pa.nb + 63) / 64;
     pa.boxes_ready = 1;

@@ -129,4 +129,87 @@ __device__ __forceinline__ void cexp_neg_units(const TrigTables &t, double g, do
   im = ex * sphi;
 }
 
+// Tables of cexp_scaled: as TrigTables, with the high word of 2^(j/256) less
+// j 2^12, so that adding k 2^12 to it (k = 256 m + j) adds m to the exponent.
+struct ScaledTables {
+  uint2 e2[TRIG_N];     // (low, high - (j << 12)) words of 2^(j/256)
+  double2 sc[TRIG_N];   // (sin(j pi/128), cos(j pi/128))
+};
+
+__device__ __forceinline__ void fill_tables(ScaledTables &t)
+{
+  for (int j = threadIdx.x; j < TRIG_N; j += blockDim.x) {
+    const double e = exp2((double)j / 256.0);
+    t.e2[j] = make_uint2((unsigned)__double2loint(e), (unsigned)__double2hiint(e) - ((unsigned)j << 12));
+    double s, c;
+    sincospi((double)j / 128.0, &s, &c);
+    t.sc[j] = make_double2(s, c);
+  }
+}
+
+// Coefficients of cexp_scaled's polynomials, held in registers over a loop:
+// the compiler otherwise moves each into a fresh register pair at every use
+// (7 moves in a term of 48 instructions).  An FMA takes one scalar operand, so
+// the first step of each polynomial has its addend in a vector register.
+struct ScaledCoeffs {
+  double e4, e3, e2, e1;  // L^4/24, L^3/6, L^2/2, L with L = ln2/256
+  double s5, s3, s1;      // P^5/120, -P^3/6, P with P = pi/128
+  double c6, c4, c2;      // -P^6/720, P^4/24, -P^2/2
+  __device__ __forceinline__ ScaledCoeffs()
+  {
+    constexpr double L = 0.0027076061740622863, P = PI_128;
+    e4 = L * L * L * L / 24.0;
+    e3 = L * L * L / 6.0;
+    e2 = L * L / 2.0;
+    e1 = L;
+    s5 = P * P * P * P * P / 120.0;
+    s3 = -P * P * P / 6.0;
+    s1 = P;
+    c6 = -P * P * P * P * P * P / 720.0;
+    c4 = P * P * P * P / 24.0;
+    c2 = -P * P / 2.0;
+    asm volatile("" : "+v"(e3), "+v"(s3), "+v"(c4));
+    asm volatile("" : "+s"(e4), "+s"(e2), "+s"(e1), "+s"(s5), "+s"(s1), "+s"(c6), "+s"(c2));
+  }
+};
+
+// in ? exp(-C t ln2/256) (cos(v pi/128) + i sin(v pi/128)) : 0 for nc = -C,
+// t >= 0 and C t < 1022 * 256 (the exponent must stay normal), |v| < 2^51 where
+// in is true; where it is false t >= 0 and v may be any finite values.  The same
+// reductions and polynomials as cexp_neg_units with both arguments in table
+// units: the remainders r = -C t - k (one FMA, exact in t) and w = v - n are in
+// units of ln2/256 and pi/128, which the coefficients carry, and k goes into
+// the exponent by one shift-and-add on the table's high word.
+__device__ __forceinline__ void cexp_scaled(const ScaledTables &tab, const ScaledCoeffs &K, double t, double nc,
+                                            double v, bool in, double &re, double &im)
+{
+  // both table reads first: the polynomials run while they are on their way
+  const double tk = fma(t, nc, RND_MAGIC);
+  const double tn = v + RND_MAGIC;
+  const int k = __double2loint(tk);
+  const uint2 e = tab.e2[k & (TRIG_N - 1)];
+  const double2 scn = tab.sc[__double2loint(tn) & (TRIG_N - 1)];
+  const double kd = tk - RND_MAGIC;
+  const double nd = tn - RND_MAGIC;
+  const double r = fma(t, nc, -kd);
+  const double w = v - nd;  // exact
+  double q = fma(r, K.e4, K.e3);
+  const double w2 = w * w;
+  double sp = fma(w2, K.s5, K.s3);
+  double cp = fma(w2, K.c6, K.c4);
+  q = fma(r, q, K.e2);
+  sp = fma(w2, sp, K.s1);
+  cp = fma(w2, cp, K.c2);
+  q = fma(r, q, K.e1);
+  const double su = w * sp;
+  const double cu = fma(w2, cp, 1.0);
+  q = q * r;  // e^{rL} - 1
+  const double tj = __hiloint2double((int)(((unsigned)k << 12) + e.y), (int)e.x);
+  const double ex = in ? fma(tj, q, tj) : 0.0;
+  const double sphi = fma(su, scn.y, cu * scn.x);
+  const double cphi = fma(cu, scn.y, -(su * scn.x));
+  re = ex * cphi;
+  im = ex * sphi;
+}
+
 }  // namespace fga

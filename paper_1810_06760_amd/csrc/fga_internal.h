@@ -126,9 +126,9 @@ struct PointsArgs {
 };
 hipError_t launch_sum_points(const PointsArgs &a, int *nblk_out, hipStream_t st);
 // beams walked by one point-sum workgroup for nb beams, n points and m samples
-// per launch (a multiple of 64 in [1024, 8192]); partial holds
-// ceil(nb / that) * m * n * 6 doubles
-int points_beams_per_block(int64_t nb, int64_t n, int m);
+// per launch (a multiple of 64 in [least, 8192], least itself a multiple of 64
+// up to 1024); partial holds ceil(nb / that) * m * n * 6 doubles
+int points_beams_per_block(int64_t nb, int64_t n, int m, int least);
 // seis[perm[r]][s0 + s][c] (+)= sum_blk partial[blk][s][r][c]   (perm NULL: identity)
 hipError_t launch_reduce_points(const double *partial, int nblk, int m, int64_t n, const int32_t *perm,
                                 double *out, int64_t out_samples, int s0, int accumulate, hipStream_t st);

@@ -1,19 +1,17 @@
 // Step 3 at scattered points (eq:FGA): receivers and seismograms.
 //
-// Beam-major layout.  A wavefront owns RW = 4 points and walks a range of
-// beams 64 at a time, one beam per lane, each lane holding its beam's
-// emission record (Q, P 128/(pi eps), B = w e^{iS/eps} A) in registers and
-// RW complex 3-vector sums; of the four points, only those whose window
-// holds some beam of the tile are evaluated.  The beam set is kept in
-// Morton order of Q, so the 64 beams of a tile are close together and the
-// window test against one point is (nearly) the same on every lane; a tile
-// whose bounding box lies out of reach of all the wavefront's points is
-// skipped without loading its records.  A workgroup covers one sample, 8 points
-// (two wavefronts) and one beam range; workgroups sharing a beam range are
-// dealt to one XCD so its records are read from HBM once.  After the beam
-// range the sums are reduced over the lanes in a fixed order and written
-// once per wavefront; per-workgroup partials are then reduced in a fixed
-// order, so the sums are bitwise reproducible and need no atomics.
+// Beam-major layout.  A wavefront owns RW points (four, or eight with 32-bit
+// sums) and walks a range of beams 64 at a time, one beam per lane, each lane
+// holding its beam's emission record (Q, P 128/(pi eps), B = w e^{iS/eps} A) in
+// registers and RW complex 3-vector sums.  The beam set is kept in Morton order
+// of Q, so the 64 beams of a tile are close together: the tile's bounding box
+// decides, per point, whether the tile is skipped, summed whole, or summed with
+// a window test per beam.  A workgroup covers one sample, the points of two
+// wavefronts and one beam range; workgroups sharing a beam range are dealt to
+// one XCD so its records are read from HBM once.  After the beam range the sums
+// are reduced over the lanes in a fixed order and written once per wavefront;
+// per-workgroup partials are then reduced in a fixed order, so the sums are
+// bitwise reproducible and need no atomics.
 #include <type_traits>
 
 #include "device_common.h"
@@ -22,15 +20,12 @@
 namespace fga {
 namespace {
 
-constexpr int RW = 4;  // points per wavefront
-constexpr int GRP = RW < 4 ? RW : 4;  // points evaluated together
 // Two wavefronts per workgroup: a new workgroup needs a free wavefront slot
 // on as many SIMDs as it has wavefronts, and the wavefronts of one finish at
 // different times (their points skip different tiles), so smaller workgroups
 // keep more of the four slots per SIMD busy (6 % faster than four, as fast
 // as one; the sums are identical).
-constexpr int WPW = 2;        // wavefronts per workgroup
-constexpr int PG = WPW * RW;  // points per workgroup
+constexpr int WPW = 2;  // wavefronts per workgroup
 
 // Workgroup -> (point group, beam range, sample).  Workgroups are dealt to
 // the 8 XCDs round-robin by id; the point groups of one (beam range, sample)
@@ -58,28 +53,40 @@ constexpr double LOG2E = 1.4426950408889634;
 
 // Summation modes: FP64 throughout; MIXED (FP32 exp / sin / cos, FP64
 // products and sums); MIXED32 (FP32 exp / sin / cos, products and per-lane
-// sums, the lane and block reductions in FP64).
-enum { SUM_FP64 = 0, SUM_MIXED = 1, SUM_MIXED32 = 2 };
+// sums, the lane and block reductions in FP64).  FP64_WIDE: FP64 for windows
+// so wide that exp(-3 tau) leaves the normal range; such exponents are clamped.
+enum { SUM_FP64 = 0, SUM_MIXED = 1, SUM_MIXED32 = 2, SUM_FP64_WIDE = 3 };
+constexpr double MAX_EXPONENT = 700.0;  // the magnitude stays normal up to here
 
-// One term's complex factor exp(-|d|^2/(2 eps) + i P.d/eps), zero outside
-// the window (in false).  Mixed modes: the exponent and the phase (in
-// revolutions, reduced to [-1/2, 1/2]) are formed in FP64, then exp2 / sin /
-// cos run on the FP32 transcendental unit.  FP64: the table-driven
-// exponential.  T is the accumulation type (float only for MIXED32).
+// Points per wavefront.  FP64 sums take 12 registers a point: four points fit
+// four wavefronts per SIMD (122 registers); eight fit three and lose what the
+// halved record reads give (33 M beams, 256 points: 25.3 against 27.8 ms per
+// launch).  With 32-bit sums eight points fit as well as four, and each tile's
+// records are read half as often: a launch over 524 k beams, 8 samples and 385
+// points takes 1.83 ms with eight and 2.35 ms with four.
+constexpr int points_per_wave(int mode) { return mode == SUM_MIXED32 ? 8 : 4; }
+
+// One term's complex factor exp(-|d|^2/(2 eps) + i P.d/eps), zero outside the
+// window (in false); v: the phase in units of pi/128 (FP64 sums) or of 2 pi.  Mixed
+// modes: the exponent and the phase (reduced to [-1/2, 1/2] revolutions) are
+// formed in FP64, then exp2 / sin / cos run on the FP32 transcendental unit.
+// FP64: the table-driven exponential.  nc: minus the exponent's scale for |d|^2
+// in the units that the exponential takes (ln2/256, or ln2 for the mixed modes).
+// T is the accumulation type (float only for MIXED32).
 template <int MODE, typename T>
-__device__ __forceinline__ void point_term(const TrigTables &tab, const double (&dd)[3], const double (&pe)[3],
-                                           bool in, double hieps, T &er, T &ei)
+__device__ __forceinline__ void point_term(const ScaledTables &tab, const ScaledCoeffs &K, const double (&dd)[3],
+                                           const double (&pe)[3], double nc, double tmax, bool in, T &er, T &ei)
 {
-  const double g = (dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]) * hieps;
-  const double v = pe[0] * dd[0] + pe[1] * dd[1] + pe[2] * dd[2];  // phase in units of pi/128
-  if constexpr (MODE != SUM_FP64) {
-    const double rev = v * (1.0 / 256.0);
-    const float r = (float)(rev - rint(rev));
-    const float amp = in ? __builtin_amdgcn_exp2f((float)(-g * LOG2E)) : 0.0f;
+  double t = dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2];
+  const double v = pe[0] * dd[0] + pe[1] * dd[1] + pe[2] * dd[2];
+  if constexpr (MODE == SUM_MIXED || MODE == SUM_MIXED32) {
+    const float r = (float)(v - rint(v));
+    const float amp = in ? __builtin_amdgcn_exp2f((float)(t * nc)) : 0.0f;
     er = (T)(amp * __builtin_amdgcn_cosf(r));
     ei = (T)(amp * __builtin_amdgcn_sinf(r));
   } else {
-    cexp_neg_units(tab, g, v, in, er, ei);
+    if constexpr (MODE == SUM_FP64_WIDE) t = fmin(t, tmax);
+    cexp_scaled(tab, K, t, nc, v, in, er, ei);
   }
 }
 
@@ -94,21 +101,78 @@ __device__ __forceinline__ void accumulate_term(T (&u)[6], const T (&B)[6], T er
   }
 }
 
-// MODE: SUM_FP64, SUM_MIXED or SUM_MIXED32 (the term and its sum as stated
-// at point_term; MIXED32 holds the tile's records B and the sums in FP32).
+// Sums 24 values over the 64 lanes, halving the values held with the lanes
+// summed: a swap of half-waves (then of 16-lane rows) leaves each half with one
+// of two values' sums, so the first two levels take 18 additions and 36 swaps in
+// place of 48 and 96, and the last four run within the rows by DPP.  Row g of
+// the wavefront (lanes 16 g ..) ends with the totals of six values in all of its
+// lanes: value 12 (g / 2) + 6 (g % 2) + i in out[i].
+__device__ __forceinline__ double swap_add32(double a, double b)
+{
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false,
+                                                   false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false,
+                                                   false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double a, double b)
+{
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false,
+                                                   false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false,
+                                                   false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+template <int ROR> __device__ __forceinline__ double row_add(double a)
+{
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(a), 0x120 + ROR, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(a), 0x120 + ROR, 0xf, 0xf, true);
+  return a + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ void reduce24(const double (&v)[24], double (&out)[6])
+{
+  double h[12];
+#pragma unroll
+  for (int i = 0; i < 12; ++i) h[i] = swap_add32(v[i], v[12 + i]);
+#pragma unroll
+  for (int i = 0; i < 6; ++i) {
+    double t = swap_add16(h[i], h[6 + i]);
+    t = row_add<8>(t);
+    t = row_add<4>(t);
+    t = row_add<2>(t);
+    out[i] = row_add<1>(t);
+  }
+}
+
+// MODE: one of the SUM_ modes (the term and its sum as stated at point_term;
+// MIXED32 holds the tile's records B and the sums in FP32).
+//
+// Bound by vector issue (busy in 79 % of the cycles on 66 k beams x 16 samples
+// x 512 points): a term inside the window costs 48 instructions, 12 of them the
+// accumulation, and reads 24 bytes of tables.  What a term does not need is
+// decided per tile by one lane each, 64 tiles at a time: a point whose window the
+// tile's box misses is not visited, and one whose window holds the whole box is
+// summed without the window test and mask.  With 63 instructions a term and the
+// test on every beam the same launch took 1.36 ms; it takes 1.14 ms, and one over
+// 4.1 M beams x 16 samples x 256 points 25.3 ms in place of 29.9.
 template <int MODE>
 __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) void k_sum_points(PointsArgs a, int groups, int64_t nblk)
 {
   using Acc = typename std::conditional<MODE == SUM_MIXED32, float, double>::type;
-  __shared__ TrigTables tab;
-  fill_tables(tab);
-  __syncthreads();
+  constexpr int RW = points_per_wave(MODE), PG = RW * WPW;
+  constexpr bool MIXED = MODE == SUM_MIXED || MODE == SUM_MIXED32;
+  __shared__ ScaledTables tab;
+  if constexpr (!MIXED) {
+    fill_tables(tab);
+    __syncthreads();
+  }
 
   const PointsWork wk = points_work(blockIdx.x, groups, nblk, a.m);
   if (!wk.valid) return;  // whole workgroup: padding of the last XCD round
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: points live in SGPRs
   const int64_t r0 = (int64_t)wk.pg * PG + w * RW;
+  if (r0 >= a.n) return;  // no point of this wavefront exists (no barrier follows)
   double xr[RW][3];
 #pragma unroll
   for (int k = 0; k < RW; ++k)
@@ -116,10 +180,14 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
     for (int d = 0; d < 3; ++d) xr[k][d] = r0 + k < a.n ? a.xyz[3 * (r0 + k) + d] : 1.0e30;
   const double R = sqrt(2.0 * a.tau * a.eps);
   const double hieps = 0.5 / a.eps;
+  const double nc = -hieps * (MIXED ? LOG2E : INV_LN2_256);
+  const double tmax = MAX_EXPONENT / hieps;
   const int64_t b0 = wk.blk * a.beams_per_block;
   const int64_t b1 = b0 + a.beams_per_block < a.nb ? b0 + a.beams_per_block : a.nb;
   const int s = wk.s;
   const double *E = a.emit + (int64_t)s * 12 * a.nb;
+  const double *TB = a.tile_box + (int64_t)s * a.ntiles * 6;
+  const ScaledCoeffs K;
   uint64_t cnt = 0;          // wave-uniform in-window count
   Acc u[RW][6];
 #pragma unroll
@@ -127,115 +195,111 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
     for (int c = 0; c < 6; ++c) u[k][c] = (Acc)0;
 
-  // bounding box of the wavefront's points; a beam tile whose box lies more
-  // than R away from it along some axis holds no term for any of them (the
-  // rounded differences are monotone, so this agrees with the per-lane test)
-  double plo[3], phi[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    plo[d] = xr[0][d];
-    phi[d] = xr[0][d];
-#pragma unroll
-    for (int k = 1; k < RW; ++k)
-      if (r0 + k < a.n) {
-        plo[d] = fmin(plo[d], xr[k][d]);
-        phi[d] = fmax(phi[d], xr[k][d]);
-      }
-  }
-  const double *TB = a.tile_box + (int64_t)s * a.ntiles * 6;
-  // The range's tiles are tested 64 at a time, one per lane (box loads in
-  // parallel), and walked through the ballot of the live ones; a tile whose
-  // box lies more than R from the points' box along an axis is skipped.
   const int64_t tb0 = b0 >> 6, tb1 = (b1 + 63) >> 6;  // b0 is a multiple of 64
-  int64_t mbase = -1;
-  uint64_t mask = 0;
-  auto next_live = [&](int64_t t0) {  // first beam of the next live tile at or after t0, else b1
-    int64_t t = t0 >> 6;
-    while (t < tb1) {
-      const int64_t base = t & ~(int64_t)63;
-      if (base != mbase) {
-        const int64_t tt = base + lane;
-        bool ok = false;
-        if (tt >= tb0 && tt < tb1) {
-          const double *tb = TB + tt * 6;  // lo[3], hi[3]
-          ok = true;
+  for (int64_t base = tb0; base < tb1; base += 64) {
+    // Lane = tile.  A tile whose box lies more than R away from the point along
+    // some axis holds no term of it; one whose corners are all within R of it
+    // holds only terms in its window (the rounded differences are monotone, so
+    // both agree with the per-beam test).  A tile without live beams has an
+    // empty box (+inf / -inf): neither.
+    uint64_t reach[RW], whole[RW], any = 0;
+    {
+      const int64_t tt = base + lane;
+      const bool ok = tt < tb1;
+      double lo[3], hi[3];
 #pragma unroll
-          for (int d = 0; d < 3; ++d) ok = ok && !(tb[d] - phi[d] > R) && !(plo[d] - tb[3 + d] > R);
-        }
-        mask = __ballot(ok);
-        mbase = base;
+      for (int d = 0; d < 3; ++d) {
+        lo[d] = ok ? TB[tt * 6 + d] : INFINITY;
+        hi[d] = ok ? TB[tt * 6 + 3 + d] : -INFINITY;
       }
-      const uint64_t rest = mask >> (t - base);
-      if (rest) return (t + __ffsll((long long)rest) - 1) << 6;
-      t = base + 64;
-    }
-    return b1;
-  };
-  // records of the lane's beam for the current tile
-  double q[3], pe[3];
-  Acc B[6];
-  auto fetch = [&](int64_t t0) {
-    const int64_t j = t0 + lane;
-    const bool v = j < b1;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      q[d] = v ? E[d * a.nb + j] : -1.0e300;
-      pe[d] = v ? E[(3 + d) * a.nb + j] : 0.0;
-    }
+      for (int k = 0; k < RW; ++k) {
+        bool rch = true, whl = true;
 #pragma unroll
-    for (int c = 0; c < 6; ++c) B[c] = v ? (Acc)E[(6 + c) * a.nb + j] : (Acc)0;
-  };
-  for (int64_t t0 = next_live(b0); t0 < b1; t0 = next_live(t0 + 64)) {
-    fetch(t0);
-    // points four at a time: when every one of the four windows holds some
-    // lane's beam, the four terms are evaluated together (four independent
-    // exponential chains per lane hide each other's latency); otherwise only
-    // the points whose window holds a beam of the tile, one chain each.
-    // Outside its window a term's magnitude is replaced by zero, so skipping
-    // a point no lane reaches changes no sum.
-#pragma unroll
-    for (int k = 0; k < RW; k += GRP) {
-      double dd[GRP][3];
-      bool in[GRP];
-      unsigned need = 0;  // wave-uniform: points with at least one lane in window
-#pragma unroll
-      for (int h = 0; h < GRP; ++h) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) dd[h][d] = xr[k + h][d] - q[d];
-        in[h] = fmax(fabs(dd[h][0]), fmax(fabs(dd[h][1]), fabs(dd[h][2]))) <= R;  // false for an all-NaN offset
-        const uint64_t bal = __ballot(in[h]);
-        cnt += __popcll(bal);
-        need |= bal ? 1u << h : 0u;
-      }
-      if (!need) continue;
-#pragma unroll
-      for (int h = 0; h < GRP; ++h)
-        if (need & (1u << h)) {
-          Acc er, ei;
-          point_term<MODE>(tab, dd[h], pe, in[h], hieps, er, ei);
-          accumulate_term(u[k + h], B, er, ei);
+        for (int d = 0; d < 3; ++d) {
+          const double dl = xr[k][d] - lo[d], dh = xr[k][d] - hi[d];
+          rch = rch && !(-dl > R) && !(dh > R);
+          whl = whl && fabs(dl) <= R && fabs(dh) <= R;
         }
+        reach[k] = __ballot(rch);
+        whole[k] = __ballot(whl);
+        any |= reach[k];
+      }
+    }
+    for (; any; any &= any - 1) {
+      const int bit = __ffsll((long long)any) - 1;
+      // records of the lane's beam: 12 loads off wave-uniform addresses, all in
+      // flight together (the last lanes of a ragged tile read its last beam's)
+      const int64_t t0 = (base + bit) << 6;
+      const int left = (int)(b1 - t0 < 64 ? b1 - t0 : 64);
+      const unsigned jl = lane < left ? lane : left - 1;
+      const double *Et = E + t0;
+      double q[3], pe[3], Bd[6];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        q[d] = (Et + d * a.nb)[jl];
+        pe[d] = (Et + (3 + d) * a.nb)[jl];
+      }
+#pragma unroll
+      for (int c = 0; c < 6; ++c) Bd[c] = (Et + (6 + c) * a.nb)[jl];
+      // dead beams and the ragged tail take a corner of the box as their place,
+      // without phase or weight
+      const bool mine = q[0] > -1.0e299 && lane < left;
+      const uint64_t live = __ballot(mine);
+      if (live != ~0ull) {
+        const double *tb = TB + (base + bit) * 6;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const double corner = tb[d];
+          q[d] = mine ? q[d] : corner;
+          pe[d] = mine ? pe[d] : 0.0;
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) Bd[c] = mine ? Bd[c] : 0.0;
+      }
+      Acc B[6];
+#pragma unroll
+      for (int c = 0; c < 6; ++c) B[c] = (Acc)Bd[c];
+      if constexpr (MIXED) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) pe[d] *= 1.0 / 256.0;  // exact: from units of pi/128 to revolutions
+      }
+#pragma unroll
+      for (int k = 0; k < RW; ++k) {
+        if (!((reach[k] >> bit) & 1)) continue;
+        double dd[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) dd[d] = xr[k][d] - q[d];
+        Acc er, ei;
+        if ((whole[k] >> bit) & 1) {
+          point_term<MODE>(tab, K, dd, pe, nc, tmax, true, er, ei);
+          cnt += __popcll(live);
+        } else {
+          const bool in = (fabs(dd[0]) <= R) & (fabs(dd[1]) <= R) & (fabs(dd[2]) <= R);
+          const uint64_t bal = __ballot(in) & live;
+          if (!bal) continue;
+          cnt += __popcll(bal);
+          point_term<MODE>(tab, K, dd, pe, nc, tmax, in, er, ei);
+        }
+        accumulate_term(u[k], B, er, ei);
+      }
     }
   }
-  // lane reduction in FP64 in a fixed butterfly order; every lane ends with the total
-  double ud[RW][6];
+  // lane reduction in FP64 in a fixed order, four points at a time
+  const int g = lane >> 4, c = lane & 15;
 #pragma unroll
-  for (int k = 0; k < RW; ++k)
+  for (int h = 0; h < RW; h += 4) {
+    double all[24], tot[6];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      double v = (double)u[k][c];
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-      ud[k][c] = v;
-    }
-  if (lane < RW * 6) {
-    const int k = lane / 6, c = lane % 6;
-    double v = 0.0;
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-    for (int kk = 0; kk < RW; ++kk)
+      for (int cc = 0; cc < 6; ++cc) all[k * 6 + cc] = (double)u[h + k][cc];
+    reduce24(all, tot);
+    // row g holds the six sums of point h + g; lane c of the row writes component c
+    double v = tot[0];
 #pragma unroll
-      for (int cc = 0; cc < 6; ++cc)
-        if (kk == k && cc == c) v = ud[kk][cc];
-    if (r0 + k < a.n) a.partial[((wk.blk * a.m + s) * a.n + r0 + k) * 6 + c] = v;
+    for (int i = 1; i < 6; ++i) v = c == i ? tot[i] : v;
+    if (c < 6 && r0 + h + g < a.n) a.partial[((wk.blk * a.m + s) * a.n + r0 + h + g) * 6 + c] = v;
   }
   if (a.evals && lane == 0 && cnt) atomicAdd(a.evals, (unsigned long long)cnt);
 }
@@ -313,15 +377,24 @@ __global__ __launch_bounds__(64 * RG) void k_reduce_points(const double *__restr
 
 }  // namespace
 
-int points_beams_per_block(int64_t nb, int64_t n, int m)
+int points_beams_per_block(int64_t nb, int64_t n, int m, int least)
 {
   // enough workgroups (about 8192) that the last partial round of resident
-  // workgroups is a small fraction of the launch; ranges are whole 64-beam tiles
+  // workgroups is a small fraction of the launch; ranges are whole 64-beam tiles.
+  // Sums too small for 8192 ranges of 1024 beams take shorter ranges, down to
+  // `least`, until the chip holds one workgroup per slot (about 2048): beyond
+  // that a workgroup's tables and final reduction (about 500 instructions, against
+  // 200 for a tile) outweigh what the extra workgroups give.
+  constexpr int PG = 4 * WPW;  // the FP64 sums' points per workgroup, for every mode
   const int64_t groups = (n + PG - 1) / PG;
   const int64_t pairs = nb * groups * (m > 0 ? m : 1);
   int64_t bpb = (pairs + 8191) / 8192;
+  if (bpb < 1024) {
+    const int64_t fill = (pairs + 2047) / 2048 < 1024 ? (pairs + 2047) / 2048 : 1024;
+    bpb = fill > bpb ? fill : bpb;
+  }
   bpb = (bpb + 63) / 64 * 64;
-  if (bpb < 1024) bpb = 1024;
+  if (bpb < least) bpb = least;
   if (bpb > 8192) bpb = 8192;
   return (int)bpb;
 }
@@ -340,15 +413,20 @@ hipError_t launch_sum_points(const PointsArgs &a, int *nblk_out, hipStream_t st)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
+  const int mode = a.precision == FGA_FP32 ? SUM_MIXED : (a.precision == FGA_FP32_ACC32 ? SUM_MIXED32 : SUM_FP64);
+  const int PG = points_per_wave(mode) * WPW;
   const int groups = (int)((a.n + PG - 1) / PG);
   const int64_t units = (nblk * a.m + 7) / 8 * 8;
   const int64_t nwg = units * groups;
   if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
   ProfScope prof(FGA_K_SUM_POINTS, st);
+  const bool wide = 3.0 * a.tau > MAX_EXPONENT - 1.0;  // an offset in the window has |d|^2 <= 3 R^2
   if (a.precision == FGA_FP32)
     hipLaunchKernelGGL(k_sum_points<SUM_MIXED>, dim3((unsigned)nwg), 64 * WPW, 0, st, a, groups, nblk);
   else if (a.precision == FGA_FP32_ACC32)
     hipLaunchKernelGGL(k_sum_points<SUM_MIXED32>, dim3((unsigned)nwg), 64 * WPW, 0, st, a, groups, nblk);
+  else if (wide)
+    hipLaunchKernelGGL(k_sum_points<SUM_FP64_WIDE>, dim3((unsigned)nwg), 64 * WPW, 0, st, a, groups, nblk);
   else
     hipLaunchKernelGGL(k_sum_points<SUM_FP64>, dim3((unsigned)nwg), 64 * WPW, 0, st, a, groups, nblk);
   return hipGetLastError();
