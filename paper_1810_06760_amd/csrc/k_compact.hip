@@ -5,33 +5,49 @@
 
 namespace fga {
 
-// Exclusive scan of n int64 values by one workgroup of 1024 threads; each
-// thread scans a contiguous chunk.  total (device) receives the sum.
+// Exclusive scan of n int64 values by one workgroup of 1024 threads, 4096
+// consecutive values at a time (four per thread, read coalesced; the wavefronts
+// scan their sums by shuffles, then their totals).  in and out may be the same
+// array.  total (device) receives the sum.
 namespace {
-__global__ __launch_bounds__(1024) void k_scan_exclusive(const int64_t *__restrict__ in, int64_t *__restrict__ out,
-                                                         int64_t n, int64_t *__restrict__ total)
+__global__ __launch_bounds__(1024) void k_scan_exclusive(const int64_t *in, int64_t *out, int64_t n,
+                                                         int64_t *__restrict__ total)
 {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
-  const int64_t per = (n + 1023) / 1024;
-  const int64_t b = t * per, e = b + per < n ? b + per : n;
-  int64_t s = 0;
-  for (int64_t i = b; i < e; ++i) s += in[i];
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    int64_t v = t >= off ? part[t - off] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
+  __shared__ int64_t wsum[2][16];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  int64_t carry = 0;
+  int buf = 0;
+  for (int64_t b = 0; b < n; b += 4096, buf ^= 1) {
+    int64_t v[4], s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = b + 4 * t + k;
+      v[k] = i < n ? in[i] : 0;
+      s += v[k];
+    }
+    int64_t incl = s;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int64_t x = __shfl_up(incl, off);
+      if (lane >= off) incl += x;
+    }
+    if (lane == 63) wsum[buf][w] = incl;
+    __syncthreads();  // the two buffers make one barrier per turn enough
+    int64_t before = carry, all = 0;
+    for (int k = 0; k < 16; ++k) {
+      const int64_t x = wsum[buf][k];
+      if (k < w) before += x;
+      all += x;
+    }
+    int64_t run = before + incl - s;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = b + 4 * t + k;
+      if (i < n) out[i] = run;
+      run += v[k];
+    }
+    carry += all;
   }
-  int64_t run = part[t] - s;
-  for (int64_t i = b; i < e; ++i) {
-    const int64_t v = in[i];
-    out[i] = run;
-    run += v;
-  }
-  if (t == 1023) *total = part[1023];
+  if (t == 0) *total = carry;
 }
 
 }  // namespace

@@ -10,6 +10,8 @@
 // with a, b, g the (q, p) pair index of each axis (a = iq*np + ip).  Beams
 // are then made per candidate lineage number, culled by |psi| and written in
 // lineage order with an order-preserving compaction.
+#include <algorithm>
+
 #include "device_common.h"
 
 namespace fga {
@@ -41,30 +43,115 @@ struct GemmDesc {
   int64_t bA, bB, bC;
 };
 
-// C = A B for complex matrices given by element strides, batched over blockIdx.z.
+// C = A B for complex matrices given by element strides, batched over
+// blockIdx.z, on the FP64 matrix cores (v_mfma_f64_16x16x4_f64).
+//
+// Bound by the matrix cores once the operands come from LDS: a workgroup takes
+// 64 x 64 outputs (WT = 2), each of its four wavefronts 32 x 32 of them as 2 x 2
+// matrix tiles, Re C += Re A Re B - Im A Im B and Im C += Re A Im B + Im A Re B,
+// so a K step of four costs four 16-byte LDS reads per lane for sixteen matrix
+// instructions; products too small to fill the chip with such tiles take 32 x 32
+// (WT = 1).  The slabs lie [k][row] and [k][column]: a matrix operand's
+// sixteen rows are consecutive entries.  The next slab's global loads are in
+// flight while the matrix cores take the current one.  The three products of a
+// 128^3 field with 256 (q, p) pairs per axis (90 GFLOP) take 1.68 ms, 54 TFLOP/s;
+// with one output per thread on the vector unit they took 4.4 ms.
+typedef double d4 __attribute__((ext_vector_type(4)));
+constexpr int GK = 16;  // K slab
+template <int WT>
 __global__ __launch_bounds__(256) void k_cgemm(const double2 *__restrict__ A, const double2 *__restrict__ B,
                                                double2 *__restrict__ C, GemmDesc d)
 {
-  __shared__ double2 As[16][17], Bs[16][17];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int64_t i = (int64_t)blockIdx.y * 16 + ty, j = (int64_t)blockIdx.x * 16 + tx;
+  constexpr int GT = 32 * WT;        // workgroup tile edge
+  constexpr int NE = GK * GT / 256;  // entries of each slab per thread
+  __shared__ double2 As[GK][GT + 1], Bs[GK][GT + 1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, kq = lane >> 4;
+  const int64_t i0 = (int64_t)blockIdx.y * GT, j0 = (int64_t)blockIdx.x * GT;
   A += d.bA * blockIdx.z;
   B += d.bB * blockIdx.z;
   C += d.bC * blockIdx.z;
-  double cr = 0.0, ci = 0.0;
-  for (int64_t k0 = 0; k0 < d.K; k0 += 16) {
-    As[ty][tx] = (i < d.M && k0 + tx < d.K) ? A[i * d.sAi + (k0 + tx) * d.sAk] : make_double2(0.0, 0.0);
-    Bs[ty][tx] = (k0 + ty < d.K && j < d.N) ? B[(k0 + ty) * d.sBk + j * d.sBj] : make_double2(0.0, 0.0);
+  // this thread's entries of each slab; along k for an operand whose k
+  // entries are adjacent in memory (A always, B in the first product), else
+  // along the columns
+  const bool bk = d.sBk == 1;
+  // (indexes past an edge are clamped: every load goes out unconditionally,
+  // rows and columns outside C are not stored, and k past K is made zero)
+  int ka[NE], ra[NE], kb[NE], rb[NE];
+  const double2 *Ap[NE], *Bp[NE];
+#pragma unroll
+  for (int t = 0; t < NE; ++t) {
+    const int e = tid + 256 * t;
+    ka[t] = e & (GK - 1);
+    ra[t] = e / GK;
+    kb[t] = bk ? ka[t] : e / GT;
+    rb[t] = bk ? ra[t] : e & (GT - 1);
+    const int64_t i = i0 + ra[t] < d.M ? i0 + ra[t] : d.M - 1, j = j0 + rb[t] < d.N ? j0 + rb[t] : d.N - 1;
+    Ap[t] = A + i * d.sAi;
+    Bp[t] = B + j * d.sBj;
+  }
+  double2 pa[NE], pb[NE];
+  auto fetch = [&](int64_t k0) {
+#pragma unroll
+    for (int t = 0; t < NE; ++t) {
+      const int64_t k = k0 + ka[t] < d.K ? k0 + ka[t] : d.K - 1, l = k0 + kb[t] < d.K ? k0 + kb[t] : d.K - 1;
+      pa[t] = Ap[t][k * d.sAk];
+      pb[t] = Bp[t][l * d.sBk];
+    }
+  };
+  const int wi = 16 * WT * (w >> 1), wj = 16 * WT * (w & 1);
+  const bool any = i0 + wi < d.M && j0 + wj < d.N;  // wave-uniform: some output of this wavefront exists
+  d4 cr[WT][WT], ci[WT][WT];
+#pragma unroll
+  for (int a = 0; a < WT; ++a)
+#pragma unroll
+    for (int b = 0; b < WT; ++b) cr[a][b] = ci[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  fetch(0);
+  for (int64_t k0 = 0; k0 < d.K; k0 += GK) {
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      const double2 a = As[ty][kk], b = Bs[kk][tx];
-      cr += a.x * b.x - a.y * b.y;
-      ci += a.x * b.y + a.y * b.x;
+    for (int t = 0; t < NE; ++t) {
+      const bool az = k0 + ka[t] < d.K, bz = k0 + kb[t] < d.K;
+      As[ka[t]][ra[t]] = make_double2(az ? pa[t].x : 0.0, az ? pa[t].y : 0.0);
+      Bs[kb[t]][rb[t]] = make_double2(bz ? pb[t].x : 0.0, bz ? pb[t].y : 0.0);
     }
     __syncthreads();
+    if (k0 + GK < d.K) fetch(k0 + GK);
+    if (!any) continue;
+#pragma unroll
+    for (int ks = 0; ks < GK; ks += 4) {
+      double2 av[WT], bv[WT];
+#pragma unroll
+      for (int a = 0; a < WT; ++a) av[a] = As[ks + kq][wi + 16 * a + li];
+#pragma unroll
+      for (int b = 0; b < WT; ++b) bv[b] = Bs[ks + kq][wj + 16 * b + li];
+#pragma unroll
+      for (int a = 0; a < WT; ++a)
+#pragma unroll
+        for (int b = 0; b < WT; ++b) {
+          cr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].x, bv[b].x, cr[a][b], 0, 0, 0);
+          ci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].x, bv[b].y, ci[a][b], 0, 0, 0);
+        }
+#pragma unroll
+      for (int a = 0; a < WT; ++a)
+#pragma unroll
+        for (int b = 0; b < WT; ++b) {
+          cr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-av[a].y, bv[b].y, cr[a][b], 0, 0, 0);
+          ci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a].y, bv[b].x, ci[a][b], 0, 0, 0);
+        }
+    }
   }
-  if (i < d.M && j < d.N) C[i * d.sCi + j * d.sCj] = make_double2(cr, ci);
+  // result register r of lane holds D[lane / 16 + 4 r][lane % 16]
+#pragma unroll
+  for (int a = 0; a < WT; ++a)
+#pragma unroll
+    for (int b = 0; b < WT; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t i = i0 + wi + 16 * a + kq + 4 * r, j = j0 + wj + 16 * b + li;
+        if (i < d.M && j < d.N) C[i * d.sCi + j * d.sCj] = make_double2(cr[a][b][r], ci[a][b][r]);
+      }
 }
 
 // h_b(y) = g(y) / c_b(y) on the quadrature mesh, for b = P (out[0]) and S (out[1]).
@@ -87,9 +174,13 @@ __global__ __launch_bounds__(256) void k_div_speed(DevMedium med, const double2 
       while (layer < med.nlayer - 1 && x[2] > med.bound[layer]) ++layer;
     }
   }
+  double c0 = 0.0;
   for (int sp = 0; sp < 2; ++sp) {
     double c, gr[3], H[6];
-    medium_eval<MK>(med, sp, layer, x, c, gr, H);
+    // one node field: c_S is the ratio times the c_P already interpolated
+    if ((MK == MK_GRID || MK == MK_GRID3) && sp && !med.two_fields) c = med.cs_ratio * c0;
+    else medium_eval<MK>(med, sp, layer, x, c, gr, H);
+    c0 = c;
     for (int comp = 0; comp < 3; ++comp) {
       const double2 v = g[comp * plane + id];
       out[(sp * 3 + comp) * plane + id] = make_double2(v.x / c, v.y / c);
@@ -111,6 +202,14 @@ struct BeamInit {
   double bound[FGA_MAX_LAYERS];
 };
 
+// Branch and direction of lineage L; false if L is not a candidate.
+__device__ __forceinline__ bool is_candidate(const BeamInit &a, int64_t L, int &br, int &dir)
+{
+  br = (int)(L / (2 * a.Np * a.Nq));
+  dir = (int)((L / (a.Np * a.Nq)) % 2);
+  return ((a.mask >> br) & 1) && !(a.one_way && dir == 1) && !(a.merge && br == 2);
+}
+
 // psi of candidate lineage L; returns false if L is not a candidate.  With
 // a.merge the SV candidates are not candidates, and an SH candidate also
 // returns the psi of its SV partner (s2r, s2i) for the merged beam.
@@ -118,10 +217,9 @@ __device__ __forceinline__ bool candidate_psi(const BeamInit &a, int64_t L, doub
                                               double e[3], double &psr, double &psi, double &s2r, double &s2i,
                                               int &br, int &sg)
 {
-  br = (int)(L / (2 * a.Np * a.Nq));
-  const int dir = (int)((L / (a.Np * a.Nq)) % 2);
+  int dir;
+  if (!is_candidate(a, L, br, dir)) return false;
   const int64_t ip = (L / a.Nq) % a.Np, iq = L % a.Nq;
-  if (!((a.mask >> br) & 1) || (a.one_way && dir == 1) || (a.merge && br == 2)) return false;
   sg = dir == 0 ? 1 : -1;
   int iqd[3] = {(int)(iq % a.nq[0]), (int)((iq / a.nq[0]) % a.nq[1]), (int)(iq / ((int64_t)a.nq[0] * a.nq[1]))};
   int ipd[3] = {(int)(ip % a.np[0]), (int)((ip / a.np[0]) % a.np[1]), (int)(ip / ((int64_t)a.np[0] * a.np[1]))};
@@ -198,34 +296,44 @@ __device__ __forceinline__ bool kept(const BeamInit &a, int br, double pr, doubl
   return k1 || !(sqrt(s2r * s2r + s2i * s2i) < a.cull);
 }
 
-__global__ __launch_bounds__(256) void k_beam_count(BeamInit a, int64_t *__restrict__ counts)
+// Kept candidates, counted in runs of 256 in lineage order.  A block takes
+// `per` runs (2 .. 8, so that one workgroup scans few block counts): first[run]
+// is the number kept in the block's earlier runs, counts[block] the block's sum.
+constexpr int MAX_RUNS = 8;
+__global__ __launch_bounds__(256) void k_beam_count(BeamInit a, int per, int64_t nrun, int64_t *__restrict__ first,
+                                                    int64_t *__restrict__ counts)
 {
-  const int64_t L = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  bool keep = false;
-  if (L < a.ncand) {
-    double q[3], p[3], e[3], pr, pi, s2r, s2i;
-    int br, sg;
-    if (candidate_psi(a, L, q, p, e, pr, pi, s2r, s2i, br, sg)) keep = kept(a, br, pr, pi, s2r, s2i);
+  __shared__ int kept_of[MAX_RUNS][4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int k = 0; k < per; ++k) {
+    const int64_t L = ((int64_t)blockIdx.x * per + k) * 256 + threadIdx.x;
+    bool keep = false;
+    if (L < a.ncand) {
+      double q[3], p[3], e[3], pr, pi, s2r, s2i;
+      int br, sg;
+      if (!(a.cull > 0.0)) keep = is_candidate(a, L, br, sg);  // nothing is culled: psi is not needed
+      else if (candidate_psi(a, L, q, p, e, pr, pi, s2r, s2i, br, sg)) keep = kept(a, br, pr, pi, s2r, s2i);
+    }
+    const int n = __popcll(__ballot(keep));
+    if (lane == 0) kept_of[k][w] = n;
   }
-  int total;
-  block_rank(keep, &total);
-  if (threadIdx.x == 0) counts[blockIdx.x] = total;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t sum = 0;
+    for (int k = 0; k < per; ++k) {
+      const int64_t run = (int64_t)blockIdx.x * per + k;
+      if (run < nrun) first[run] = sum;
+      sum += kept_of[k][0] + kept_of[k][1] + kept_of[k][2] + kept_of[k][3];
+    }
+    counts[blockIdx.x] = sum;
+  }
 }
 
-__global__ __launch_bounds__(256) void k_beam_write(BeamInit a, const int64_t *__restrict__ offs, double *__restrict__ F,
-                                                    int32_t *__restrict__ I, int64_t *__restrict__ lineage, int64_t cap)
+__device__ __forceinline__ void write_beam(const BeamInit &a, int64_t L, int64_t i, const double q[3], const double p[3],
+                                           const double e[3], double pr, double pi, double s2r, double s2i, int br,
+                                           int sg, double *__restrict__ F, int32_t *__restrict__ I,
+                                           int64_t *__restrict__ lineage, int64_t cap)
 {
-  const int64_t L = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  bool keep = false;
-  double q[3], p[3], e[3], pr = 0, pi = 0, s2r = 0, s2i = 0;
-  int br = 0, sg = 1;
-  if (L < a.ncand) {
-    if (candidate_psi(a, L, q, p, e, pr, pi, s2r, s2i, br, sg)) keep = kept(a, br, pr, pi, s2r, s2i);
-  }
-  int total;
-  const int r = block_rank(keep, &total);
-  if (!keep) return;
-  const int64_t i = offs[blockIdx.x] + r;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     F[(FGA_Q + d) * cap + i] = q[d];
@@ -276,6 +384,24 @@ __global__ __launch_bounds__(256) void k_beam_write(BeamInit a, const int64_t *_
   lineage[i] = L;
 }
 
+__global__ __launch_bounds__(256) void k_beam_write(BeamInit a, int per, const int64_t *__restrict__ first,
+                                                    const int64_t *__restrict__ offs, double *__restrict__ F,
+                                                    int32_t *__restrict__ I, int64_t *__restrict__ lineage, int64_t cap)
+{
+  const int64_t L = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  bool keep = false;
+  double q[3], p[3], e[3], pr = 0, pi = 0, s2r = 0, s2i = 0;
+  int br = 0, sg = 1;
+  if (L < a.ncand) {
+    if (candidate_psi(a, L, q, p, e, pr, pi, s2r, s2i, br, sg)) keep = kept(a, br, pr, pi, s2r, s2i);
+  }
+  int total;
+  const int r = block_rank(keep, &total);
+  if (!keep) return;
+  write_beam(a, L, offs[blockIdx.x / per] + first[blockIdx.x] + r, q, p, e, pr, pi, s2r, s2i, br, sg, F, I, lineage,
+             cap);
+}
+
 struct FbiPlan {
   int na[3];
   int64_t t1, t2, ft, tab[3];
@@ -296,9 +422,13 @@ FbiPlan fbi_plan(const fga_mesh *m)
 
 hipError_t gemm(const double2 *A, const double2 *B, double2 *C, const GemmDesc &d, int64_t batch, hipStream_t st)
 {
-  dim3 grid((unsigned)((d.N + 15) / 16), (unsigned)((d.M + 15) / 16), (unsigned)batch);
+  // 64 x 64 tiles where they give every compute unit two workgroups
+  const int64_t big = ((d.N + 63) / 64) * ((d.M + 63) / 64) * batch;
+  const int edge = big >= 512 ? 64 : 32;
+  dim3 grid((unsigned)((d.N + edge - 1) / edge), (unsigned)((d.M + edge - 1) / edge), (unsigned)batch);
   ProfScope prof(FGA_K_FBI_GEMM, st);
-  hipLaunchKernelGGL(k_cgemm, grid, 256, 0, st, A, B, C, d);
+  if (edge == 64) hipLaunchKernelGGL(k_cgemm<2>, grid, 256, 0, st, A, B, C, d);
+  else hipLaunchKernelGGL(k_cgemm<1>, grid, 256, 0, st, A, B, C, d);
   return hipGetLastError();
 }
 
@@ -407,16 +537,19 @@ fga_status decompose_impl(const DevMedium &dm, const fga_mesh *m, const double *
   a.nlayer = dm.kind == FGA_MEDIUM_LAYERED ? dm.nlayer : 1;
   for (int l = 0; l < FGA_MAX_LAYERS; ++l) a.bound[l] = dm.bound[l];
 
-  hipLaunchKernelGGL(k_beam_count, (unsigned)nblk, 256, 0, st, a, counts);
+  // the blocks' counts and their scan share one array: 2 ceil(nblk / per) <= nblk + 1
+  const int per = (int)std::min<int64_t>(MAX_RUNS, std::max<int64_t>(2, nblk / 16384));
+  const int64_t nb = (nblk + per - 1) / per;
+  hipLaunchKernelGGL(k_beam_count, (unsigned)nb, 256, 0, st, a, per, nblk, offs, counts);
   FGA_LAUNCH_CHECK();
-  FGA_HIP(launch_scan(counts, offs, nblk, total, st));
+  FGA_HIP(launch_scan(counts, counts + nb, nb, total, st));
   int64_t made = 0;
   FGA_HIP(hipMemcpyAsync(&made, total, sizeof(int64_t), hipMemcpyDeviceToHost, st));
   FGA_HIP(hipStreamSynchronize(st));
   if (made > beams->capacity)
     return fail(FGA_ECAPACITY, "decomposition makes %lld beams but capacity is %lld", (long long)made,
                 (long long)beams->capacity);
-  hipLaunchKernelGGL(k_beam_write, (unsigned)nblk, 256, 0, st, a, offs, beams->f64, beams->i32, beams->lineage,
+  hipLaunchKernelGGL(k_beam_write, (unsigned)nblk, 256, 0, st, a, per, offs, counts + nb, beams->f64, beams->i32, beams->lineage,
                      beams->capacity);
   FGA_LAUNCH_CHECK();
   beams->count = made;
