@@ -40,7 +40,11 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int T = 16;       // tile edge (points)
 constexpr int NB = 16;      // beams per LDS batch
 constexpr int MAXR = 1024;  // max candidate runs per tile: (2 reach + 1)^2
-constexpr int NSEG = 4096;  // work items per launch beyond one per tile (at most 8 per tile)
+// Work items per launch beyond one per tile: eight per tile up to MAX_SEG, and at
+// least MIN_SEG, so that a grid of few tiles still fills the chip (512 workgroups
+// at two wavefronts per SIMD) with a round to spare; 32^3 points (8 tiles) and
+// 98 k beams took 3.30 ms in 72 items.
+constexpr int MAX_SEG = 4096, MIN_SEG = 512, SEG_BEAMS = 64;  // SEG_BEAMS: shortest item
 
 struct GridGeom {
   int n[3], nt[3], nc[3], reach[3];
@@ -792,7 +796,8 @@ fga_status grid_sum_impl(const fga_beams *b, double eps, double tau, const int n
   const int ntile = g.nt[0] * g.nt[1] * g.nt[2];
   const int64_t ncells = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
   if (ncells >= 0x7fffffff) return fail(FGA_EUNSUPPORTED, "too many cells");
-  const int nseg = NSEG < 8 * ntile ? NSEG : 8 * ntile;
+  const int64_t most = (int64_t)ntile * ((nb + SEG_BEAMS - 1) / SEG_BEAMS);  // no item shorter than SEG_BEAMS
+  const int nseg = (int)std::min<int64_t>(std::min(MAX_SEG, std::max(MIN_SEG, 8 * ntile)), std::max<int64_t>(most, 1));
   const int max_items = nseg + ntile;
 
   int32_t *keys = ar.take<int32_t>(nb + 1), *keys2 = ar.take<int32_t>(nb + 1);
@@ -848,7 +853,7 @@ fga_status grid_sum_impl(const fga_beams *b, double eps, double tau, const int n
   int64_t total = 0;
   for (int t = 0; t < ntile; ++t) total += hc[t];
   int64_t seg = (total + nseg - 1) / nseg;
-  if (seg < 64) seg = 64;
+  if (seg < SEG_BEAMS) seg = SEG_BEAMS;
   seg = (seg + NB - 1) / NB * NB;
   std::vector<Item> hi;
   std::vector<int32_t> hf(ntile), hn(ntile);
