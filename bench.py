@@ -54,8 +54,8 @@ HBM_PEAK = 8.0e12
 TRAFFIC = {
     "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "0c7a0571f27155e8",
                    "beams": 33044152, "bytes_per_launch": 2.1412e10},
-    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "b905efd85e76b798",
-                  "beams": 33044152, "bytes_per_launch": 9.9295e9},
+    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "3f25671a99fb0ed7",
+                  "beams": 33044152, "bytes_per_launch": 9.0504e9},
 }
 
 

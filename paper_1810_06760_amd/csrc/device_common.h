@@ -6,6 +6,24 @@
 
 namespace fga {
 
+// 1/x and 1/sqrt(x) of a normal positive x: the hardware's estimate (about 24
+// bits) and one third-order step, e the residual: r + r (e + e^2), and
+// y + y e (1/2 + 3/8 e).  Within two units in the last place in 4 and 6
+// instructions; the library's division and square root take about 10 and 16 for
+// the last half unit and for subnormals.
+__device__ __forceinline__ double fast_rcp(double x)
+{
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+__device__ __forceinline__ double fast_rsqrt(double x)
+{
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
 // Medium kinds a kernel is specialised for.
 // MK_GRID: trilinear node records; MK_GRID3: cubic B-spline of the node values.
 enum { MK_HOMOG = 0, MK_GRID = 1, MK_LAYERED = 2, MK_GRID3 = 3 };
@@ -41,15 +59,109 @@ __device__ __forceinline__ double iface_level(const DevMedium &m, int iface)
 // Speed of wave type sp (0 = P, 1 = S) at x: c, gradient g and Hessian H
 // (xx, yy, zz, xy, xz, yz).  Grid media interpolate the ten precomputed node
 // fields trilinearly (periodic); each node is one 128-byte record.
-// A block of MEDBLK^3 grid nodes held in LDS by a workgroup: the ten fields
-// of node (o + l) (periodic) at lds[10 (l_z MEDBLK^2 + l_y MEDBLK + l_x)].
-constexpr int MEDBLK = 12;
-// Cubic media: a block of MEDBLK3^3 spline coefficients per node field, the
-// c_S field (two_fields) MEDBLK3^3 doubles after the c_P field.
+// Cubic media: a block of MEDBLK3^3 spline coefficients per node field held in LDS
+// by a workgroup, the c_S field (two_fields) MEDBLK3^3 doubles after the c_P field.
 constexpr int MEDBLK3 = 16;
 struct MedBlock {
   const double *lds;  // NULL: no block
   int o[3];
+};
+
+// Cell (node i0, periodic) and offsets t in it of a point of a grid medium.
+__device__ __forceinline__ void grid_cell(const DevMedium &m, const double *x, int i0[3], double t[3])
+{
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double u = (x[d] - m.lo[d]) * m.ih[d];
+    const double fl = floor(u);
+    t[d] = u - fl;
+    int ii = (int)fl;
+    if (ii < 0 || ii >= m.n[d]) ii = ((ii % m.n[d]) + m.n[d]) % m.n[d];  // periodic (rare)
+    i0[d] = ii;
+  }
+}
+
+// The eight node records of the cell each lane's beam is in, held in LDS over a
+// launch.  A beam stays in a cell for several steps (c dt is a fraction of h),
+// so a stage's trilinear sum reads its forty 16-byte pieces from the lane's own
+// column of rec (consecutive lanes, no bank conflicts, one address for all) and
+// memory is touched only where a beam has moved on: then its forty pieces go from
+// the table straight to LDS (no registers), requested as soon as the stage before
+// knows where the ray goes, a whole stage's arithmetic ahead.
+constexpr int CELL_PIECES = 40;  // 8 corners x 5 pairs of fields
+static_assert(FGA_GRID_NODE_DOUBLES * sizeof(double) == 128, "node records are addressed by shifts");
+typedef double v2d __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) v2d lds_v2d;
+struct CellCache {
+  // the wavefront's pieces, [CELL_PIECES][64] (the workgroup is one wavefront); a
+  // constant address, so the LDS side of a request costs no vector instruction
+  static __device__ __forceinline__ lds_v2d *rec()
+  {
+    __shared__ v2d pieces[CELL_PIECES * 64];
+    return (lds_v2d *)pieces;
+  }
+  int cell[3];   // the cell the lane's column holds (-1: none)
+  double t[3];   // offsets in it of the point asked for last
+  template <int K> static __device__ __forceinline__ void piece(const char *p, lds_v2d *col)
+  {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)p,
+                                     (__attribute__((address_space(3))) void *)(col + 63 * K), 16, 16 * K, 0);
+  }
+  __device__ __forceinline__ void request(const DevMedium &m, int sp, const double *x)
+  {
+    int i0[3];
+    grid_cell(m, x, i0, t);
+    if (i0[0] == cell[0] && i0[1] == cell[1] && i0[2] == cell[2]) return;
+    const char *tab = reinterpret_cast<const char *>(m.table + (sp && m.two_fields ? m.field_stride : 0));
+    int i1[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      cell[d] = i0[d];
+      i1[d] = i0[d] + 1 == m.n[d] ? 0 : i0[d] + 1;
+    }
+#pragma unroll
+    for (int row = 0; row < 4; ++row) {
+      const uint64_t r = ((uint64_t)(unsigned)((row & 2) ? i1[2] : i0[2]) * (unsigned)m.n[1] +
+                          (unsigned)((row & 1) ? i1[1] : i0[1])) * (unsigned)m.n[0];
+#pragma unroll
+      for (int cx = 0; cx < 2; ++cx) {
+        const int corner = 2 * row + cx;
+        const char *p = tab + ((r + (unsigned)(cx ? i1[0] : i0[0])) << 7);  // 128-byte records
+        // one address a corner: the pieces' offsets are the instruction's, which
+        // also moves the LDS address by as much
+        lds_v2d *col = rec() + 64 * 5 * corner;
+        piece<0>(p, col);
+        piece<1>(p, col);
+        piece<2>(p, col);
+        piece<3>(p, col);
+        piece<4>(p, col);
+      }
+    }
+  }
+  // every request has arrived (vmcnt 0)
+  __device__ __forceinline__ void wait() const
+  {
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    asm volatile("" ::: "memory");
+  }
+  // the ten fields at the point asked for last
+  __device__ __forceinline__ void fields(double v[10]) const
+  {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int f = 0; f < 10; ++f) v[f] = 0.0;
+#pragma unroll
+    for (int corner = 0; corner < 8; ++corner) {
+      const double w = ((corner & 1) ? t[0] : 1.0 - t[0]) * ((corner & 2) ? t[1] : 1.0 - t[1]) *
+                       ((corner & 4) ? t[2] : 1.0 - t[2]);
+#pragma unroll
+      for (int k = 0; k < 5; ++k) {
+        const v2d a = rec()[64 * (5 * corner + k) + lane];
+        v[2 * k] += w * a.x;
+        v[2 * k + 1] += w * a.y;
+      }
+    }
+  }
 };
 
 // Cubic B-spline weights of the nodes i-1 .. i+2 at the fraction t of cell i,
@@ -184,16 +296,10 @@ __device__ __forceinline__ void medium_eval(const DevMedium &m, int sp, int laye
       else scale = m.cs_ratio;
     }
     int i0[3];
-    double w[3][4], d1[3][4], d2[3][4];
+    double t[3], w[3][4], d1[3][4], d2[3][4];
+    grid_cell(m, x, i0, t);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const double u = (x[d] - m.lo[d]) * m.ih[d];
-      const double fl = floor(u);
-      int ii = (int)fl;
-      if (ii < 0 || ii >= m.n[d]) ii = ((ii % m.n[d]) + m.n[d]) % m.n[d];  // periodic (rare)
-      i0[d] = ii;
-      bspline_weights(u - fl, m.ih[d], w[d], d1[d], d2[d]);
-    }
+    for (int d = 0; d < 3; ++d) bspline_weights(t[d], m.ih[d], w[d], d1[d], d2[d]);
     // the 4x4x4 stencil from the LDS block when it lies in it for every lane
     bool inblk = blk != nullptr && blk->lds != nullptr;
     int l[3] = {0, 0, 0};
@@ -239,63 +345,26 @@ __device__ __forceinline__ void medium_eval(const DevMedium &m, int sp, int laye
     }
     int i0[3], i1[3];
     double t[3];
+    grid_cell(m, x, i0, t);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      double u = (x[d] - m.lo[d]) * m.ih[d];
-      double fl = floor(u);
-      t[d] = u - fl;
-      int ii = (int)fl;
-      if (ii < 0 || ii >= m.n[d]) ii = ((ii % m.n[d]) + m.n[d]) % m.n[d];  // periodic (rare)
-      i0[d] = ii;
-      i1[d] = ii + 1 == m.n[d] ? 0 : ii + 1;
-    }
+    for (int d = 0; d < 3; ++d) i1[d] = i0[d] + 1 == m.n[d] ? 0 : i0[d] + 1;
     double v[10];
 #pragma unroll
     for (int f = 0; f < 10; ++f) v[f] = 0.0;
-    // the cell's eight nodes from the LDS block when they all lie in it
-    bool inblk = blk != nullptr && blk->lds != nullptr;
-    int l[3] = {0, 0, 0};
-    if (inblk) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        int li = i0[d] - blk->o[d];
-        if (li < 0) li += m.n[d];
-        l[d] = li;
-        inblk = inblk && li <= MEDBLK - 2;
-      }
-    }
-    // LDS path when every lane of the wavefront has its cell in the block
-    // (the common case: Morton-ordered neighbours), else global memory for all
-    if (__all(inblk)) {
-#pragma unroll 8
-      for (int corner = 0; corner < 8; ++corner) {
-        const int lx = l[0] + (corner & 1), ly = l[1] + ((corner >> 1) & 1), lz = l[2] + ((corner >> 2) & 1);
-        const double w = ((corner & 1) ? t[0] : 1.0 - t[0]) * ((corner & 2) ? t[1] : 1.0 - t[1]) *
-                         ((corner & 4) ? t[2] : 1.0 - t[2]);
-        const double2 *p = reinterpret_cast<const double2 *>(blk->lds + 10 * ((lz * MEDBLK + ly) * MEDBLK + lx));
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          const double2 a = p[k];
-          v[2 * k] += w * a.x;
-          v[2 * k + 1] += w * a.y;
-        }
-      }
-    } else {
 #pragma unroll 2
-      for (int corner = 0; corner < 8; ++corner) {
-        const int ix = (corner & 1) ? i1[0] : i0[0];
-        const int iy = (corner & 2) ? i1[1] : i0[1];
-        const int iz = (corner & 4) ? i1[2] : i0[2];
-        const double w = ((corner & 1) ? t[0] : 1.0 - t[0]) * ((corner & 2) ? t[1] : 1.0 - t[1]) *
-                         ((corner & 4) ? t[2] : 1.0 - t[2]);
-        const double2 *p = reinterpret_cast<const double2 *>(
-            tab + (size_t)FGA_GRID_NODE_DOUBLES * (((size_t)iz * m.n[1] + iy) * m.n[0] + ix));
+    for (int corner = 0; corner < 8; ++corner) {
+      const int ix = (corner & 1) ? i1[0] : i0[0];
+      const int iy = (corner & 2) ? i1[1] : i0[1];
+      const int iz = (corner & 4) ? i1[2] : i0[2];
+      const double w = ((corner & 1) ? t[0] : 1.0 - t[0]) * ((corner & 2) ? t[1] : 1.0 - t[1]) *
+                       ((corner & 4) ? t[2] : 1.0 - t[2]);
+      const double2 *p = reinterpret_cast<const double2 *>(
+          tab + (size_t)FGA_GRID_NODE_DOUBLES * (((size_t)iz * m.n[1] + iy) * m.n[0] + ix));
 #pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          const double2 a = p[k];
-          v[2 * k] += w * a.x;
-          v[2 * k + 1] += w * a.y;
-        }
+      for (int k = 0; k < 5; ++k) {
+        const double2 a = p[k];
+        v[2 * k] += w * a.x;
+        v[2 * k + 1] += w * a.y;
       }
     }
     c = scale * v[0];
@@ -312,9 +381,9 @@ __device__ __forceinline__ void s_frame(const double P[3], const double e[3], do
   double x0 = e[1] * P[2] - e[2] * P[1];
   double x1 = e[2] * P[0] - e[0] * P[2];
   double x2 = e[0] * P[1] - e[1] * P[0];
-  double in = 1.0 / sqrt(x0 * x0 + x1 * x1 + x2 * x2);
+  double in = fast_rsqrt(x0 * x0 + x1 * x1 + x2 * x2);
   nsh[0] = x0 * in; nsh[1] = x1 * in; nsh[2] = x2 * in;
-  double ip = 1.0 / sqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
+  double ip = fast_rsqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
   double p0 = P[0] * ip, p1 = P[1] * ip, p2 = P[2] * ip;
   nsv[0] = p1 * nsh[2] - p2 * nsh[1];
   nsv[1] = p2 * nsh[0] - p0 * nsh[2];

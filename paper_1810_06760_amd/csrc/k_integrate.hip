@@ -8,6 +8,14 @@
 // have a one-step kernel of their own (k_step_layered): there a beam whose
 // centre leaves its layer during the step keeps its stored state and is
 // flagged for the interface step.
+//
+// The general step is bound by instruction issue at the one wavefront per SIMD
+// its registers allow, so what it waits for is paid in full.  In the trilinear
+// medium it waited for its gathers: with a block of nodes staged per workgroup
+// and global memory for the rest, 4.1 M beams x 16 steps took 13.6 ms (9.7 with
+// the gathers left out) and 66 k beams of a point source, which share no block,
+// 517 us (182 without gathers).  With each lane's cell kept in LDS and the next
+// one fetched a stage ahead (CellCache) they take 11.5 ms and 235 us.
 #include "fastmath.h"
 #include "rk4.h"
 
@@ -16,11 +24,12 @@ namespace {
 
 using namespace rk;
 
-// Emission record of the current state: Q (3), P 128/(pi eps) (3), B = w e^{iS/eps} A (3 complex).
+// Emission record of the current state: Q (3), P 128/(pi eps) (3), B = W A (3 complex),
+// W = w e^{iS/eps} (S does not change, so W is formed once per launch).
 // SV = 1: an S beam's state holds A itself (frame-free form).
 template <int SV = 0>
 __device__ __forceinline__ void emit_record(double *__restrict__ out, int64_t nb, int64_t j,
-                                            const double *y, const double e[3], double wr, double wi,
+                                            const double *y, const double e[3], double Wr, double Wi,
                                             bool isS, double ieps)
 {
   double A[6];
@@ -32,7 +41,7 @@ __device__ __forceinline__ void emit_record(double *__restrict__ out, int64_t nb
     A[4] = y[IAZ];
     A[5] = y[IAZ + 1];
   } else if (!isS) {
-    const double inp = 1.0 / sqrt(y[IP] * y[IP] + y[IP + 1] * y[IP + 1] + y[IP + 2] * y[IP + 2]);
+    const double inp = fast_rsqrt(y[IP] * y[IP] + y[IP + 1] * y[IP + 1] + y[IP + 2] * y[IP + 2]);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       const double nh = y[IP + c] * inp;
@@ -48,9 +57,6 @@ __device__ __forceinline__ void emit_record(double *__restrict__ out, int64_t nb
       A[2 * c + 1] = y[IA + 1] * nsv[c] + y[IA + 3] * nsh[c];
     }
   }
-  double sn, cs;
-  sincos(y[IS] * ieps, &sn, &cs);
-  const double Wr = wr * cs - wi * sn, Wi = wr * sn + wi * cs;
   const double pscale = ieps * INV_PI_128;
   double r[12];
 #pragma unroll
@@ -72,6 +78,15 @@ __device__ __forceinline__ void emit_record(double *__restrict__ out, int64_t nb
   for (int f = 0; f < 12; ++f) out[f * nb + j] = finite ? r[f] : (f < 3 ? -1.0e300 : 0.0);
 }
 
+// W = w e^{iS/eps}
+__device__ __forceinline__ void emit_weight(double wr, double wi, double S, double ieps, double &Wr, double &Wi)
+{
+  double sn, cs;
+  sincos(S * ieps, &sn, &cs);
+  Wr = wr * cs - wi * sn;
+  Wi = wr * sn + wi * cs;
+}
+
 __device__ __forceinline__ void emit_dead(double *__restrict__ out, int64_t nb, int64_t j)
 {
   // dead beams sit at -1e300 (idle point lanes use +1e300), never in any window
@@ -81,18 +96,18 @@ __device__ __forceinline__ void emit_dead(double *__restrict__ out, int64_t nb, 
   for (int f = 3; f < 12; ++f) out[f * nb + j] = 0.0;
 }
 
-// Whether the quantities a step's sample is formed from (Q, P, the
-// amplitudes and S) are finite.
+// Whether the quantities a step's sample is formed from (Q, P and the
+// amplitudes) are finite: 0 x is zero for a finite x and NaN otherwise.
 template <int SV = 0>
 __device__ __forceinline__ bool emitted_finite(const double *y)
 {
-  bool ok = true;
+  double z = 0.0;
 #pragma unroll
-  for (int d = 0; d < 3; ++d) ok = ok && isfinite(y[IQ + d]) && isfinite(y[IP + d]);
+  for (int d = 0; d < 3; ++d) z = fma(y[IQ + d], 0.0, fma(y[IP + d], 0.0, z));
 #pragma unroll
-  for (int t = 0; t < 4; ++t) ok = ok && isfinite(y[IA + t]);
-  if (SV) ok = ok && isfinite(y[IAZ]) && isfinite(y[IAZ + 1]);
-  return ok && isfinite(y[IS]);
+  for (int t = 0; t < 4; ++t) z = fma(y[IA + t], 0.0, z);
+  if (SV) z = fma(y[IAZ], 0.0, fma(y[IAZ + 1], 0.0, z));
+  return z == 0.0;
 }
 
 // Frame-free S amplitudes: (a_SV, a_SH) in the beam's frame -> A in y, and back.
@@ -130,62 +145,24 @@ __device__ __forceinline__ void vector_to_frame(double *y, double e[3])
   y[IA + 3] = Ai[0] * nsh[0] + Ai[1] * nsh[1] + Ai[2] * nsh[2];
 }
 
+// Threads per workgroup: one wavefront in the trilinear medium, whose lanes keep
+// their cells in LDS (40 KB a wavefront, so four per compute unit fill it) and
+// share nothing.
+template <int MK> constexpr int block_of() { return MK == MK_GRID ? 64 : 256; }
+
 template <int MK, int SV = 0>
 __device__ __forceinline__ void integrate_body(const DevMedium &med, const IntegrateArgs &a)
 {
-  const int64_t i = a.beg + (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = a.beg + (int64_t)blockIdx.x * block_of<MK>() + threadIdx.x;
   const bool active = i < a.end;
   unsigned long long steps_done = 0, culled = 0, quar = 0;
-  // Grid media: the workgroup's beams are neighbours in Morton order, so the
-  // nodes they interpolate from for the whole launch mostly lie in one small
-  // block around them; that block is staged in LDS once and the trilinear
-  // gathers read it (cells outside it fall back to global memory).
   MedBlock blk{nullptr, {0, 0, 0}};
-  if constexpr (MK == MK_GRID) {
-    __shared__ double lds_med[MEDBLK * MEDBLK * MEDBLK * 10];
-    __shared__ int bb[6];
-    if (!med.two_fields) {
-      if (threadIdx.x < 3) {
-        bb[threadIdx.x] = 0x7fffffff;
-        bb[3 + threadIdx.x] = -0x7fffffff;
-      }
-      __syncthreads();
-      if (active && (a.i32[FGA_FLAGS * a.cap + i] & FGA_FLAG_ALIVE)) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const double u = (a.f64[(FGA_Q + d) * a.cap + i] - med.lo[d]) * med.ih[d];
-          const int cell = (int)fmax(fmin(floor(u), 1.0e9), -1.0e9);
-          atomicMin(&bb[d], cell);
-          atomicMax(&bb[3 + d], cell);
-        }
-      }
-      __syncthreads();
-      if (bb[0] <= bb[3]) {
-        int o[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const int c0 = bb[d] / 2 + bb[3 + d] / 2 - MEDBLK / 2 + 1;
-          o[d] = ((c0 % med.n[d]) + med.n[d]) % med.n[d];
-        }
-        for (int idx = threadIdx.x; idx < MEDBLK * MEDBLK * MEDBLK; idx += 256) {
-          const int lx = idx % MEDBLK, ly = (idx / MEDBLK) % MEDBLK, lz = idx / (MEDBLK * MEDBLK);
-          const int nx = (o[0] + lx) % med.n[0], ny = (o[1] + ly) % med.n[1], nz = (o[2] + lz) % med.n[2];
-          const double *src =
-              med.table + (size_t)FGA_GRID_NODE_DOUBLES * (((size_t)nz * med.n[1] + ny) * med.n[0] + nx);
-#pragma unroll
-          for (int f = 0; f < 10; ++f) lds_med[10 * idx + f] = src[f];
-        }
-        __syncthreads();
-        blk.lds = lds_med;
-        blk.o[0] = o[0];
-        blk.o[1] = o[1];
-        blk.o[2] = o[2];
-      }
-    }
-  }
   if constexpr (MK == MK_GRID3) {
-    // the same for the cubic stencils: a MEDBLK3^3 block of spline coefficients
-    // (both node fields when there are two) around the beams' cells
+    // The workgroup's beams are neighbours in Morton order, so the nodes they
+    // interpolate from for the whole launch mostly lie in one small block around
+    // them; that MEDBLK3^3 block of spline coefficients (of both node fields when
+    // there are two) is staged in LDS once and the 4x4x4 stencils read it (stencils
+    // outside it fall back to global memory).
     constexpr int B3 = MEDBLK3 * MEDBLK3 * MEDBLK3;
     __shared__ double lds_cf[2 * B3];
     __shared__ int bb[6];
@@ -259,18 +236,27 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
       // After every step: a beam whose sampled quantities are no longer finite
       // is quarantined, and one with |w| max|a| below the cutoff is dropped;
       // either stops stepping and emits dead records from that step's sample on.
+      CellCache cells{{-1, -1, -1}, {0.0, 0.0, 0.0}};
       bool live = isfinite(wabs) && isfinite(e[0]) && isfinite(e[1]) && isfinite(e[2]);
       if (!live) {
         flags = FGA_FLAG_QUARANTINED;
         quar = 1;
       }
+      const double S = y[IS];
+      const bool s_finite = isfinite(S);
+      double Wr = 0.0, Wi = 0.0;
+      if (a.stride) emit_weight(wr, wi, S, ieps, Wr, Wi);
+      if constexpr (MK == MK_GRID) {
+        if (live) cells.request(med, sp, y + IQ);
+      }
       for (int s = 0; s < a.nsteps; ++s) {
         if (live) {
-          if constexpr (MK == MK_GRID || MK == MK_GRID3) rk4_step<MK, SV>(med, sp, layer, sg, isS, e, y, dt, &blk);
+          if constexpr (MK == MK_GRID) rk4_step<MK, SV, true>(med, sp, layer, sg, isS, e, y, dt, nullptr, &cells);
+          else if constexpr (MK == MK_GRID3) rk4_step<MK, SV, true>(med, sp, layer, sg, isS, e, y, dt, &blk);
           else rk4_step_pc<MK>(med, sp, layer, sg, isS, y, dt);  // grad c = 0
           if (isS && !SV) reframe_s(y, e);
           ++steps_done;
-          if (!emitted_finite<SV>(y)) {
+          if (!(emitted_finite<SV>(y) && s_finite)) {
             live = false;
             flags = FGA_FLAG_QUARANTINED;
             quar = 1;
@@ -290,7 +276,7 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
         }
         if (a.stride && (a.step0 + s + 1) % a.stride == 0) {
           double *rec = a.emit + (int64_t)((a.step0 + s + 1) / a.stride - 1 - first_emit) * 12 * nb;
-          if (live) emit_record<SV>(rec, nb, j, y, e, wr, wi, isS, ieps);
+          if (live) emit_record<SV>(rec, nb, j, y, e, Wr, Wi, isS, ieps);
           else emit_dead(rec, nb, j);
         }
       }
@@ -305,13 +291,17 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
           quar = 1;
         }
       }
-      // where grad c = 0 the step leaves P and dzP as they were: not stored
+      // the steps leave S as it was, and where grad c = 0 P and dzP too: not stored
+      // (the addresses are formed anew: kept from the loads they would take a
+      // hundred registers through the steps)
+      int64_t io = i;
+      asm volatile("" : "+v"(io));
 #pragma unroll
       for (int f = 0; f < NS; ++f)
-        if (MK == MK_GRID || MK == MK_GRID3 || !((f >= IP && f < IP + 3) || (f >= IZPR && f < IZPR + 18)))
-          F[f * cap + i] = y[f];
+        if (f != IS && (MK == MK_GRID || MK == MK_GRID3 || !((f >= IP && f < IP + 3) || (f >= IZPR && f < IZPR + 18))))
+          F[f * cap + io] = y[f];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + i] = e[d];
+      for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + io] = e[d];
       a.i32[FGA_FLAGS * cap + i] = flags;
       }
     }
@@ -330,7 +320,7 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
 }
 
 template <int MK, int SV = 0>
-__global__ __launch_bounds__(256) void k_integrate(DevMedium med, IntegrateArgs a)
+__global__ __launch_bounds__(block_of<MK>()) void k_integrate(DevMedium med, IntegrateArgs a)
 {
   integrate_body<MK, SV>(med, a);
 }
@@ -339,7 +329,7 @@ __global__ __launch_bounds__(256) void k_integrate(DevMedium med, IntegrateArgs 
 // (no emission).  The same arithmetic as the general kernel with
 // rk4_step_pc, ordered so that little stays live: the ray (Q, S) advances
 // first and a beam leaving its layer stops there, flagged, with its stored
-// state untouched; otherwise Q, S and dzQ are stored as soon as they are
+// state untouched; otherwise Q and dzQ are stored as soon as they are
 // formed, dzP enters only through Z0 = dzQ + i dzP and K = d(dzQ)/dt, and P
 // and dzP are not stored (unchanged by the step).  That fits two wavefronts
 // per SIMD, so one wavefront's loads overlap another's arithmetic.
@@ -382,8 +372,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int t = 0; t < 4; ++t) A[t] = F[(FGA_A0_RE + t) * cap + i];
 #pragma unroll
       for (int d = 0; d < 3; ++d) e[d] = F[(FGA_E + d) * cap + i];
-      double kQ[3], kS, ph[3], ci;
-      pc_ray_rates(c, sg, P, kQ, kS, ph, ci);
+      double kQ[3], ph[3], ci;
+      pc_ray_rates(c, sg, P, kQ, ph, ci);
       double Qn[3];
 #pragma unroll
       for (int d = 0; d < 3; ++d) Qn[d] = rk4_const(Q[d], kQ[d], h6);
@@ -402,14 +392,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // the interface step redoes this step from the stored state
         a.i32[FGA_FLAGS * cap + i] = flags | FGA_FLAG_CROSS;
       } else {
-        const double Sn = rk4_const(S, kS, h6);
-        bool finite = isfinite(Sn) && isfinite(P[0]) && isfinite(P[1]) && isfinite(P[2]);
+        bool finite = isfinite(S) && isfinite(P[0]) && isfinite(P[1]) && isfinite(P[2]);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           F[(FGA_Q + d) * cap + i] = Qn[d];
           finite = finite && isfinite(Qn[d]);
         }
-        F[FGA_S * cap + i] = Sn;
         double kr[9], ki[9], z0r[9], z0i[9];
         pc_jac_rates(ph, ci, pr, pi, kr, ki);
 #pragma unroll
@@ -490,7 +478,7 @@ __global__ __launch_bounds__(256) void k_step_layered_grad(DevMedium med, Integr
         y[nstate<SV>() - 1] = 0.0;
         if (isS) frame_to_vector(y, e);
       }
-      rk4_step<MK_LAYERED, SV>(med, sp, layer, sg, isS, e, y, a.dt);
+      rk4_step<MK_LAYERED, SV, true>(med, sp, layer, sg, isS, e, y, a.dt);
       int iface, nl;
       if (layer_exit(med, layer, y + IQ, iface, nl)) {
         // the interface step redoes this step from the stored state
@@ -514,7 +502,8 @@ __global__ __launch_bounds__(256) void k_step_layered_grad(DevMedium med, Integr
           }
         }
 #pragma unroll
-        for (int f = 0; f < NS; ++f) F[f * cap + i] = y[f];
+        for (int f = 0; f < NS; ++f)
+          if (f != IS) F[f * cap + i] = y[f];
 #pragma unroll
         for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + i] = e[d];
         a.i32[FGA_FLAGS * cap + i] = flags;
@@ -553,8 +542,9 @@ __global__ __launch_bounds__(256) void k_emit(const double *__restrict__ F, cons
 #pragma unroll
       for (int f = 0; f < NS; ++f) y[f] = F[f * cap + i];
       const double e[3] = {F[(FGA_E + 0) * cap + i], F[(FGA_E + 1) * cap + i], F[(FGA_E + 2) * cap + i]};
-      emit_record(out, nb, j, y, e, F[FGA_W_RE * cap + i], F[FGA_W_IM * cap + i], I[FGA_BRANCH * cap + i] != 0,
-                  ieps);
+      double Wr, Wi;
+      emit_weight(F[FGA_W_RE * cap + i], F[FGA_W_IM * cap + i], y[IS], ieps, Wr, Wi);
+      emit_record(out, nb, j, y, e, Wr, Wi, I[FGA_BRANCH * cap + i] != 0, ieps);
       q[0] = y[IQ];
       q[1] = y[IQ + 1];
       q[2] = y[IQ + 2];
@@ -593,6 +583,7 @@ hipError_t launch_integrate(const DevMedium &m, const IntegrateArgs &a, hipStrea
   const int64_t n = a.end - a.beg;
   if (n <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)((n + 255) / 256);
+  const unsigned waves = (unsigned)((n + block_of<MK_GRID>() - 1) / block_of<MK_GRID>());
   ProfScope prof(FGA_K_INTEGRATE, st);
   switch (m.kind) {
   case FGA_MEDIUM_HOMOGENEOUS: hipLaunchKernelGGL(k_integrate<MK_HOMOG>, blocks, 256, 0, st, m, a); break;
@@ -601,8 +592,8 @@ hipError_t launch_integrate(const DevMedium &m, const IntegrateArgs &a, hipStrea
     // homogeneous medium P is constant and the two forms are one)
     if (m.smooth && a.s_vector) hipLaunchKernelGGL((k_integrate<MK_GRID3, 1>), blocks, 256, 0, st, m, a);
     else if (m.smooth) hipLaunchKernelGGL(k_integrate<MK_GRID3>, blocks, 256, 0, st, m, a);
-    else if (a.s_vector) hipLaunchKernelGGL((k_integrate<MK_GRID, 1>), blocks, 256, 0, st, m, a);
-    else hipLaunchKernelGGL(k_integrate<MK_GRID>, blocks, 256, 0, st, m, a);
+    else if (a.s_vector) hipLaunchKernelGGL((k_integrate<MK_GRID, 1>), waves, block_of<MK_GRID>(), 0, st, m, a);
+    else hipLaunchKernelGGL(k_integrate<MK_GRID>, waves, block_of<MK_GRID>(), 0, st, m, a);
     break;
   default:
     // layered media advance one step per launch, the interface step between

@@ -7,7 +7,8 @@
 //   da_P/dt = a_P (sigma grad c . P/|P| + tr(Z^{-1} dZ/dt)/2)       (eq:amp_P)
 //   d(a_SV, a_SH)/dt = s (a_SV, a_SH) + omega (-a_SH, a_SV),
 //     omega = dN_SH/dt . N_SV = sigma (P.e) e.(grad c x P)/|e x P|^2  (eq:amp_SV, eq:amp_SH)
-//   dS/dt = P . dQ/dt - sigma c |P|
+//   dS/dt = P . dQ/dt - sigma c |P| = 0: H is homogeneous of degree one in P, so the
+//     action keeps its value and no step touches it
 // tr(Z^{-1} dZ/dt) is formed as (sum_ij cof(Z)_ij dZ_ij) / det Z, so no
 // matrix inverse is built.  Frame-free S amplitudes (SV = 1): the physical
 // polarisation A = a_SV N_SV + a_SH N_SH is advanced instead, by
@@ -27,24 +28,58 @@ constexpr int IAZ = 47;
 template <int SV> constexpr int nstate() { return SV ? 49 : NS; }
 constexpr double COS10 = 0.98480775301220805936;  // cos(10 degrees)
 
-// One RK4 stage: k = f(yt); acc += wacc*k; yt <- y + cnext*k in place.  The
-// derivative is folded in as soon as each group of components is complete,
-// row by row for dzQ/dzP, so the live state stays at y, acc and yt.
-template <int MK, int SV = 0>
+// One RK4 stage: k = f(stage input), acc += weight k, yt <- y + fraction dt k in
+// place.  The derivative is folded in as soon as each group of components is
+// complete, row by row for dzQ/dzP, so the live state stays at y, acc and yt.
+//
+// LAST: the fourth stage, which forms no further stage input and writes y itself;
+// otherwise stage `st` of a loop.
+template <int MK, int SV = 0, bool LAST = false>
 __device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, double sg, bool isS,
-                                      const double e[3], const double *__restrict__ y, double *__restrict__ yt,
-                                      double *__restrict__ acc, double wacc, double cnext,
-                                      const MedBlock *blk = nullptr)
+                                      const double e[3], double *__restrict__ y, double *__restrict__ yt,
+                                      double *__restrict__ acc, int st, double dt,
+                                      const MedBlock *blk = nullptr, CellCache *cells = nullptr)
 {
+  const double h2 = 0.5 * dt, h6 = dt / 6.0;
+  const double wacc = (st == 0 || st == 3) ? 1.0 : 2.0;
+  const double cnext = st == 2 ? dt : (st == 3 ? 0.0 : h2);
+  auto fold = [&](int f, double k) {
+    if (LAST) {
+      y[f] += h6 * (acc[f] + k);
+    } else {
+      acc[f] += wacc * k;
+      yt[f] = y[f] + cnext * k;
+    }
+  };
   double c, g[3], H6[6];
-  medium_eval<MK>(med, sp, layer, yt + IQ, c, g, H6, blk);
+  if (MK == MK_GRID && cells) {
+    double v[10];
+    cells->fields(v);
+    const double scale = sp && !med.two_fields ? med.cs_ratio : 1.0;
+    c = scale * v[0];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g[k] = scale * v[1 + k];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) H6[k] = scale * v[4 + k];
+  } else {
+    medium_eval<MK>(med, sp, layer, yt + IQ, c, g, H6, blk);
+  }
   const double H[3][3] = {{H6[0], H6[3], H6[4]}, {H6[3], H6[1], H6[5]}, {H6[4], H6[5], H6[2]}};
   const double P0 = yt[IP], P1 = yt[IP + 1], P2 = yt[IP + 2];
-  const double np = sqrt(P0 * P0 + P1 * P1 + P2 * P2);
-  const double inp = 1.0 / np;
+  const double np2 = P0 * P0 + P1 * P1 + P2 * P2;
+  const double inp = fast_rsqrt(np2), np = np2 * inp;
   const double ph[3] = {P0 * inp, P1 * inp, P2 * inp};
   const double sc = sg * c;
   const double ci = sc * inp;
+  // the ray first: the next stage's point (after the last stage the next step's)
+  // is known before the Jacobians' work begins, and its cell is asked for (the
+  // trilinear medium's steps are all peeled)
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const double k = sc * ph[j];
+    fold(IQ + j, k);
+  }
+  if (MK == MK_GRID && cells) cells->request(med, sp, LAST ? y + IQ : yt + IQ);
 
   // cofactors of Z = dzQ + i dzP and det Z (cyclic index form carries the sign)
   double Cr[9], Ci[9];
@@ -71,23 +106,31 @@ __device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, d
     deti += zr * Ci[j] + zi * Cr[j];
   }
 
+  // -sigma |P| Hess c and -sigma grad c
+  double Hn[3][3], gn[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    gn[i] = -sg * g[i];
+#pragma unroll
+    for (int j = 0; j <= i; ++j) Hn[i][j] = Hn[j][i] = (-sg * np) * H[i][j];
+  }
   double Tr = 0.0, Ti = 0.0;
 #pragma unroll
   for (int m = 0; m < 3; ++m) {
-    const double ur = yt[IZQR + 3 * m] * g[0] + yt[IZQR + 3 * m + 1] * g[1] + yt[IZQR + 3 * m + 2] * g[2];
-    const double ui = yt[IZQI + 3 * m] * g[0] + yt[IZQI + 3 * m + 1] * g[1] + yt[IZQI + 3 * m + 2] * g[2];
-    const double vr = yt[IZPR + 3 * m] * ph[0] + yt[IZPR + 3 * m + 1] * ph[1] + yt[IZPR + 3 * m + 2] * ph[2];
-    const double vi = yt[IZPI + 3 * m] * ph[0] + yt[IZPI + 3 * m + 1] * ph[1] + yt[IZPI + 3 * m + 2] * ph[2];
+    const double *qr = yt + IZQR + 3 * m, *qi = yt + IZQI + 3 * m, *pr = yt + IZPR + 3 * m, *pi = yt + IZPI + 3 * m;
+    const double vr = pr[0] * ph[0] + pr[1] * ph[1] + pr[2] * ph[2];
+    const double vi = pi[0] * ph[0] + pi[1] * ph[1] + pi[2] * ph[2];
+    // sigma (row . grad c) - sigma c/|P| (row . Phat): what multiplies Phat in d(dzQ)/dt
+    const double ur = -(qr[0] * gn[0] + qr[1] * gn[1] + qr[2] * gn[2]) - ci * vr;
+    const double ui = -(qi[0] * gn[0] + qi[1] * gn[1] + qi[2] * gn[2]) - ci * vi;
     double kq_r[3], kq_i[3], kp_r[3], kp_i[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       const int o = 3 * m + j;
-      kq_r[j] = sg * ur * ph[j] + ci * (yt[IZPR + o] - vr * ph[j]);
-      kq_i[j] = sg * ui * ph[j] + ci * (yt[IZPI + o] - vi * ph[j]);
-      const double hr = yt[IZQR + 3 * m] * H[0][j] + yt[IZQR + 3 * m + 1] * H[1][j] + yt[IZQR + 3 * m + 2] * H[2][j];
-      const double hi = yt[IZQI + 3 * m] * H[0][j] + yt[IZQI + 3 * m + 1] * H[1][j] + yt[IZQI + 3 * m + 2] * H[2][j];
-      kp_r[j] = -sg * (np * hr + vr * g[j]);
-      kp_i[j] = -sg * (np * hi + vi * g[j]);
+      kq_r[j] = ur * ph[j] + ci * pr[j];
+      kq_i[j] = ui * ph[j] + ci * pi[j];
+      kp_r[j] = vr * gn[j] + qr[0] * Hn[0][j] + qr[1] * Hn[1][j] + qr[2] * Hn[2][j];
+      kp_i[j] = vi * gn[j] + qi[0] * Hn[0][j] + qi[1] * Hn[1][j] + qi[2] * Hn[2][j];
       // dZ = d(dzQ) + i d(dzP); T += cof(Z) : dZ
       const double dr = kq_r[j] - kp_i[j], di = kq_i[j] + kp_r[j];
       Tr += Cr[o] * dr - Ci[o] * di;
@@ -96,17 +139,13 @@ __device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, d
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       const int o = 3 * m + j;
-      const double kk[4] = {kq_r[j], kq_i[j], kp_r[j], kp_i[j]};
-      const int base[4] = {IZQR, IZQI, IZPR, IZPI};
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int f = base[t] + o;
-        acc[f] += wacc * kk[t];
-        yt[f] = y[f] + cnext * kk[t];
-      }
+      fold(IZQR + o, kq_r[j]);
+      fold(IZQI + o, kq_i[j]);
+      fold(IZPR + o, kp_r[j]);
+      fold(IZPI + o, kp_i[j]);
     }
   }
-  const double idd = 1.0 / (detr * detr + deti * deti);
+  const double idd = fast_rcp(detr * detr + deti * deti);
   const double trr = (Tr * detr + Ti * deti) * idd;
   const double tri = (Ti * detr - Tr * deti) * idd;
   const double sr = sg * (g[0] * ph[0] + g[1] * ph[1] + g[2] * ph[2]) + 0.5 * trr;
@@ -137,33 +176,17 @@ __device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, d
       const double egp = e[0] * gx0 + e[1] * gx1 + e[2] * gx2;
       const double pe = P0 * e[0] + P1 * e[1] + P2 * e[2];
       const double x0 = e[1] * P2 - e[2] * P1, x1 = e[2] * P0 - e[0] * P2, x2 = e[0] * P1 - e[1] * P0;
-      const double om = sg * pe * egp / (x0 * x0 + x1 * x1 + x2 * x2);
+      const double om = sg * pe * egp * fast_rcp(x0 * x0 + x1 * x1 + x2 * x2);
       ka[0] = sr * a0r - si * a0i - om * a1r;
       ka[1] = sr * a0i + si * a0r - om * a1i;
       ka[2] = sr * a1r - si * a1i + om * a0r;
       ka[3] = sr * a1i + si * a1r + om * a0i;
     }
   }
-  double kr[7];
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    kr[j] = sc * ph[j];
-    kr[3 + j] = -sg * np * g[j];
-  }
-  kr[6] = P0 * kr[0] + P1 * kr[1] + P2 * kr[2] - sc * np;
-  const int fr[7] = {IQ, IQ + 1, IQ + 2, IP, IP + 1, IP + 2, IS};
+  for (int t = 0; t < (SV ? 6 : 4); ++t) fold(t < 4 ? IA + t : IAZ + t - 4, ka[t]);
 #pragma unroll
-  for (int t = 0; t < (SV ? 6 : 4); ++t) {
-    const int f = t < 4 ? IA + t : IAZ + t - 4;
-    acc[f] += wacc * ka[t];
-    yt[f] = y[f] + cnext * ka[t];
-  }
-#pragma unroll
-  for (int t = 0; t < 7; ++t) {
-    const int f = fr[t];
-    acc[f] += wacc * kr[t];
-    yt[f] = y[f] + cnext * kr[t];
-  }
+  for (int j = 0; j < 3; ++j) fold(IP + j, np * gn[j]);
 }
 
 // After a step: an S beam whose P has come within 10 degrees of its frame
@@ -171,9 +194,9 @@ __device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, d
 // physical polarisation a_SV N_SV + a_SH N_SH is unchanged.
 __device__ __forceinline__ void reframe_s(const double P[3], double A[4], double e[3])
 {
-  const double np = sqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
+  const double inp = fast_rsqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
   const double pe = P[0] * e[0] + P[1] * e[1] + P[2] * e[2];
-  if (fabs(pe) / np > COS10) {
+  if (fabs(pe) * inp > COS10) {
     double nsh[3], nsv[3];
     s_frame(P, e, nsh, nsv);
     double Ar[3], Ai[3];
@@ -196,30 +219,42 @@ __device__ __forceinline__ void reframe_s(const double P[3], double A[4], double
 
 __device__ __forceinline__ void reframe_s(double *y, double e[3]) { reframe_s(y + IP, y + IA, e); }
 
-// One classic RK4 step of size dt in place, y' = y + dt/6 (k1 + 2 k2 + 2 k3 + k4);
-// the four stages run as a loop so that only y, acc and the stage input stay live.
+// One classic RK4 step of size dt in place, y' = y + dt/6 (k1 + 2 k2 + 2 k3 + k4).
 // SV = 1: frame-free S amplitudes (y holds nstate<1>() values); after the
 // step A is projected on the plane orthogonal to the new P, which the exact
 // solution never leaves (the projection removes the step's truncation drift).
-template <int MK, int SV = 0>
+// PEEL: the fourth stage on its own after a loop of three.  The arithmetic
+// reaches half of the register file, and y and acc live in the other half: the
+// loop's fourth turn reads y for a stage input that nobody takes and the step's
+// end reads y and acc once more (4.1 M beams x 16 steps in the trilinear medium:
+// 12.0 ms as a loop of four, 11.5 peeled).  All four in a row are 65 KB of code,
+// as much as the instruction cache holds for two compute units: 16.9 ms.  Callers
+// with many steps in a row of code (the interface step) keep the loop.
+template <int MK, int SV = 0, bool PEEL = false>
 __device__ __forceinline__ void rk4_step(const DevMedium &med, int sp, int layer, double sg, bool isS,
-                                         const double e[3], double *y, double dt, const MedBlock *blk = nullptr)
+                                         const double e[3], double *y, double dt, const MedBlock *blk = nullptr,
+                                         CellCache *cells = nullptr)
 {
   constexpr int N = nstate<SV>();
   double acc[N], yt[N];
 #pragma unroll
   for (int f = 0; f < N; ++f) { yt[f] = y[f]; acc[f] = 0.0; }
-  const double h2 = 0.5 * dt, h6 = dt / 6.0;
 #pragma nounroll
-  for (int st = 0; st < 4; ++st) {
-    const double wacc = (st == 0 || st == 3) ? 1.0 : 2.0;
-    const double cnext = st == 2 ? dt : (st == 3 ? 0.0 : h2);
-    stage<MK, SV>(med, sp, layer, sg, isS, e, y, yt, acc, wacc, cnext, blk);
+  for (int st = 0; st < (PEEL ? 3 : 4); ++st) {
+    if (MK == MK_GRID && cells) cells->wait();
+    stage<MK, SV>(med, sp, layer, sg, isS, e, y, yt, acc, st, dt, blk, cells);
   }
+  if constexpr (PEEL) {
+    if (MK == MK_GRID && cells) cells->wait();
+    stage<MK, SV, true>(med, sp, layer, sg, isS, e, y, yt, acc, 3, dt, blk, cells);
+  } else {
+    const double h6 = dt / 6.0;
 #pragma unroll
-  for (int f = 0; f < N; ++f) y[f] += h6 * acc[f];
+    for (int f = 0; f < N; ++f)
+      if (f != IS) y[f] += h6 * acc[f];
+  }
   if (SV && isS) {
-    const double inp = 1.0 / sqrt(y[IP] * y[IP] + y[IP + 1] * y[IP + 1] + y[IP + 2] * y[IP + 2]);
+    const double inp = fast_rsqrt(y[IP] * y[IP] + y[IP + 1] * y[IP + 1] + y[IP + 2] * y[IP + 2]);
     const double ph[3] = {y[IP] * inp, y[IP + 1] * inp, y[IP + 2] * inp};
     const double apr = y[IA] * ph[0] + y[IA + 2] * ph[1] + y[IAZ] * ph[2];
     const double api = y[IA + 1] * ph[0] + y[IA + 3] * ph[1] + y[IAZ + 1] * ph[2];
@@ -234,7 +269,7 @@ __device__ __forceinline__ void rk4_step(const DevMedium &med, int sp, int layer
 
 // The pieces of the classic RK4 step where grad c = 0 (a homogeneous medium,
 // or inside one layer of a layered medium).  There P and dzP have zero
-// derivative and Q, dzQ and S constant ones, so every stage's derivative of
+// derivative and Q and dzQ constant ones, so every stage's derivative of
 // those equals the first; only the amplitudes' derivative depends on the
 // stage, through Z = dzQ + i dzP at the stage input in tr(Z^{-1} dZ/dt).
 // Since dzP is fixed, Z at a stage input is Z0 + c K with Z0 = Z at the step's
@@ -249,13 +284,12 @@ __device__ __forceinline__ double rk4_const(double y0, double k, double h6)
   return y0 + h6 * (((k + 2.0 * k) + 2.0 * k) + k);
 }
 
-// dQ/dt and dS/dt for speed c (eq:char_plus, eq:char_minus); also P/|P| and
+// dQ/dt for speed c (eq:char_plus, eq:char_minus); also P/|P| and
 // sigma c / |P| for the Jacobian rates.
-__device__ __forceinline__ void pc_ray_rates(double c, double sg, const double P[3], double kQ[3], double &kS,
-                                             double ph[3], double &ci)
+__device__ __forceinline__ void pc_ray_rates(double c, double sg, const double P[3], double kQ[3], double ph[3],
+                                             double &ci)
 {
-  const double np = sqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
-  const double inp = 1.0 / np;
+  const double inp = fast_rsqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
   ph[0] = P[0] * inp;
   ph[1] = P[1] * inp;
   ph[2] = P[2] * inp;
@@ -263,7 +297,6 @@ __device__ __forceinline__ void pc_ray_rates(double c, double sg, const double P
   ci = sc * inp;
 #pragma unroll
   for (int j = 0; j < 3; ++j) kQ[j] = sc * ph[j];
-  kS = P[0] * kQ[0] + P[1] * kQ[1] + P[2] * kQ[2] - sc * np;
 }
 
 // d(dzQ)/dt = sigma c dzP (I - P (x) P/|P|^2)/|P| (eq:DzDt with grad c = 0),
@@ -322,7 +355,7 @@ __device__ __forceinline__ void pc_amplitude(const double z0r[9], const double z
         Ti += Cr * ki[3 * i + j] + Ci * kr[3 * i + j];
       }
     }
-    const double idd = 1.0 / (detr * detr + deti * deti);
+    const double idd = fast_rcp(detr * detr + deti * deti);
     const double sr = 0.5 * ((Tr * detr + Ti * deti) * idd);
     const double si = 0.5 * ((Ti * detr - Tr * deti) * idd);
     double ka[4];
@@ -347,8 +380,8 @@ __device__ __forceinline__ void rk4_step_pc(const DevMedium &med, int sp, int la
 {
   double c, g[3], H6[6];
   medium_eval<MK>(med, sp, layer, y + IQ, c, g, H6);
-  double kQ[3], kS, ph[3], ci, kr[9], ki[9], z0r[9], z0i[9];
-  pc_ray_rates(c, sg, y + IP, kQ, kS, ph, ci);
+  double kQ[3], ph[3], ci, kr[9], ki[9], z0r[9], z0i[9];
+  pc_ray_rates(c, sg, y + IP, kQ, ph, ci);
   pc_jac_rates(ph, ci, y + IZPR, y + IZPI, kr, ki);
 #pragma unroll
   for (int o = 0; o < 9; ++o) {
@@ -364,7 +397,6 @@ __device__ __forceinline__ void rk4_step_pc(const DevMedium &med, int sp, int la
     y[IZQR + o] = rk4_const(y[IZQR + o], kr[o], h6);
     y[IZQI + o] = rk4_const(y[IZQI + o], ki[o], h6);
   }
-  y[IS] = rk4_const(y[IS], kS, h6);
 }
 
 }  // namespace rk
