@@ -52,10 +52,10 @@ HBM_PEAK = 8.0e12
 # scaled by a 1 GiB copy calibration; valid only while the kernel's source is
 # unchanged (sha256 prefix) and the beam set is the one profiled, else null
 TRAFFIC = {
-    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "0c7a0571f27155e8",
-                   "beams": 33044152, "bytes_per_launch": 2.1412e10},
-    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "3f25671a99fb0ed7",
-                  "beams": 33044152, "bytes_per_launch": 9.0504e9},
+    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "9730ff55d3021186",
+                   "beams": 33044152, "bytes_per_launch": 2.1081e10},
+    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "b36f923df1fb4076",
+                  "beams": 33044152, "bytes_per_launch": 9.0506e9},
 }
 
 

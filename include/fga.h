@@ -379,9 +379,7 @@ typedef struct {
                               step and is not summed from that step's sample on      */
   int compact;             /* 1: compact the beam set at the end of the call (stable
                               order; dead, culled and quarantined beams leave)        */
-  int64_t batch;           /* beams per receiver batch (0: library default 2^22); in
-                              layered media, which sum one sample per step, a batch
-                              holds (chunk + stride - 1) / stride + 1 times as many  */
+  int64_t batch;           /* beams per receiver batch (0: library default 2^22)       */
   int resort;              /* steps between spatial re-orderings of the beam set
                               (0: library default: with receivers in grid and
                                homogeneous media 32 for sets of 2^23 beams or more,
@@ -446,8 +444,10 @@ size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_
  * eq:Inter_DzQDzP in the local tangent-normal frame, and the remaining
  * (1 - theta) dt in its own layer.  The first child takes the parent's slot,
  * the others are appended after `count` in a deterministic order; a parent at
- * the generation cap, or with no child, is retired.  The call then
- * synchronises `stream` after every step and steps one at a time.  If the
+ * the generation cap, or with no child, is retired.  The steps are
+ * taken in chunks (opts->chunk, 0: 16 with receivers, else 50, and no further
+ * than the next re-ordering) with the children going on from their crossings;
+ * the call then synchronises `stream` several times a chunk.  If the
  * children would not fit in `capacity` the call stops with FGA_ECAPACITY
  * (nothing is dropped silently; the beam set is then partly advanced).
  * Errors: FGA_EINVAL, FGA_ENOMEM (workspace), FGA_ECAPACITY, FGA_EDEVICE. */

@@ -538,8 +538,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
   const int s_vector = opts && opts->s_vector ? 1 : 0;
   hipStream_t st = (hipStream_t)stream;
   EvolvePlan p = evolve_plan(beams, nsteps, opts, rec);
-  // layered media step one step per launch and re-sort a beam set grown by
-  // interface children: re-sorting every 64 steps costs less than it saves
+  // layered media re-sort a beam set grown by interface children: re-sorting every 64 steps costs less than it saves
   // (152 -> 148 s per step on the layered Earth with 16); the workspace does
   // not depend on the interval
   if (dm.kind == FGA_MEDIUM_LAYERED && p.resort > 0 && !(opts && opts->resort > 0)) p.resort = 64;
@@ -567,78 +566,102 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
   const double cutoff = opts ? opts->cutoff_abs : 0.0;
   int last_sort = -1;
   if (dm.kind == FGA_MEDIUM_LAYERED) {
-    // one step at a time: integrator, interface split, then the sample
+    // A chunk of steps at a time.  A beam that would leave its layer stops at the
+    // start of that step; the interface kernels split it there, and the children
+    // go on through what is left of the chunk in the next round, until no beam
+    // stops.  Children appended beyond the batch's records make a later batch.
+    // A step's work is the same, and a beam's result to the bit, for any chunk.
     const int gen_max = (opts && opts->gen_max > 0) ? opts->gen_max : 3;
     const double child_cut = (opts && opts->child_cut != 0.0) ? (opts->child_cut < 0.0 ? 0.0 : opts->child_cut) : 1e-3;
-    for (int s0 = 0; s0 < nsteps; ++s0) {
+    const int chunk = p.chunk < MAX_LAYERED_CHUNK ? p.chunk : MAX_LAYERED_CHUNK;
+    for (int s0 = 0, m = 0; s0 < nsteps; s0 += m) {
       if (p.resort > 0 && (last_sort < 0 || s0 - last_sort >= p.resort)) {
         Arena sa(static_cast<char *>(workspace) + sort_base, sub_bytes);
         size_t need = 0;
         if ((s = sort_beams_spatial(beams, sa, wb.idle, wb.idle_bytes, st, false, &need)) != FGA_OK) return s;
         last_sort = s0;
       }
-      const int64_t n = beams->count;
-      IntegrateArgs a{};
-      a.f64 = beams->f64;
-      a.i32 = beams->i32;
-      a.cap = beams->capacity;
-      a.beg = 0;
-      a.end = n;
-      a.dt = dt;
-      a.nsteps = 1;
-      a.step0 = s0;
-      a.stride = 0;
-      a.eps_emit = 1.0;
-      a.cutoff_abs = cutoff;
-      a.counters = ctr;
-      a.s_vector = s_vector;
-      FGA_HIP(launch_integrate(dm, a, st));
-      InterfaceArgs ia{};
-      ia.f64 = beams->f64;
-      ia.i32 = beams->i32;
-      ia.lineage = beams->lineage;
-      ia.cap = beams->capacity;
-      ia.n = n;
-      ia.dt = dt;
-      ia.gen_max = gen_max;
-      ia.child_cut = child_cut;
-      ia.blk_extra = wb.blk_extra;
-      ia.blk_off = wb.blk_off;
-      ia.counters = ctr + 4;
-      // the crossing beams, in slot order (children slots as if every beam
-      // were visited in order)
-      int64_t ncross = 0;
-      FGA_HIP(collect_crossers(beams->i32 + FGA_FLAGS * beams->capacity, n, wb.cross_list, wb.cross_sorted,
-                               wb.cross_count, wb.cross_tmp, wb.cross_tmp_bytes, st, &ncross));
-      ia.list = wb.cross_sorted;
-      ia.nlist = ncross;
-      if (ncross > 0) {
-        FGA_HIP(launch_interface(dm, ia, 0, st));
-        FGA_HIP(launch_scan(wb.blk_extra, wb.blk_off, (ncross + 255) / 256, wb.total, st));
-        int64_t extra = 0;
-        FGA_HIP(hipMemcpyAsync(&extra, wb.total, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        FGA_HIP(hipStreamSynchronize(st));
-        if (n + extra > beams->capacity)
-          return fail(FGA_ECAPACITY, "step %d: %lld beams after interface splitting exceed the capacity %lld", s0,
-                      (long long)(n + extra), (long long)beams->capacity);
-        FGA_HIP(launch_interface(dm, ia, 1, st));
-        beams->count = n + extra;
+      FGA_HIP(hipMemsetAsync(wb.cross_count, 0, sizeof(unsigned long long), st));
+      m = chunk < nsteps - s0 ? chunk : nsteps - s0;
+      if (p.resort > 0 && m > last_sort + p.resort - s0) m = last_sort + p.resort - s0;
+      int ns = 0, sfirst = 0;
+      if (rec && rec->n > 0) {
+        sfirst = s0 / rec->stride;
+        ns = (s0 + m) / rec->stride - sfirst;
       }
-      if (rec && (s0 + 1) % rec->stride == 0 && rec->n > 0) {
-        const int sample = (s0 + 1) / rec->stride - 1;
-        const int64_t nb = beams->count;
-        if (nb == 0) FGA_HIP(launch_reduce_points(partial, 0, 1, rec->n, wb.perm, seis, p.nsamp, sample, 0, st));
-        // one sample per step here: the records, boxes and partials laid out
-        // for m samples of p.batch beams hold one sample of m * p.batch beams
-        // (with the same beams per workgroup, which depends on beams x samples)
-        const int64_t lbatch = p.batch * (int64_t)((p.chunk + rec->stride - 1) / rec->stride + 1);
-        for (int64_t b0 = 0; b0 < nb; b0 += lbatch) {
-          const int64_t b1 = b0 + lbatch < nb ? b0 + lbatch : nb;
-          FGA_HIP(launch_emit(beams->f64, beams->i32, beams->capacity, b0, b1, rec->eps, emit, wb.box, st));
+      const int64_t fresh_end = beams->count;
+      if (fresh_end == 0 && ns > 0)
+        FGA_HIP(launch_reduce_points(partial, 0, ns, rec->n, wb.perm, seis, p.nsamp, sfirst, 0, st));
+      for (int64_t b0 = 0, b1 = 0; b0 < beams->count; b0 = b1) {
+        // the slots [b0, most) have records
+        const int64_t most = ns > 0 && beams->capacity - b0 > p.batch ? b0 + p.batch : beams->capacity;
+        IntegrateArgs a{};
+        a.f64 = beams->f64;
+        a.i32 = beams->i32;
+        a.cap = beams->capacity;
+        a.beg = b0;
+        a.end = b1 = beams->count < most ? beams->count : most;
+        a.dt = dt;
+        a.nsteps = m;
+        a.step0 = s0;
+        a.stride = ns > 0 ? rec->stride : 0;
+        a.emit = emit;
+        a.eps_emit = rec ? rec->eps : 1.0;
+        a.cutoff_abs = cutoff;
+        a.counters = ctr;
+        a.s_vector = s_vector;
+        a.list = wb.cross_sorted;
+        a.nlist = 0;
+        a.fresh_end = fresh_end;
+        a.rec0 = b0;
+        a.ld = p.batch;
+        a.cross = wb.cross_list;
+        a.ncross = wb.cross_count;
+        for (;;) {
+          FGA_HIP(launch_integrate(dm, a, st));
+          int64_t ncross = 0;
+          FGA_HIP(sort_crossers(wb.cross_list, wb.cross_sorted, wb.cross_count, wb.cross_tmp, wb.cross_tmp_bytes, st,
+                                &ncross));
+          if (ncross == 0) break;
+          const int64_t n = beams->count;
+          InterfaceArgs ia{};
+          ia.f64 = beams->f64;
+          ia.i32 = beams->i32;
+          ia.lineage = beams->lineage;
+          ia.cap = beams->capacity;
+          ia.n = n;
+          ia.dt = dt;
+          ia.gen_max = gen_max;
+          ia.child_cut = child_cut;
+          ia.blk_extra = wb.blk_extra;
+          ia.blk_off = wb.blk_off;
+          ia.counters = ctr + 4;
+          ia.list = wb.cross_sorted;  // in slot order: the children's slots do not depend on the order of arrival
+          ia.nlist = ncross;
+          ia.ncross = wb.cross_count;
+          FGA_HIP(launch_interface(dm, ia, 0, st));
+          FGA_HIP(launch_scan(wb.blk_extra, wb.blk_off, (ncross + 255) / 256, wb.total, st));
+          int64_t extra = 0;
+          FGA_HIP(hipMemcpyAsync(&extra, wb.total, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+          FGA_HIP(hipStreamSynchronize(st));
+          if (n + extra > beams->capacity) {
+            FGA_HIP(launch_clear_resume(beams->i32 + FGA_FLAGS * beams->capacity, n, st));
+            return fail(FGA_ECAPACITY, "steps %d to %d: %lld beams after interface splitting exceed the capacity %lld",
+                        s0, s0 + m - 1, (long long)(n + extra), (long long)beams->capacity);
+          }
+          FGA_HIP(launch_interface(dm, ia, 1, st));
+          beams->count = n + extra;
+          a.nlist = ncross;
+          a.beg = n < most ? n : most;
+          a.end = n + extra < most ? n + extra : most;
+          if (a.end > b1) b1 = a.end;
+        }
+        if (ns > 0) {
           PointsArgs pa{};
           pa.emit = emit;
           pa.nb = b1 - b0;
-          pa.m = 1;
+          pa.ld = p.batch;
+          pa.m = ns;
           pa.xyz = wb.xs;
           pa.n = rec->n;
           pa.eps = rec->eps;
@@ -648,11 +671,10 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
           pa.evals = ctr + 3;
           pa.tile_box = wb.box;
           pa.ntiles = (pa.nb + 63) / 64;
-          pa.boxes_ready = 1;
           pa.precision = rec->precision;
           int nblk = 0;
           FGA_HIP(launch_sum_points(pa, &nblk, st));
-          FGA_HIP(launch_reduce_points(partial, nblk, 1, rec->n, wb.perm, seis, p.nsamp, sample, b0 > 0 ? 1 : 0, st));
+          FGA_HIP(launch_reduce_points(partial, nblk, ns, rec->n, wb.perm, seis, p.nsamp, sfirst, b0 > 0 ? 1 : 0, st));
         }
       }
     }
@@ -692,7 +714,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
       if (rec && ns > 0 && rec->n > 0) {
         PointsArgs pa{};
         pa.emit = emit;
-        pa.nb = b1 - b0;
+        pa.nb = pa.ld = b1 - b0;
         pa.m = ns;
         pa.xyz = wb.xs;
         pa.n = rec->n;
@@ -784,7 +806,7 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
     FGA_HIP(launch_emit(beams->f64, beams->i32, beams->capacity, b0, b1, eps, emit, box, st));
     PointsArgs pa{};
     pa.emit = emit;
-    pa.nb = b1 - b0;
+    pa.nb = pa.ld = b1 - b0;
     pa.m = 1;
     pa.xyz = xs;
     pa.n = n;
@@ -910,7 +932,7 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
     FGA_HIP(launch_emit(beams->f64, beams->i32, beams->capacity, b0, b1, eps, emit, box, st));
     PointsArgs pa{};
     pa.emit = emit;
-    pa.nb = b1 - b0;
+    pa.nb = pa.ld = b1 - b0;
     pa.m = 1;
     pa.xyz = xyz;
     pa.n = n;

@@ -106,12 +106,26 @@ struct IntegrateArgs {
   double cutoff_abs;
   unsigned long long *counters;  // [0] beam-steps, [1] culled, [2] quarantined
   int s_vector;              // 1: frame-free S amplitudes (grid media)
+  // layered media: the beams are list[0, nlist), then the slots [beg, end)
+  const int32_t *list;
+  int64_t nlist;
+  int64_t fresh_end;         // slots below it start the chunk anew: their flags hold no resume step
+  int64_t rec0, ld;          // slot of the first record, and the records' plane stride (emit is [n_emit][12][ld])
+  int32_t *cross;            // slots that stopped at an interface, in no order
+  unsigned long long *ncross;
 };
+// Layered media, within a chunk: the flags of a beam that stopped at an
+// interface hold the step (of the chunk) that would leave the layer, those of a
+// beam that comes from an interface the step it goes on with, from bit
+// RESUME_SHIFT on; FLAG_BORN: the slot held no beam before that step.
+enum { FLAG_BORN = 0x80, RESUME_SHIFT = 8, FLAG_MASK = 0x7f };
+constexpr int MAX_LAYERED_CHUNK = 65535;  // samples that one launch of the sums takes
 hipError_t launch_integrate(const DevMedium &m, const IntegrateArgs &a, hipStream_t st);
 
 struct PointsArgs {
-  const double *emit;        // [m][12][nb] records
+  const double *emit;        // [m][12][ld] records
   int64_t nb;                // beams in the batch
+  int64_t ld;                // plane stride of the records (>= nb)
   int m;                     // samples in the batch
   const double *xyz;         // [n][3]
   int64_t n;
@@ -156,9 +170,9 @@ struct DecompArgs {
 fga_status decompose_impl(const DevMedium &dm, const fga_mesh *mesh, const double *f, const double *g,
                           fga_beams *beams, Arena &ar, hipStream_t st, bool size_only, size_t *need);
 
-// Interface step of a layered medium after one integrator step: beams that
-// left their layer during the step (flag FGA_FLAG_CROSS, state still at the
-// start of the step) are split into children (Snell, elastic boundary
+// Interface step of a layered medium: beams that would leave their layer in the
+// step their flags name (flag FGA_FLAG_CROSS, state at the start of the step) are
+// split into children (Snell, elastic boundary
 // problem, Jacobian map) which finish the step in their own layers.
 struct InterfaceArgs {
   double *f64;
@@ -174,18 +188,19 @@ struct InterfaceArgs {
   int64_t *blk_extra;        // [ceil(nlist / 256)] extra slots per workgroup (pass 1 output)
   int64_t *blk_off;          // [ceil(nlist / 256)] exclusive scan of blk_extra (pass 2 input)
   unsigned long long *counters;  // [0] crossings, [1] children, [2] retired at the generation cap
+  unsigned long long *ncross;    // pass 1 sets it to 0
 };
 // pass 1 (write = 0): per-workgroup counts of extra slots; pass 2 (write = 1):
 // children written (first child in the parent's slot, the others appended at
 // n + blk_off + rank)
 hipError_t launch_interface(const DevMedium &m, const InterfaceArgs &a, int write, hipStream_t st);
-// The slots of [0, n) flagged FGA_FLAG_CROSS, in increasing order, into
-// sorted[0, *ncross) (list: unordered scratch of the same size; count: one
-// device counter; tmp: cross_sort_bytes(cap) bytes).  Synchronises st.
+// The *count slots in list in increasing order into sorted (tmp:
+// cross_sort_bytes(cap) bytes); *ncross is their number.  Synchronises st.
 size_t cross_sort_bytes(int64_t cap);
-hipError_t collect_crossers(const int32_t *flags, int64_t n, int32_t *list, int32_t *sorted,
-                            unsigned long long *count, void *tmp, size_t tmp_bytes, hipStream_t st,
-                            int64_t *ncross);
+hipError_t sort_crossers(const int32_t *list, int32_t *sorted, const unsigned long long *count, void *tmp,
+                         size_t tmp_bytes, hipStream_t st, int64_t *ncross);
+// The resume steps out of the flags of [0, n) (after a failure within a chunk).
+hipError_t launch_clear_resume(int32_t *flags, int64_t n, hipStream_t st);
 
 // exclusive scan of n int64 values (one workgroup); total = sum
 hipError_t launch_scan(const int64_t *in, int64_t *out, int64_t n, int64_t *total, hipStream_t st);

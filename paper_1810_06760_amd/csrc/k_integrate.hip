@@ -4,10 +4,9 @@
 // planes (coalesced), advances it by `nsteps` classic RK4 steps held entirely
 // in registers, optionally writes an emission record (Q, P, w e^{iS/eps} A)
 // after every sample step for the receiver summation, and stores the state
-// back (the right-hand side and the RK4 step are in rk4.h).  Layered media
-// have a one-step kernel of their own (k_step_layered): there a beam whose
-// centre leaves its layer during the step keeps its stored state and is
-// flagged for the interface step.
+// back (the right-hand side and the RK4 step are in rk4.h).  In layered media
+// a beam stops at the step that would take its centre out of its layer, for the
+// interface step (layered_body).
 //
 // The general step is bound by instruction issue at the one wavefront per SIMD
 // its registers allow, so what it waits for is paid in full.  In the trilinear
@@ -325,144 +324,50 @@ __global__ __launch_bounds__(block_of<MK>()) void k_integrate(DevMedium med, Int
   integrate_body<MK, SV>(med, a);
 }
 
-// One step of every beam in a layered medium, the interface step's cadence
-// (no emission).  The same arithmetic as the general kernel with
-// rk4_step_pc, ordered so that little stays live: the ray (Q, S) advances
-// first and a beam leaving its layer stops there, flagged, with its stored
-// state untouched; otherwise Q and dzQ are stored as soon as they are
-// formed, dzP enters only through Z0 = dzQ + i dzP and K = d(dzQ)/dt, and P
-// and dzP are not stored (unchanged by the step).  That fits two wavefronts
-// per SIMD, so one wavefront's loads overlap another's arithmetic.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_step_layered(DevMedium med,
-                                                                                                 IntegrateArgs a)
+// The steps of a chunk in a layered medium.  As in the other media the state stays
+// in registers from step to step and each sample's record is written as it comes;
+// a beam whose next step would end outside its layer stops there: its state at
+// that step's start is stored, the flags get FGA_FLAG_CROSS and the step's number,
+// and its slot joins the list of the interface kernels.  Their children come back
+// in a launch over that list and the slots appended, and go on with the step after
+// (their flags name it); a slot's samples before that are its parent's, or, where
+// it was appended (FLAG_BORN), dead records.
+//
+// GRAD: some layer has a speed gradient (rays bend): the general RK4 step.  Else
+// P, dzP and so d(dzQ)/dt = K are constant in a layer, and K is formed once a
+// launch; two wavefronts per SIMD.  One step per launch, with the state's 0.6 to
+// 0.9 KB a beam to and from memory, a scan of all beams for those that stopped and
+// the interface kernels each time, was bound by memory and launches: 898 k beams of
+// a point source in a layered Earth took 410 us a step and sample beside the sums,
+// chunks of 16 steps 112; 553 k beams in the crosswell model (GRAD) 190 and 77.
+template <bool GRAD, int SV>
+__device__ __forceinline__ void layered_body(const DevMedium &med, const IntegrateArgs &a)
 {
-  const int64_t i = a.beg + (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t idx = (int64_t)blockIdx.x * 64 + threadIdx.x;
   unsigned long long steps_done = 0, culled = 0, quar = 0;
-  if (i < a.end) {
-    const int64_t cap = a.cap;
+  bool cross = false;
+  int64_t i = 0;
+  if (idx < a.nlist + (a.end - a.beg)) {
+    i = idx < a.nlist ? (int64_t)a.list[idx] : a.beg + (idx - a.nlist);
+    const int64_t cap = a.cap, j = i - a.rec0;
     double *__restrict__ F = a.f64;
     int32_t flags = a.i32[FGA_FLAGS * cap + i];
-    const int br = a.i32[FGA_BRANCH * cap + i];
-    const int sgi = a.i32[FGA_SIGMA * cap + i];
-    const int layer = a.i32[FGA_LAYER * cap + i];
-    if (flags & FGA_FLAG_ALIVE) {
-      steps_done = 1;
-      const double sg = (double)sgi;
-      const bool isS = br != 0;
-      const double dt = a.dt, h6 = dt / 6.0;
-      // all of the state, and the layer's speed and bounding interfaces, are
-      // requested at once (one memory latency per beam)
-      const double c = isS ? med.csl[layer] : med.cpl[layer];
-      const double b_in = med.bound[layer], b_out = med.bound[layer > 0 ? layer - 1 : 0];
-      double Q[3], P[3], e[3], A[4], qr[9], qi[9], pr[9], pi[9];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        Q[d] = F[(FGA_Q + d) * cap + i];
-        P[d] = F[(FGA_P + d) * cap + i];
-      }
-      const double S = F[FGA_S * cap + i];
-#pragma unroll
-      for (int o = 0; o < 9; ++o) {
-        qr[o] = F[(FGA_ZQ_RE + o) * cap + i];
-        qi[o] = F[(FGA_ZQ_IM + o) * cap + i];
-        pr[o] = F[(FGA_ZP_RE + o) * cap + i];
-        pi[o] = F[(FGA_ZP_IM + o) * cap + i];
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) A[t] = F[(FGA_A0_RE + t) * cap + i];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) e[d] = F[(FGA_E + d) * cap + i];
-      double kQ[3], ph[3], ci;
-      pc_ray_rates(c, sg, P, kQ, ph, ci);
-      double Qn[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) Qn[d] = rk4_const(Q[d], kQ[d], h6);
-      // the test of layer_exit: interface `layer` below (flat) or inside
-      // (spherical), interface layer - 1 above or outside
-      const bool in_ok = layer < med.nlayer - 1, out_ok = layer > 0;
-      bool crossed;
-      if (med.geometry == 1) {
-        const double r = sqrt(Qn[0] * Qn[0] + Qn[1] * Qn[1] + Qn[2] * Qn[2]);
-        crossed = (in_ok && r < b_in) || (out_ok && r > b_out) || (layer == 0 && med.surface > 0.0 && r > med.surface);
-      } else {
-        crossed = (in_ok && Qn[2] > b_in) || (out_ok && Qn[2] < b_out) ||
-                  (layer == med.nlayer - 1 && med.surface > 0.0 && Qn[2] > med.surface);
-      }
-      if (crossed) {
-        // the interface step redoes this step from the stored state
-        a.i32[FGA_FLAGS * cap + i] = flags | FGA_FLAG_CROSS;
-      } else {
-        bool finite = isfinite(S) && isfinite(P[0]) && isfinite(P[1]) && isfinite(P[2]);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          F[(FGA_Q + d) * cap + i] = Qn[d];
-          finite = finite && isfinite(Qn[d]);
-        }
-        double kr[9], ki[9], z0r[9], z0i[9];
-        pc_jac_rates(ph, ci, pr, pi, kr, ki);
-#pragma unroll
-        for (int o = 0; o < 9; ++o) {
-          z0r[o] = qr[o] - pi[o];
-          z0i[o] = qi[o] + pr[o];
-          const double nr = rk4_const(qr[o], kr[o], h6), ni = rk4_const(qi[o], ki[o], h6);
-          F[(FGA_ZQ_RE + o) * cap + i] = nr;
-          F[(FGA_ZQ_IM + o) * cap + i] = ni;
-          finite = finite && isfinite(nr) && isfinite(ni) && isfinite(pr[o]) && isfinite(pi[o]);
-        }
-        pc_amplitude(z0r, z0i, kr, ki, isS, A, dt);
-        if (isS) reframe_s(P, A, e);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) finite = finite && isfinite(A[t]);
-        if (!finite) {
-          flags = FGA_FLAG_QUARANTINED;
-          quar = 1;
-        } else if (a.cutoff_abs > 0.0) {
-          const double wr = F[FGA_W_RE * cap + i], wi = F[FGA_W_IM * cap + i];
-          const double m0 = A[0] * A[0] + A[1] * A[1];
-          const double m1 = A[2] * A[2] + A[3] * A[3];
-          const double amax = sqrt(m0 > m1 ? m0 : m1);
-          if (sqrt(wr * wr + wi * wi) * amax < a.cutoff_abs) {
-            flags = 0;
-            culled = 1;
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) F[(FGA_A0_RE + t) * cap + i] = A[t];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + i] = e[d];
-        a.i32[FGA_FLAGS * cap + i] = flags;
-      }
-    }
-  }
-  for (int off = 32; off > 0; off >>= 1) {
-    steps_done += __shfl_down(steps_done, off);
-    culled += __shfl_down(culled, off);
-    quar += __shfl_down(quar, off);
-  }
-  if ((threadIdx.x & 63) == 0 && a.counters) {
-    if (steps_done) atomicAdd(a.counters + 0, steps_done);
-    if (culled) atomicAdd(a.counters + 1, culled);
-    if (quar) atomicAdd(a.counters + 2, quar);
-  }
-}
-
-// One step of every beam in a layered medium where some layer has a speed
-// gradient: the general RK4 step (medium_eval gives c, grad c and Hess c of
-// the beam's layer at each stage), and a beam whose centre has left its
-// layer is flagged with its stored state untouched, as in k_step_layered.
-// SV = 1: S beams take the step with the frame-free amplitude (A formed from
-// the frame at the load and returned to it before the store).
-template <int SV = 0>
-__global__ __launch_bounds__(256) void k_step_layered_grad(DevMedium med, IntegrateArgs a)
-{
-  const int64_t i = a.beg + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  unsigned long long steps_done = 0, culled = 0, quar = 0;
-  if (i < a.end) {
-    const int64_t cap = a.cap;
-    double *__restrict__ F = a.f64;
-    int32_t flags = a.i32[FGA_FLAGS * cap + i];
-    if (flags & FGA_FLAG_ALIVE) {
-      steps_done = 1;
+    const bool fresh = idx >= a.nlist && i < a.fresh_end;
+    const int resume = fresh ? 0 : flags >> RESUME_SHIFT;
+    // the first step whose sample this launch writes
+    const int first = (fresh || (flags & FLAG_BORN)) ? 0 : (resume > 0 ? resume - 1 : 0);
+    const int born = fresh ? 0 : resume - 1;  // the step whose end the state is at, if of this chunk
+    flags &= FGA_FLAG_ALIVE | FGA_FLAG_QUARANTINED;
+    const int first_emit = a.stride ? a.step0 / a.stride : 0;
+    auto record = [&](int s) {
+      return a.emit + (int64_t)((a.step0 + s + 1) / a.stride - 1 - first_emit) * 12 * a.ld;
+    };
+    if (!(flags & FGA_FLAG_ALIVE)) {
+      if (a.stride)
+        for (int s = first; s < a.nsteps; ++s)
+          if ((a.step0 + s + 1) % a.stride == 0) emit_dead(record(s), a.ld, j);
+      a.i32[FGA_FLAGS * cap + i] = flags;
+    } else {
       const int br = a.i32[FGA_BRANCH * cap + i];
       const double sg = (double)a.i32[FGA_SIGMA * cap + i];
       const int layer = a.i32[FGA_LAYER * cap + i];
@@ -476,50 +381,134 @@ __global__ __launch_bounds__(256) void k_step_layered_grad(DevMedium med, Integr
       if (SV) {
         y[nstate<SV>() - 2] = 0.0;
         y[nstate<SV>() - 1] = 0.0;
-        if (isS) frame_to_vector(y, e);
       }
-      rk4_step<MK_LAYERED, SV, true>(med, sp, layer, sg, isS, e, y, a.dt);
-      int iface, nl;
-      if (layer_exit(med, layer, y + IQ, iface, nl)) {
-        // the interface step redoes this step from the stored state
-        a.i32[FGA_FLAGS * cap + i] = flags | FGA_FLAG_CROSS;
-      } else {
-        if (isS && SV) vector_to_frame(y, e);
-        else if (isS) reframe_s(y, e);
+      const double wr = F[FGA_W_RE * cap + i], wi = F[FGA_W_IM * cap + i];
+      const double dt = a.dt;
+      const double ieps = 1.0 / a.eps_emit;
+      const double wabs = sqrt(wr * wr + wi * wi);
+      const double S = y[IS];
+      const bool s_finite = isfinite(S);
+      double Wr = 0.0, Wi = 0.0;
+      if (a.stride) emit_weight(wr, wi, S, ieps, Wr, Wi);
+      double kQ[3], ph[3], ci, kr[9], ki[9];
+      if constexpr (!GRAD) {
+        pc_ray_rates(isS ? med.csl[layer] : med.cpl[layer], sg, y + IP, kQ, ph, ci);
+        pc_jac_rates(ph, ci, y + IZPR, y + IZPI, kr, ki);
+      }
+      bool live = true;
+      for (int s = 0; s < a.nsteps; ++s) {
+        if (s >= resume && live && !cross) {
+          if constexpr (GRAD) {
+            double A0[4];
+            if (SV) {
+#pragma unroll
+              for (int t = 0; t < 4; ++t) A0[t] = y[IA + t];
+              if (isS) frame_to_vector(y, e);
+            }
+            cross = rk4_step<MK_LAYERED, SV, true, true>(med, sp, layer, sg, isS, e, y, dt);
+            if (SV && cross) {
+#pragma unroll
+              for (int t = 0; t < 4; ++t) y[IA + t] = A0[t];
+            } else if (isS && SV) {
+              vector_to_frame(y, e);
+            } else if (isS && !cross) {
+              reframe_s(y, e);
+            }
+          } else {
+            const double h6 = dt / 6.0;
+            double q[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) q[d] = rk4_const(y[IQ + d], kQ[d], h6);
+            int iface, nl;
+            cross = layer_exit(med, layer, q, iface, nl);
+            if (!cross) {
+              double z0r[9], z0i[9];
+#pragma unroll
+              for (int d = 0; d < 3; ++d) y[IQ + d] = q[d];
+#pragma unroll
+              for (int o = 0; o < 9; ++o) {
+                z0r[o] = y[IZQR + o] - y[IZPI + o];
+                z0i[o] = y[IZQI + o] + y[IZPR + o];
+                y[IZQR + o] = rk4_const(y[IZQR + o], kr[o], h6);
+                y[IZQI + o] = rk4_const(y[IZQI + o], ki[o], h6);
+              }
+              pc_amplitude(z0r, z0i, kr, ki, isS, y + IA, dt);
+              if (isS) reframe_s(y, e);
+            }
+          }
+          ++steps_done;
+          if (cross) {
+            flags = FGA_FLAG_ALIVE | FGA_FLAG_CROSS | (s << RESUME_SHIFT);
+          } else if (!(emitted_finite(y) && s_finite)) {
+            live = false;
+            flags = FGA_FLAG_QUARANTINED;
+            quar = 1;
+          } else if (a.cutoff_abs > 0.0) {
+            const double m0 = y[IA] * y[IA] + y[IA + 1] * y[IA + 1];
+            const double m1 = y[IA + 2] * y[IA + 2] + y[IA + 3] * y[IA + 3];
+            if (wabs * sqrt(m0 > m1 ? m0 : m1) < a.cutoff_abs) {
+              live = false;
+              flags = 0;
+              culled = 1;
+            }
+          }
+        }
+        if (a.stride && s >= first && !cross && (a.step0 + s + 1) % a.stride == 0) {
+          if (live && s >= born) emit_record(record(s), a.ld, j, y, e, Wr, Wi, isS, ieps);
+          else emit_dead(record(s), a.ld, j);
+        }
+      }
+      if (live && !cross) {
         bool finite = true;
 #pragma unroll
         for (int f = 0; f < NS; ++f) finite = finite && isfinite(y[f]);
         if (!finite) {
           flags = FGA_FLAG_QUARANTINED;
           quar = 1;
-        } else if (a.cutoff_abs > 0.0) {
-          const double wr = F[FGA_W_RE * cap + i], wi = F[FGA_W_IM * cap + i];
-          const double m0 = y[IA] * y[IA] + y[IA + 1] * y[IA + 1];
-          const double m1 = y[IA + 2] * y[IA + 2] + y[IA + 3] * y[IA + 3];
-          if (sqrt(wr * wr + wi * wi) * sqrt(m0 > m1 ? m0 : m1) < a.cutoff_abs) {
-            flags = 0;
-            culled = 1;
-          }
         }
-#pragma unroll
-        for (int f = 0; f < NS; ++f)
-          if (f != IS) F[f * cap + i] = y[f];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + i] = e[d];
-        a.i32[FGA_FLAGS * cap + i] = flags;
       }
+      // the addresses are formed anew: kept from the loads they would take a
+      // hundred registers through the steps
+      int64_t io = i;
+      asm volatile("" : "+v"(io));
+#pragma unroll
+      for (int f = 0; f < NS; ++f)
+        if (f != IS && (GRAD || !((f >= IP && f < IP + 3) || (f >= IZPR && f < IZPR + 18)))) F[f * cap + io] = y[f];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + io] = e[d];
+      a.i32[FGA_FLAGS * cap + io] = flags;
     }
+  }
+  const int lane = threadIdx.x & 63;
+  const unsigned long long stopped = __ballot(cross);
+  if (stopped) {
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd(a.ncross, (unsigned long long)__popcll(stopped));
+    base = __shfl(base, 0);
+    if (cross) a.cross[base + __popcll(stopped & ((1ull << lane) - 1))] = (int32_t)i;
   }
   for (int off = 32; off > 0; off >>= 1) {
     steps_done += __shfl_down(steps_done, off);
     culled += __shfl_down(culled, off);
     quar += __shfl_down(quar, off);
   }
-  if ((threadIdx.x & 63) == 0 && a.counters) {
+  if (lane == 0 && a.counters) {
     if (steps_done) atomicAdd(a.counters + 0, steps_done);
     if (culled) atomicAdd(a.counters + 1, culled);
     if (quar) atomicAdd(a.counters + 2, quar);
   }
+}
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_layered(DevMedium med,
+                                                                                           IntegrateArgs a)
+{
+  layered_body<false, 0>(med, a);
+}
+
+template <int SV>
+__global__ __launch_bounds__(64) void k_layered_grad(DevMedium med, IntegrateArgs a)
+{
+  layered_body<true, SV>(med, a);
 }
 
 // Emission records of the current state (no stepping), e.g. for t = 0
@@ -581,8 +570,9 @@ __global__ __launch_bounds__(256) void k_emit(const double *__restrict__ F, cons
 hipError_t launch_integrate(const DevMedium &m, const IntegrateArgs &a, hipStream_t st)
 {
   const int64_t n = a.end - a.beg;
-  if (n <= 0) return hipSuccess;
+  if (n + a.nlist <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)((n + 255) / 256);
+  const unsigned lwaves = (unsigned)((n + a.nlist + 63) / 64);
   const unsigned waves = (unsigned)((n + block_of<MK_GRID>() - 1) / block_of<MK_GRID>());
   ProfScope prof(FGA_K_INTEGRATE, st);
   switch (m.kind) {
@@ -596,11 +586,10 @@ hipError_t launch_integrate(const DevMedium &m, const IntegrateArgs &a, hipStrea
     else hipLaunchKernelGGL(k_integrate<MK_GRID>, waves, block_of<MK_GRID>(), 0, st, m, a);
     break;
   default:
-    // layered media advance one step per launch, the interface step between
-    if (a.nsteps != 1 || a.stride != 0) return hipErrorInvalidValue;
-    if (m.any_grad && a.s_vector) hipLaunchKernelGGL(k_step_layered_grad<1>, blocks, 256, 0, st, m, a);
-    else if (m.any_grad) hipLaunchKernelGGL(k_step_layered_grad<0>, blocks, 256, 0, st, m, a);
-    else hipLaunchKernelGGL(k_step_layered, blocks, 256, 0, st, m, a);
+    if (a.nsteps > MAX_LAYERED_CHUNK) return hipErrorInvalidValue;
+    if (m.any_grad && a.s_vector) hipLaunchKernelGGL(k_layered_grad<1>, lwaves, 64, 0, st, m, a);
+    else if (m.any_grad) hipLaunchKernelGGL(k_layered_grad<0>, lwaves, 64, 0, st, m, a);
+    else hipLaunchKernelGGL(k_layered, lwaves, 64, 0, st, m, a);
     break;
   }
   return hipGetLastError();

@@ -1,7 +1,7 @@
 // Interface step of layered media (Sec. 3.1: eq:p:int, eq:Yilmaz,
-// eq:Inter_DzQDzP), run after every integrator step.
+// eq:Inter_DzQDzP), run on the beams that a launch of the integrator stopped.
 //
-// The integrator leaves a beam that left its layer during the step at the
+// The integrator leaves a beam that would leave its layer in a step at the
 // start of the step, flagged FGA_FLAG_CROSS.  Here each such beam redoes the
 // step to find where it left (speeds are constant inside a layer, so the ray
 // is the straight segment Q0 -> Q1 and the crossing fraction theta is found
@@ -440,6 +440,7 @@ template <bool WRITE>
 __global__ __launch_bounds__(256) void k_interface(DevMedium m, InterfaceArgs a)
 {
   const int64_t li = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (!WRITE && li == 0) *a.ncross = 0;
   const int64_t i = li < a.nlist ? a.list[li] : 0;
   const bool mine = li < a.nlist && (a.i32[FGA_FLAGS * a.cap + i] & FGA_FLAG_CROSS);
   if (!__syncthreads_or(mine)) {
@@ -466,7 +467,8 @@ __global__ __launch_bounds__(256) void k_interface(DevMedium m, InterfaceArgs a)
   const int sp_in = br == 0 ? 0 : 1;
   const int sigma = a.i32[FGA_SIGMA * cap + i];
   const int gen = a.i32[FGA_GEN * cap + i];
-  const int flags = a.i32[FGA_FLAGS * cap + i] & ~FGA_FLAG_CROSS;
+  // the children, and a beam that did not cross after all, go on with the next step
+  const int next = ((a.i32[FGA_FLAGS * cap + i] >> RESUME_SHIFT) + 1) << RESUME_SHIFT;
   const int64_t lin = a.lineage[i];
   const double wr = a.f64[FGA_W_RE * cap + i], wi = a.f64[FGA_W_IM * cap + i];
   if (c.th < 0.0) {
@@ -474,17 +476,18 @@ __global__ __launch_bounds__(256) void k_interface(DevMedium m, InterfaceArgs a)
     if (sp_in == 1) reframe_s(y, e);
     for (int f = 0; f < NS; ++f) a.f64[f * cap + i] = y[f];
     for (int d = 0; d < 3; ++d) a.f64[(FGA_E + d) * cap + i] = e[d];
-    a.i32[FGA_FLAGS * cap + i] = flags;
+    a.i32[FGA_FLAGS * cap + i] = FGA_FLAG_ALIVE | next;
     return;
   }
   unsigned long long nchild = 0;
-  if (c.nkeep == 0) a.i32[FGA_FLAGS * cap + i] = 0;  // retired (generation cap or no child)
+  if (c.nkeep == 0) a.i32[FGA_FLAGS * cap + i] = next;  // retired (generation cap or no child)
   double c_in, g_in[3], H6[6];
   medium_eval<MK_LAYERED>(m, sp_in, L, y + IQ, c_in, g_in, H6);  // at the crossing point
   int j = 0;
   for (int k = 0; k < 4; ++k) {
     if (!c.keep[k]) continue;
     const int64_t slot = j == 0 ? i : a.n + a.blk_off[blockIdx.x] + off + (j - 1);
+    const int born = j == 0 ? 0 : FLAG_BORN;
     ++j;
     const int layc = c.md.side[k] == 1 ? c.newL : L;
     const int spc = c.md.sp[k];
@@ -526,7 +529,7 @@ __global__ __launch_bounds__(256) void k_interface(DevMedium m, InterfaceArgs a)
     a.i32[FGA_SIGMA * cap + slot] = sigma;
     a.i32[FGA_LAYER * cap + slot] = layc;
     a.i32[FGA_GEN * cap + slot] = gen + 1;
-    a.i32[FGA_FLAGS * cap + slot] = FGA_FLAG_ALIVE;
+    a.i32[FGA_FLAGS * cap + slot] = FGA_FLAG_ALIVE | born | next;
     a.lineage[slot] = FGA_LINEAGE_CHILD(lin, gen, k);
     ++nchild;
   }
@@ -538,21 +541,10 @@ __global__ __launch_bounds__(256) void k_interface(DevMedium m, InterfaceArgs a)
 }
 
 
-// Crossing beams of [0, n): one atomic per wavefront reserves its run of the
-// (unordered) list; the list is then sorted, so the children's slots do not
-// depend on the order in which wavefronts ran.
-__global__ __launch_bounds__(256) void k_collect_cross(const int32_t *__restrict__ flags, int64_t n,
-                                                       int32_t *__restrict__ list, unsigned long long *__restrict__ count)
+__global__ __launch_bounds__(256) void k_clear_resume(int32_t *__restrict__ flags, int64_t n)
 {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const bool c = i < n && (flags[i] & FGA_FLAG_CROSS);
-  const unsigned long long b = __ballot(c);
-  if (b == 0) return;
-  const int lane = threadIdx.x & 63;
-  unsigned long long base = 0;
-  if (lane == 0) base = atomicAdd(count, (unsigned long long)__popcll(b));
-  base = __shfl(base, 0);
-  if (c) list[base + __popcll(b & ((1ull << lane) - 1))] = (int32_t)i;
+  if (i < n) flags[i] &= FLAG_MASK;
 }
 
 }  // namespace
@@ -565,26 +557,25 @@ size_t cross_sort_bytes(int64_t cap)
   return bytes;
 }
 
-hipError_t collect_crossers(const int32_t *flags, int64_t n, int32_t *list, int32_t *sorted,
-                            unsigned long long *count, void *tmp, size_t tmp_bytes, hipStream_t st,
-                            int64_t *ncross)
+hipError_t sort_crossers(const int32_t *list, int32_t *sorted, const unsigned long long *count, void *tmp,
+                         size_t tmp_bytes, hipStream_t st, int64_t *ncross)
 {
   *ncross = 0;
-  if (n <= 0) return hipSuccess;
-  hipError_t e = hipMemsetAsync(count, 0, sizeof(unsigned long long), st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_collect_cross, (unsigned)((n + 255) / 256), 256, 0, st, flags, n, list, count);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   unsigned long long h = 0;
-  if ((e = hipMemcpyAsync(&h, count, sizeof h, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-  if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-  if (h == 0) return hipSuccess;
+  hipError_t e = hipMemcpyAsync(&h, count, sizeof h, hipMemcpyDeviceToHost, st);
+  if (e != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess || h == 0) return e;
   if ((e = hipcub::DeviceRadixSort::SortKeys(tmp, tmp_bytes, list, sorted, (int)h, 0, 32, st)) != hipSuccess)
     return e;
   *ncross = (int64_t)h;
   return hipSuccess;
 }
 
+hipError_t launch_clear_resume(int32_t *flags, int64_t n, hipStream_t st)
+{
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_clear_resume, (unsigned)((n + 255) / 256), 256, 0, st, flags, n);
+  return hipGetLastError();
+}
 
 hipError_t launch_interface(const DevMedium &m, const InterfaceArgs &a, int write, hipStream_t st)
 {

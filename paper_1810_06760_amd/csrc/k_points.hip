@@ -185,7 +185,7 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
   const int64_t b0 = wk.blk * a.beams_per_block;
   const int64_t b1 = b0 + a.beams_per_block < a.nb ? b0 + a.beams_per_block : a.nb;
   const int s = wk.s;
-  const double *E = a.emit + (int64_t)s * 12 * a.nb;
+  const double *E = a.emit + (int64_t)s * 12 * a.ld;
   const double *TB = a.tile_box + (int64_t)s * a.ntiles * 6;
   const ScaledCoeffs K;
   uint64_t cnt = 0;          // wave-uniform in-window count
@@ -237,11 +237,11 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
       double q[3], pe[3], Bd[6];
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        q[d] = (Et + d * a.nb)[jl];
-        pe[d] = (Et + (3 + d) * a.nb)[jl];
+        q[d] = (Et + d * a.ld)[jl];
+        pe[d] = (Et + (3 + d) * a.ld)[jl];
       }
 #pragma unroll
-      for (int c = 0; c < 6; ++c) Bd[c] = (Et + (6 + c) * a.nb)[jl];
+      for (int c = 0; c < 6; ++c) Bd[c] = (Et + (6 + c) * a.ld)[jl];
       // dead beams and the ragged tail take a corner of the box as their place,
       // without phase or weight
       const bool mine = q[0] > -1.0e299 && lane < left;
@@ -306,19 +306,19 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
 
 // Per sample and 64-beam tile: bounding box of the live beams' centres Q
 // (lo[3], hi[3]; an all-dead tile gets an empty box +inf / -inf).
-__global__ __launch_bounds__(256) void k_tile_box(const double *__restrict__ emit, int64_t nb, int64_t ntiles,
+__global__ __launch_bounds__(256) void k_tile_box(const double *__restrict__ emit, int64_t nb, int64_t ld, int64_t ntiles,
                                                   double *__restrict__ box)
 {
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int s = blockIdx.y;
   if (t >= ntiles) return;
-  const double *E = emit + (int64_t)s * 12 * nb;
+  const double *E = emit + (int64_t)s * 12 * ld;
   const int64_t j = t * 64 + lane;
   double lo[3], hi[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const double q = j < nb ? E[d * nb + j] : -1.0e300;
+    const double q = j < nb ? E[d * ld + j] : -1.0e300;
     const bool dead = !(q > -1.0e299);
     lo[d] = dead ? INFINITY : q;
     hi[d] = dead ? -INFINITY : q;
@@ -406,10 +406,10 @@ hipError_t launch_sum_points(const PointsArgs &a, int *nblk_out, hipStream_t st)
   if (a.nb == 0 || a.n == 0 || a.m == 0) return hipSuccess;
   if (a.m > 65535) return hipErrorInvalidConfiguration;
   const int64_t ntiles = (a.nb + 63) / 64;
-  if (ntiles != a.ntiles) return hipErrorInvalidValue;
+  if (ntiles != a.ntiles || a.ld < a.nb) return hipErrorInvalidValue;
   if (!a.boxes_ready) {
     hipLaunchKernelGGL(k_tile_box, dim3((unsigned)((ntiles + 3) / 4), (unsigned)a.m), 256, 0, st, a.emit, a.nb,
-                       ntiles, a.tile_box);
+                       a.ld, ntiles, a.tile_box);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -34,8 +34,10 @@ constexpr double COS10 = 0.98480775301220805936;  // cos(10 degrees)
 //
 // LAST: the fourth stage, which forms no further stage input and writes y itself;
 // otherwise stage `st` of a loop.
-template <int MK, int SV = 0, bool LAST = false>
-__device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, double sg, bool isS,
+// EXIT (layered media, LAST): true, and y as it was, where the step's end lies
+// outside the beam's layer.
+template <int MK, int SV = 0, bool LAST = false, bool EXIT = false>
+__device__ __forceinline__ bool stage(const DevMedium &med, int sp, int layer, double sg, bool isS,
                                       const double e[3], double *__restrict__ y, double *__restrict__ yt,
                                       double *__restrict__ acc, int st, double dt,
                                       const MedBlock *blk = nullptr, CellCache *cells = nullptr)
@@ -74,10 +76,20 @@ __device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, d
   // the ray first: the next stage's point (after the last stage the next step's)
   // is known before the Jacobians' work begins, and its cell is asked for (the
   // trilinear medium's steps are all peeled)
+  if constexpr (EXIT) {
+    double q[3];
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const double k = sc * ph[j];
-    fold(IQ + j, k);
+    for (int j = 0; j < 3; ++j) q[j] = y[IQ + j] + h6 * (acc[IQ + j] + sc * ph[j]);
+    int iface, nl;
+    if (layer_exit(med, layer, q, iface, nl)) return true;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) y[IQ + j] = q[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const double k = sc * ph[j];
+      fold(IQ + j, k);
+    }
   }
   if (MK == MK_GRID && cells) cells->request(med, sp, LAST ? y + IQ : yt + IQ);
 
@@ -187,6 +199,7 @@ __device__ __forceinline__ void stage(const DevMedium &med, int sp, int layer, d
   for (int t = 0; t < (SV ? 6 : 4); ++t) fold(t < 4 ? IA + t : IAZ + t - 4, ka[t]);
 #pragma unroll
   for (int j = 0; j < 3; ++j) fold(IP + j, np * gn[j]);
+  return false;
 }
 
 // After a step: an S beam whose P has come within 10 degrees of its frame
@@ -230,8 +243,10 @@ __device__ __forceinline__ void reframe_s(double *y, double e[3]) { reframe_s(y 
 // 12.0 ms as a loop of four, 11.5 peeled).  All four in a row are 65 KB of code,
 // as much as the instruction cache holds for two compute units: 16.9 ms.  Callers
 // with many steps in a row of code (the interface step) keep the loop.
-template <int MK, int SV = 0, bool PEEL = false>
-__device__ __forceinline__ void rk4_step(const DevMedium &med, int sp, int layer, double sg, bool isS,
+// EXIT (layered media, with PEEL): a step that would leave the beam's layer is
+// not taken: y stays as it was and the result is true.
+template <int MK, int SV = 0, bool PEEL = false, bool EXIT = false>
+__device__ __forceinline__ bool rk4_step(const DevMedium &med, int sp, int layer, double sg, bool isS,
                                          const double e[3], double *y, double dt, const MedBlock *blk = nullptr,
                                          CellCache *cells = nullptr)
 {
@@ -246,7 +261,7 @@ __device__ __forceinline__ void rk4_step(const DevMedium &med, int sp, int layer
   }
   if constexpr (PEEL) {
     if (MK == MK_GRID && cells) cells->wait();
-    stage<MK, SV, true>(med, sp, layer, sg, isS, e, y, yt, acc, 3, dt, blk, cells);
+    if (stage<MK, SV, true, EXIT>(med, sp, layer, sg, isS, e, y, yt, acc, 3, dt, blk, cells)) return true;
   } else {
     const double h6 = dt / 6.0;
 #pragma unroll
@@ -265,6 +280,7 @@ __device__ __forceinline__ void rk4_step(const DevMedium &med, int sp, int layer
     y[IA + 3] -= api * ph[1];
     y[IAZ + 1] -= api * ph[2];
   }
+  return false;
 }
 
 // The pieces of the classic RK4 step where grad c = 0 (a homogeneous medium,
