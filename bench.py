@@ -52,10 +52,10 @@ HBM_PEAK = 8.0e12
 # scaled by a 1 GiB copy calibration; valid only while the kernel's source is
 # unchanged (sha256 prefix) and the beam set is the one profiled, else null
 TRAFFIC = {
-    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "9730ff55d3021186",
-                   "beams": 33044152, "bytes_per_launch": 2.1081e10},
-    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "b36f923df1fb4076",
-                  "beams": 33044152, "bytes_per_launch": 9.0506e9},
+    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "a1599d8314b21260",
+                   "beams": 33044152, "bytes_per_launch": 2.1306e10},
+    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "1294e8c4b42ae3ee",
+                  "beams": 33044152, "bytes_per_launch": 9.0501e9},
 }
 
 

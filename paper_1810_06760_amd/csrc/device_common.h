@@ -50,6 +50,51 @@ __device__ __forceinline__ bool layer_exit(const DevMedium &m, int L, const doub
   return false;
 }
 
+// Larger of a and b over two halves (pairs of 16-lane rows): of two values each
+// reduced half way, the lower halves (the even rows) hold a's and the upper b's.
+__device__ __forceinline__ double swap_max32(double a, double b)
+{
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false,
+                                                   false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false,
+                                                   false);
+  return fmax(__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1]));
+}
+__device__ __forceinline__ double swap_max16(double a, double b)
+{
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false,
+                                                   false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false,
+                                                   false);
+  return fmax(__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1]));
+}
+template <int ROR> __device__ __forceinline__ double row_max(double a)
+{
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(a), 0x120 + ROR, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(a), 0x120 + ROR, 0xf, 0xf, true);
+  return fmax(a, __hiloint2double(hi, lo));
+}
+
+// The bounding box lo[3], hi[3] of the q of the wavefront's lanes with `in`, into
+// box[6] (+inf / -inf without any).  All 64 lanes take part.
+__device__ __forceinline__ void store_tile_box(const double q[3], bool in, double *__restrict__ box)
+{
+  double v[6];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    v[d] = in ? -q[d] : -INFINITY;
+    v[3 + d] = in ? q[d] : -INFINITY;
+  }
+  const double w0 = swap_max32(v[0], v[1]), w1 = swap_max32(v[2], v[3]), w2 = swap_max32(v[4], v[5]);
+  // rows of 16 lanes: v0 v2 v1 v3, and v4 v4 v5 v5
+  double x0 = swap_max16(w0, w1), x1 = swap_max16(w2, w2);
+  x0 = row_max<1>(row_max<2>(row_max<4>(row_max<8>(x0))));
+  x1 = row_max<1>(row_max<2>(row_max<4>(row_max<8>(x1))));
+  const int lane = threadIdx.x & 63, row = lane >> 4;
+  const int k = (lane & 1) ? 4 + (row >> 1) : (row == 0 ? 0 : (row == 1 ? 2 : (row == 2 ? 1 : 3)));
+  if ((lane & 15) < ((row & 1) ? 1 : 2)) box[k] = (lane & 1) ? x1 : (k < 3 ? -x0 : x0);
+}
+
 // Level (z or radius) of interface iface, or of the free surface.
 __device__ __forceinline__ double iface_level(const DevMedium &m, int iface)
 {

@@ -26,8 +26,9 @@ using namespace rk;
 // Emission record of the current state: Q (3), P 128/(pi eps) (3), B = W A (3 complex),
 // W = w e^{iS/eps} (S does not change, so W is formed once per launch).
 // SV = 1: an S beam's state holds A itself (frame-free form).
+// Returns whether the record is a live one.
 template <int SV = 0>
-__device__ __forceinline__ void emit_record(double *__restrict__ out, int64_t nb, int64_t j,
+__device__ __forceinline__ bool emit_record(double *__restrict__ out, int64_t nb, int64_t j,
                                             const double *y, const double e[3], double Wr, double Wi,
                                             bool isS, double ieps)
 {
@@ -75,6 +76,7 @@ __device__ __forceinline__ void emit_record(double *__restrict__ out, int64_t nb
   for (int f = 0; f < 12; ++f) finite = finite && isfinite(r[f]);
 #pragma unroll
   for (int f = 0; f < 12; ++f) out[f * nb + j] = finite ? r[f] : (f < 3 ? -1.0e300 : 0.0);
+  return finite;
 }
 
 // W = w e^{iS/eps}
@@ -522,7 +524,8 @@ __global__ __launch_bounds__(256) void k_emit(const double *__restrict__ F, cons
 {
   const int64_t i = beg + (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t nb = end - beg, j = i - beg;
-  double q[3] = {-1.0e300, -1.0e300, -1.0e300};  // dead beams and the ragged tail
+  double q[3] = {0.0, 0.0, 0.0};
+  bool in = false;
   if (i < end) {
     if (!(I[FGA_FLAGS * cap + i] & FGA_FLAG_ALIVE)) {
       emit_dead(out, nb, j);
@@ -533,36 +536,13 @@ __global__ __launch_bounds__(256) void k_emit(const double *__restrict__ F, cons
       const double e[3] = {F[(FGA_E + 0) * cap + i], F[(FGA_E + 1) * cap + i], F[(FGA_E + 2) * cap + i]};
       double Wr, Wi;
       emit_weight(F[FGA_W_RE * cap + i], F[FGA_W_IM * cap + i], y[IS], ieps, Wr, Wi);
-      emit_record(out, nb, j, y, e, Wr, Wi, I[FGA_BRANCH * cap + i] != 0, ieps);
-      q[0] = y[IQ];
-      q[1] = y[IQ + 1];
-      q[2] = y[IQ + 2];
+      in = emit_record(out, nb, j, y, e, Wr, Wi, I[FGA_BRANCH * cap + i] != 0, ieps);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) q[d] = y[IQ + d];
     }
   }
-  if (box) {
-    const int lane = threadIdx.x & 63;
-    double lo[3], hi[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const bool dead = !(q[d] > -1.0e299);
-      lo[d] = dead ? INFINITY : q[d];
-      hi[d] = dead ? -INFINITY : q[d];
-      for (int off = 32; off > 0; off >>= 1) {
-        lo[d] = fmin(lo[d], __shfl_xor(lo[d], off));
-        hi[d] = fmax(hi[d], __shfl_xor(hi[d], off));
-      }
-    }
-    const int64_t t = (j - lane) >> 6;  // this wavefront's tile
-    if (lane < 6 && t * 64 < nb) {
-      double v = 0.0;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        if (lane == d) v = lo[d];
-        if (lane == 3 + d) v = hi[d];
-      }
-      box[t * 6 + lane] = v;
-    }
-  }
+  const int64_t t0 = j - (threadIdx.x & 63);  // this wavefront's tile
+  if (box && t0 < nb) store_tile_box(q, in, box + (t0 >> 6) * 6);
 }
 
 }  // namespace
