@@ -706,6 +706,8 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
       a.step0 = s0;
       a.stride = (rec && ns > 0) ? rec->stride : 0;
       a.emit = emit;
+      a.rec0 = b0;
+      a.ld = b1 - b0;
       a.eps_emit = rec ? rec->eps : 1.0;
       a.cutoff_abs = cutoff;
       a.counters = ctr;

@@ -106,11 +106,11 @@ struct IntegrateArgs {
   double cutoff_abs;
   unsigned long long *counters;  // [0] beam-steps, [1] culled, [2] quarantined
   int s_vector;              // 1: frame-free S amplitudes (grid media)
+  int64_t rec0, ld;          // slot of the first record, and the records' plane stride (emit is [n_emit][12][ld])
   // layered media: the beams are list[0, nlist), then the slots [beg, end)
   const int32_t *list;
   int64_t nlist;
   int64_t fresh_end;         // slots below it start the chunk anew: their flags hold no resume step
-  int64_t rec0, ld;          // slot of the first record, and the records' plane stride (emit is [n_emit][12][ld])
   int32_t *cross;            // slots that stopped at an interface, in no order
   unsigned long long *ncross;
 };

@@ -146,10 +146,10 @@ __device__ __forceinline__ void vector_to_frame(double *y, double e[3])
   y[IA + 3] = Ai[0] * nsh[0] + Ai[1] * nsh[1] + Ai[2] * nsh[2];
 }
 
-// Threads per workgroup: one wavefront in the trilinear medium, whose lanes keep
-// their cells in LDS (40 KB a wavefront, so four per compute unit fill it) and
-// share nothing.
-template <int MK> constexpr int block_of() { return MK == MK_GRID ? 64 : 256; }
+// Threads per workgroup: one wavefront, except in cubic media, where four share the
+// block of coefficients.  (In the trilinear medium a wavefront's cells take 40 KB
+// of LDS, so four fill a compute unit.)
+template <int MK> constexpr int block_of() { return MK == MK_GRID3 ? 256 : 64; }
 
 template <int MK, int SV = 0>
 __device__ __forceinline__ void integrate_body(const DevMedium &med, const IntegrateArgs &a)
@@ -253,8 +253,7 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
       for (int s = 0; s < a.nsteps; ++s) {
         if (live) {
           if constexpr (MK == MK_GRID) rk4_step<MK, SV, true>(med, sp, layer, sg, isS, e, y, dt, nullptr, &cells);
-          else if constexpr (MK == MK_GRID3) rk4_step<MK, SV, true>(med, sp, layer, sg, isS, e, y, dt, &blk);
-          else rk4_step_pc<MK>(med, sp, layer, sg, isS, y, dt);  // grad c = 0
+          else rk4_step<MK, SV, true>(med, sp, layer, sg, isS, e, y, dt, &blk);
           if (isS && !SV) reframe_s(y, e);
           ++steps_done;
           if (!(emitted_finite<SV>(y) && s_finite)) {
@@ -281,8 +280,11 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
           else emit_dead(rec, nb, j);
         }
       }
-      {
       if (SV && isS) vector_to_frame(y, e);
+      // the steps leave S as it was: not stored (the addresses are formed anew: kept from the loads they would take a
+      // hundred registers through the steps)
+      int64_t io = i;
+      asm volatile("" : "+v"(io));
       if (live) {
         bool finite = true;
 #pragma unroll
@@ -292,19 +294,12 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
           quar = 1;
         }
       }
-      // the steps leave S as it was, and where grad c = 0 P and dzP too: not stored
-      // (the addresses are formed anew: kept from the loads they would take a
-      // hundred registers through the steps)
-      int64_t io = i;
-      asm volatile("" : "+v"(io));
 #pragma unroll
       for (int f = 0; f < NS; ++f)
-        if (f != IS && (MK == MK_GRID || MK == MK_GRID3 || !((f >= IP && f < IP + 3) || (f >= IZPR && f < IZPR + 18))))
-          F[f * cap + io] = y[f];
+        if (f != IS) F[f * cap + io] = y[f];
 #pragma unroll
       for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + io] = e[d];
       a.i32[FGA_FLAGS * cap + i] = flags;
-      }
     }
   }
   // wavefront-level reduction of the counters, one atomic per wavefront
@@ -336,151 +331,145 @@ __global__ __launch_bounds__(block_of<MK>()) void k_integrate(DevMedium med, Int
 // it was appended (FLAG_BORN), dead records.
 //
 // GRAD: some layer has a speed gradient (rays bend): the general RK4 step.  Else
-// P, dzP and so d(dzQ)/dt = K are constant in a layer, and K is formed once a
-// launch; two wavefronts per SIMD.  One step per launch, with the state's 0.6 to
+// ConstRates, with two wavefronts per SIMD; a homogeneous medium is that without
+// layers (LAYERS false).  One step per launch, with the state's 0.6 to
 // 0.9 KB a beam to and from memory, a scan of all beams for those that stopped and
 // the interface kernels each time, was bound by memory and launches: 898 k beams of
 // a point source in a layered Earth took 410 us a step and sample beside the sums,
-// chunks of 16 steps 112; 553 k beams in the crosswell model (GRAD) 190 and 77.
-template <bool GRAD, int SV>
+// chunks of 16 steps 66; 553 k beams in the crosswell model (GRAD) 190 and 77.
+template <bool LAYERS, bool GRAD, int SV>
 __device__ __forceinline__ void layered_body(const DevMedium &med, const IntegrateArgs &a)
 {
   const int64_t idx = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const int64_t cap = a.cap;
+  double *__restrict__ F = a.f64;
+  const bool active = idx < a.nlist + (a.end - a.beg);
+  const int64_t i = !active ? 0 : (LAYERS && idx < a.nlist ? (int64_t)a.list[idx] : a.beg + (idx - a.nlist));
   unsigned long long steps_done = 0, culled = 0, quar = 0;
-  bool cross = false;
-  int64_t i = 0;
-  if (idx < a.nlist + (a.end - a.beg)) {
-    i = idx < a.nlist ? (int64_t)a.list[idx] : a.beg + (idx - a.nlist);
-    const int64_t cap = a.cap, j = i - a.rec0;
-    double *__restrict__ F = a.f64;
-    int32_t flags = a.i32[FGA_FLAGS * cap + i];
-    const bool fresh = idx >= a.nlist && i < a.fresh_end;
-    const int resume = fresh ? 0 : flags >> RESUME_SHIFT;
-    // the first step whose sample this launch writes
-    const int first = (fresh || (flags & FLAG_BORN)) ? 0 : (resume > 0 ? resume - 1 : 0);
-    const int born = fresh ? 0 : resume - 1;  // the step whose end the state is at, if of this chunk
-    flags &= FGA_FLAG_ALIVE | FGA_FLAG_QUARANTINED;
-    const int first_emit = a.stride ? a.step0 / a.stride : 0;
-    auto record = [&](int s) {
-      return a.emit + (int64_t)((a.step0 + s + 1) / a.stride - 1 - first_emit) * 12 * a.ld;
-    };
-    if (!(flags & FGA_FLAG_ALIVE)) {
-      if (a.stride)
-        for (int s = first; s < a.nsteps; ++s)
-          if ((a.step0 + s + 1) % a.stride == 0) emit_dead(record(s), a.ld, j);
-      a.i32[FGA_FLAGS * cap + i] = flags;
-    } else {
-      const int br = a.i32[FGA_BRANCH * cap + i];
-      const double sg = (double)a.i32[FGA_SIGMA * cap + i];
-      const int layer = a.i32[FGA_LAYER * cap + i];
-      const int sp = br == 0 ? 0 : 1;
-      const bool isS = br != 0;
-      double y[nstate<SV>()], e[3];
+  int32_t flags = active ? a.i32[FGA_FLAGS * cap + i] : 0;
+  const bool fresh = !LAYERS || (idx >= a.nlist && i < a.fresh_end);
+  const int resume = fresh ? 0 : flags >> RESUME_SHIFT;
+  // the first step whose sample this launch writes, and the step whose end the
+  // state is at (if of this chunk)
+  const int first = (fresh || (flags & FLAG_BORN)) ? 0 : (resume > 0 ? resume - 1 : 0);
+  const int born = fresh ? 0 : resume - 1;
+  flags &= FGA_FLAG_ALIVE | FGA_FLAG_QUARANTINED;
+  const bool alive = active && (flags & FGA_FLAG_ALIVE);
+  const int first_emit = a.stride ? a.step0 / a.stride : 0;
+  const double dt = a.dt;
+  const double ieps = 1.0 / a.eps_emit;
+  __shared__ double2 zp_lds[GRAD ? 1 : 9 * 64];
+  const ZpLds zp{zp_lds};
+  ConstRates rates;
+  int layer = 0, sp = 0;
+  bool isS = false, live = alive, cross = false, s_finite = false, zp_finite = true;
+  double sg = 0.0, wabs = 0.0, Wr = 0.0, Wi = 0.0;
+  double y[nstate<SV>()], e[3];
+  if (alive) {
+    const int br = a.i32[FGA_BRANCH * cap + i];
+    sg = (double)a.i32[FGA_SIGMA * cap + i];
+    layer = a.i32[FGA_LAYER * cap + i];
+    sp = br == 0 ? 0 : 1;
+    isS = br != 0;
 #pragma unroll
-      for (int f = 0; f < NS; ++f) y[f] = F[f * cap + i];
+    for (int f = 0; f < NS; ++f) y[f] = F[f * cap + i];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) e[d] = F[(FGA_E + d) * cap + i];
-      if (SV) {
-        y[nstate<SV>() - 2] = 0.0;
-        y[nstate<SV>() - 1] = 0.0;
-      }
-      const double wr = F[FGA_W_RE * cap + i], wi = F[FGA_W_IM * cap + i];
-      const double dt = a.dt;
-      const double ieps = 1.0 / a.eps_emit;
-      const double wabs = sqrt(wr * wr + wi * wi);
-      const double S = y[IS];
-      const bool s_finite = isfinite(S);
-      double Wr = 0.0, Wi = 0.0;
-      if (a.stride) emit_weight(wr, wi, S, ieps, Wr, Wi);
-      double kQ[3], ph[3], ci, kr[9], ki[9];
-      if constexpr (!GRAD) {
-        pc_ray_rates(isS ? med.csl[layer] : med.cpl[layer], sg, y + IP, kQ, ph, ci);
-        pc_jac_rates(ph, ci, y + IZPR, y + IZPI, kr, ki);
-      }
-      bool live = true;
-      for (int s = 0; s < a.nsteps; ++s) {
-        if (s >= resume && live && !cross) {
-          if constexpr (GRAD) {
-            double A0[4];
-            if (SV) {
-#pragma unroll
-              for (int t = 0; t < 4; ++t) A0[t] = y[IA + t];
-              if (isS) frame_to_vector(y, e);
-            }
-            cross = rk4_step<MK_LAYERED, SV, true, true>(med, sp, layer, sg, isS, e, y, dt);
-            if (SV && cross) {
-#pragma unroll
-              for (int t = 0; t < 4; ++t) y[IA + t] = A0[t];
-            } else if (isS && SV) {
-              vector_to_frame(y, e);
-            } else if (isS && !cross) {
-              reframe_s(y, e);
-            }
-          } else {
-            const double h6 = dt / 6.0;
-            double q[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) q[d] = rk4_const(y[IQ + d], kQ[d], h6);
-            int iface, nl;
-            cross = layer_exit(med, layer, q, iface, nl);
-            if (!cross) {
-              double z0r[9], z0i[9];
-#pragma unroll
-              for (int d = 0; d < 3; ++d) y[IQ + d] = q[d];
-#pragma unroll
-              for (int o = 0; o < 9; ++o) {
-                z0r[o] = y[IZQR + o] - y[IZPI + o];
-                z0i[o] = y[IZQI + o] + y[IZPR + o];
-                y[IZQR + o] = rk4_const(y[IZQR + o], kr[o], h6);
-                y[IZQI + o] = rk4_const(y[IZQI + o], ki[o], h6);
-              }
-              pc_amplitude(z0r, z0i, kr, ki, isS, y + IA, dt);
-              if (isS) reframe_s(y, e);
-            }
-          }
-          ++steps_done;
-          if (cross) {
-            flags = FGA_FLAG_ALIVE | FGA_FLAG_CROSS | (s << RESUME_SHIFT);
-          } else if (!(emitted_finite(y) && s_finite)) {
-            live = false;
-            flags = FGA_FLAG_QUARANTINED;
-            quar = 1;
-          } else if (a.cutoff_abs > 0.0) {
-            const double m0 = y[IA] * y[IA] + y[IA + 1] * y[IA + 1];
-            const double m1 = y[IA + 2] * y[IA + 2] + y[IA + 3] * y[IA + 3];
-            if (wabs * sqrt(m0 > m1 ? m0 : m1) < a.cutoff_abs) {
-              live = false;
-              flags = 0;
-              culled = 1;
-            }
-          }
-        }
-        if (a.stride && s >= first && !cross && (a.step0 + s + 1) % a.stride == 0) {
-          if (live && s >= born) emit_record(record(s), a.ld, j, y, e, Wr, Wi, isS, ieps);
-          else emit_dead(record(s), a.ld, j);
-        }
-      }
-      if (live && !cross) {
-        bool finite = true;
-#pragma unroll
-        for (int f = 0; f < NS; ++f) finite = finite && isfinite(y[f]);
-        if (!finite) {
-          flags = FGA_FLAG_QUARANTINED;
-          quar = 1;
-        }
-      }
-      // the addresses are formed anew: kept from the loads they would take a
-      // hundred registers through the steps
-      int64_t io = i;
-      asm volatile("" : "+v"(io));
-#pragma unroll
-      for (int f = 0; f < NS; ++f)
-        if (f != IS && (GRAD || !((f >= IP && f < IP + 3) || (f >= IZPR && f < IZPR + 18)))) F[f * cap + io] = y[f];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + io] = e[d];
-      a.i32[FGA_FLAGS * cap + io] = flags;
+    for (int d = 0; d < 3; ++d) e[d] = F[(FGA_E + d) * cap + i];
+    if (SV) {
+      y[nstate<SV>() - 2] = 0.0;
+      y[nstate<SV>() - 1] = 0.0;
+    }
+    const double wr = F[FGA_W_RE * cap + i], wi = F[FGA_W_IM * cap + i];
+    wabs = sqrt(wr * wr + wi * wi);
+    const double S = y[IS];
+    s_finite = isfinite(S);
+    if (a.stride) emit_weight(wr, wi, S, ieps, Wr, Wi);
+    if (!LAYERS && !(isfinite(wabs) && isfinite(e[0]) && isfinite(e[1]) && isfinite(e[2]))) {
+      live = false;
+      flags = FGA_FLAG_QUARANTINED;
+      quar = 1;
+    }
+    if constexpr (!GRAD) {
+      zp_finite = zp.put(y);
+      rates.init(LAYERS ? (isS ? med.csl[layer] : med.cpl[layer]) : (isS ? med.cs : med.cp), sg, y, zp);
     }
   }
+  for (int s = 0; s < a.nsteps; ++s) {
+    if (s >= resume && live && !cross) {
+      if constexpr (GRAD) {
+        double A0[4];
+        if (SV) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) A0[t] = y[IA + t];
+          if (isS) frame_to_vector(y, e);
+        }
+        cross = rk4_step<MK_LAYERED, SV, true, true>(med, sp, layer, sg, isS, e, y, dt);
+        if (SV && cross) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) y[IA + t] = A0[t];
+        } else if (isS && SV) {
+          vector_to_frame(y, e);
+        } else if (isS && !cross) {
+          reframe_s(y, e);
+        }
+      } else {
+        double q[3];
+        rates.move(y + IQ, dt / 6.0, q);
+        int iface, nl;
+        if (LAYERS) cross = layer_exit(med, layer, q, iface, nl);
+        if (!cross) {
+#pragma unroll
+          for (int d = 0; d < 3; ++d) y[IQ + d] = q[d];
+          rates.step(y + IA, isS, dt, zp);
+          if (isS) reframe_s(y, e);
+        }
+      }
+      ++steps_done;
+      if (cross) {
+        flags = FGA_FLAG_ALIVE | FGA_FLAG_CROSS | (s << RESUME_SHIFT);
+      } else if (!(emitted_finite(y) && s_finite)) {
+        live = false;
+        flags = FGA_FLAG_QUARANTINED;
+        quar = 1;
+      } else if (a.cutoff_abs > 0.0) {
+        const double m0 = y[IA] * y[IA] + y[IA + 1] * y[IA + 1];
+        const double m1 = y[IA + 2] * y[IA + 2] + y[IA + 3] * y[IA + 3];
+        if (wabs * sqrt(m0 > m1 ? m0 : m1) < a.cutoff_abs) {
+          live = false;
+          flags = 0;
+          culled = 1;
+        }
+      }
+    }
+    if (a.stride && active && s >= first && !cross && (a.step0 + s + 1) % a.stride == 0) {
+      double *rec = a.emit + (int64_t)((a.step0 + s + 1) / a.stride - 1 - first_emit) * 12 * a.ld;
+      if (live && s >= born) emit_record(rec, a.ld, i - a.rec0, y, e, Wr, Wi, isS, ieps);
+      else emit_dead(rec, a.ld, i - a.rec0);
+    }
+  }
+  if (alive) {
+    if constexpr (!GRAD) rates.store(y);
+    if (live && !cross) {
+      bool finite = zp_finite && s_finite;
+#pragma unroll
+      for (int f = 0; f < NS; ++f)
+        if (f != IS && (GRAD || f < IZPR || f >= IZPR + 18)) finite = finite && isfinite(y[f]);
+      if (!finite) {
+        flags = FGA_FLAG_QUARANTINED;
+        quar = 1;
+      }
+    }
+    // the addresses are formed anew: kept from the loads they would take a
+    // hundred registers through the steps
+    int64_t io = i;
+    asm volatile("" : "+v"(io));
+#pragma unroll
+    for (int f = 0; f < NS; ++f)
+      if (f != IS && (GRAD || !((f >= IP && f < IP + 3) || (f >= IZPR && f < IZPR + 18)))) F[f * cap + io] = y[f];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) F[(FGA_E + d) * cap + io] = e[d];
+  }
+  if (active) a.i32[FGA_FLAGS * cap + i] = flags;
   const int lane = threadIdx.x & 63;
   const unsigned long long stopped = __ballot(cross);
   if (stopped) {
@@ -504,13 +493,19 @@ __device__ __forceinline__ void layered_body(const DevMedium &med, const Integra
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_layered(DevMedium med,
                                                                                            IntegrateArgs a)
 {
-  layered_body<false, 0>(med, a);
+  layered_body<true, false, 0>(med, a);
 }
 
 template <int SV>
 __global__ __launch_bounds__(64) void k_layered_grad(DevMedium med, IntegrateArgs a)
 {
-  layered_body<true, SV>(med, a);
+  layered_body<true, true, SV>(med, a);
+}
+
+// A homogeneous medium: the same body without layers to leave.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_homog(DevMedium med, IntegrateArgs a)
+{
+  layered_body<false, false, 0>(med, a);
 }
 
 // Emission records of the current state (no stepping), e.g. for t = 0
@@ -552,24 +547,23 @@ hipError_t launch_integrate(const DevMedium &m, const IntegrateArgs &a, hipStrea
   const int64_t n = a.end - a.beg;
   if (n + a.nlist <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)((n + 255) / 256);
-  const unsigned lwaves = (unsigned)((n + a.nlist + 63) / 64);
-  const unsigned waves = (unsigned)((n + block_of<MK_GRID>() - 1) / block_of<MK_GRID>());
+  const unsigned waves = (unsigned)((n + a.nlist + 63) / 64);
   ProfScope prof(FGA_K_INTEGRATE, st);
   switch (m.kind) {
-  case FGA_MEDIUM_HOMOGENEOUS: hipLaunchKernelGGL(k_integrate<MK_HOMOG>, blocks, 256, 0, st, m, a); break;
+  case FGA_MEDIUM_HOMOGENEOUS: hipLaunchKernelGGL(k_homog, waves, 64, 0, st, m, a); break;
   case FGA_MEDIUM_GRID:
     // frame-free S amplitudes: a variant of the grid-medium kernels (in a
     // homogeneous medium P is constant and the two forms are one)
     if (m.smooth && a.s_vector) hipLaunchKernelGGL((k_integrate<MK_GRID3, 1>), blocks, 256, 0, st, m, a);
     else if (m.smooth) hipLaunchKernelGGL(k_integrate<MK_GRID3>, blocks, 256, 0, st, m, a);
-    else if (a.s_vector) hipLaunchKernelGGL((k_integrate<MK_GRID, 1>), waves, block_of<MK_GRID>(), 0, st, m, a);
-    else hipLaunchKernelGGL(k_integrate<MK_GRID>, waves, block_of<MK_GRID>(), 0, st, m, a);
+    else if (a.s_vector) hipLaunchKernelGGL((k_integrate<MK_GRID, 1>), waves, 64, 0, st, m, a);
+    else hipLaunchKernelGGL(k_integrate<MK_GRID>, waves, 64, 0, st, m, a);
     break;
   default:
     if (a.nsteps > MAX_LAYERED_CHUNK) return hipErrorInvalidValue;
-    if (m.any_grad && a.s_vector) hipLaunchKernelGGL(k_layered_grad<1>, lwaves, 64, 0, st, m, a);
-    else if (m.any_grad) hipLaunchKernelGGL(k_layered_grad<0>, lwaves, 64, 0, st, m, a);
-    else hipLaunchKernelGGL(k_layered, lwaves, 64, 0, st, m, a);
+    if (m.any_grad && a.s_vector) hipLaunchKernelGGL(k_layered_grad<1>, waves, 64, 0, st, m, a);
+    else if (m.any_grad) hipLaunchKernelGGL(k_layered_grad<0>, waves, 64, 0, st, m, a);
+    else hipLaunchKernelGGL(k_layered, waves, 64, 0, st, m, a);
     break;
   }
   return hipGetLastError();

@@ -283,76 +283,65 @@ __device__ __forceinline__ bool rk4_step(const DevMedium &med, int sp, int layer
   return false;
 }
 
-// The pieces of the classic RK4 step where grad c = 0 (a homogeneous medium,
-// or inside one layer of a layered medium).  There P and dzP have zero
-// derivative and Q and dzQ constant ones, so every stage's derivative of
-// those equals the first; only the amplitudes' derivative depends on the
-// stage, through Z = dzQ + i dzP at the stage input in tr(Z^{-1} dZ/dt).
-// Since dzP is fixed, Z at a stage input is Z0 + c K with Z0 = Z at the step's
-// start and K = d(dzQ)/dt.  The stage formulas, weights and summation order
-// are those of rk4_step with the medium's gradient and Hessian at zero
-// (omega = 0 for S beams), so the two agree to rounding.
+// The classic RK4 step where grad c = 0 (a homogeneous medium, or inside one layer
+// of a layered medium).  There P and dzP have zero derivative and Q and dzQ
+// constant ones, so Q and dzQ, and with it Z = dzQ + i dzP, move by h/6 X, X = 6
+// times their rate, for as long as the beam stays in its layer.  The amplitudes' derivative is s a,
+// s = tr(Z^{-1} dZ/dt)/2 at the stage's time: the two middle stages share one s and
+// a step's last s is the next one's first, so a step needs two traces, and both
+// amplitudes (complex a_P; a_SV and a_SH, omega = 0) grow by one complex factor.
+// The formulas are those of rk4_step with the medium's gradient and Hessian at
+// zero, so the two agree to rounding.  With four traces a step, K formed anew and
+// one wavefront per SIMD 98 k beams x 50 steps in a homogeneous medium took 247 us
+// and 898 k beams x 48 steps and records in a layered Earth 4.0 ms; so 132 us and
+// 2.0 ms, the latter 3.5 TB/s of state and records.
+// dzP is read through a functor (re(o), im(o) of entry o), from registers or LDS.
+struct ConstRates {
+  double xq[3];                          // 6 dQ/dt
+  double qr[9], qi[9], xr[9], xi[9];     // dzQ and 6 d(dzQ)/dt, rows m (the derivative by one z_m)
+  double sr, si;                         // s at dzQ
 
-// y0 + dt/6 (k + 2k + 2k + k) for a derivative equal in all four stages,
-// summed in rk4_step's order.
-__device__ __forceinline__ double rk4_const(double y0, double k, double h6)
-{
-  return y0 + h6 * (((k + 2.0 * k) + 2.0 * k) + k);
-}
-
-// dQ/dt for speed c (eq:char_plus, eq:char_minus); also P/|P| and
-// sigma c / |P| for the Jacobian rates.
-__device__ __forceinline__ void pc_ray_rates(double c, double sg, const double P[3], double kQ[3], double ph[3],
-                                             double &ci)
-{
-  const double inp = fast_rsqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
-  ph[0] = P[0] * inp;
-  ph[1] = P[1] * inp;
-  ph[2] = P[2] * inp;
-  const double sc = sg * c;
-  ci = sc * inp;
+  // for speed c: dQ/dt = sigma c Phat (eq:char_plus, eq:char_minus), d(dzQ)/dt =
+  // sigma c dzP (I - Phat (x) Phat)/|P| (eq:DzDt with grad c = 0)
+  template <class ZP> __device__ __forceinline__ void init(double c, double sg, const double *y, const ZP &zp)
+  {
+    const double *P = y + IP, *pr = y + IZPR, *pi = y + IZPI;
+    const double inp = fast_rsqrt(P[0] * P[0] + P[1] * P[1] + P[2] * P[2]);
+    const double ph[3] = {P[0] * inp, P[1] * inp, P[2] * inp};
+    const double sc = 6.0 * sg * c, ci = sc * inp;
 #pragma unroll
-  for (int j = 0; j < 3; ++j) kQ[j] = sc * ph[j];
-}
-
-// d(dzQ)/dt = sigma c dzP (I - P (x) P/|P|^2)/|P| (eq:DzDt with grad c = 0),
-// rows m, real and imaginary parts; dzr/dzi are dzP's.
-__device__ __forceinline__ void pc_jac_rates(const double ph[3], double ci, const double dzr[9],
-                                             const double dzi[9], double kr[9], double ki[9])
-{
+    for (int j = 0; j < 3; ++j) xq[j] = sc * ph[j];
 #pragma unroll
-  for (int m = 0; m < 3; ++m) {
-    const double vr = dzr[3 * m] * ph[0] + dzr[3 * m + 1] * ph[1] + dzr[3 * m + 2] * ph[2];
-    const double vi = dzi[3 * m] * ph[0] + dzi[3 * m + 1] * ph[1] + dzi[3 * m + 2] * ph[2];
+    for (int m = 0; m < 3; ++m) {
+      const double vr = pr[3 * m] * ph[0] + pr[3 * m + 1] * ph[1] + pr[3 * m + 2] * ph[2];
+      const double vi = pi[3 * m] * ph[0] + pi[3 * m + 1] * ph[1] + pi[3 * m + 2] * ph[2];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      kr[3 * m + j] = ci * (dzr[3 * m + j] - vr * ph[j]);
-      ki[3 * m + j] = ci * (dzi[3 * m + j] - vi * ph[j]);
+      for (int j = 0; j < 3; ++j) {
+        const int o = 3 * m + j;
+        xr[o] = ci * (pr[o] - vr * ph[j]);
+        xi[o] = ci * (pi[o] - vi * ph[j]);
+        qr[o] = y[IZQR + o];
+        qi[o] = y[IZQI + o];
+      }
     }
+    trace(zp, 0.0, sr, si);
   }
-}
 
-// The four stages of the amplitudes (eq:amp_P, eq:amp_SV, eq:amp_SH with
-// grad c = 0: da/dt = a tr(Z^{-1} dZ/dt)/2), a[4] = (re, im) of a_P or of
-// (a_SV, a_SH), advanced in place.
-__device__ __forceinline__ void pc_amplitude(const double z0r[9], const double z0i[9], const double kr[9],
-                                             const double ki[9], bool isS, double a0[4], double dt)
-{
-  const double h2 = 0.5 * dt, h6 = dt / 6.0;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  double a[4] = {a0[0], a0[1], a0[2], a0[3]};  // stage input
-#pragma nounroll
-  for (int st = 0; st < 4; ++st) {
-    const double cs = st == 0 ? 0.0 : (st == 3 ? dt : h2);  // this stage's input: Z0 + cs K
-    const double wacc = (st == 0 || st == 3) ? 1.0 : 2.0;
-    const double cnext = st == 2 ? dt : (st == 3 ? 0.0 : h2);
-    double zr[9], zi[9];
+  // s at dzQ + h X
+  template <class ZP> __device__ __forceinline__ void trace(const ZP &zp, double h, double &s_r, double &s_i) const
+  {
+    double ar[9], ai[9];
+    zp.again();
 #pragma unroll
     for (int o = 0; o < 9; ++o) {
-      zr[o] = z0r[o] + cs * kr[o];
-      zi[o] = z0i[o] + cs * ki[o];
+      ar[o] = qr[o] - zp.im(o);
+      ai[o] = qi[o] + zp.re(o);
+      if (h != 0.0) {
+        ar[o] += h * xr[o];
+        ai[o] += h * xi[o];
+      }
     }
-    // cofactors (cyclic index form), det Z and T = cof(Z) : dZ/dt, dZ/dt = K
+    // cofactors (cyclic index form), det Z and T = cof(Z) : X
     double detr = 0.0, deti = 0.0, Tr = 0.0, Ti = 0.0;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -361,33 +350,101 @@ __device__ __forceinline__ void pc_amplitude(const double z0r[9], const double z
       for (int j = 0; j < 3; ++j) {
         const int j1 = (j + 1) % 3, j2 = (j + 2) % 3;
         const int ia = 3 * i1 + j1, ib = 3 * i2 + j2, ic = 3 * i1 + j2, id = 3 * i2 + j1;
-        const double Cr = (zr[ia] * zr[ib] - zi[ia] * zi[ib]) - (zr[ic] * zr[id] - zi[ic] * zi[id]);
-        const double Ci = (zr[ia] * zi[ib] + zi[ia] * zr[ib]) - (zr[ic] * zi[id] + zi[ic] * zr[id]);
+        const double Cr = (ar[ia] * ar[ib] - ai[ia] * ai[ib]) - (ar[ic] * ar[id] - ai[ic] * ai[id]);
+        const double Ci = (ar[ia] * ai[ib] + ai[ia] * ar[ib]) - (ar[ic] * ai[id] + ai[ic] * ar[id]);
         if (i == 0) {
-          detr += zr[j] * Cr - zi[j] * Ci;
-          deti += zr[j] * Ci + zi[j] * Cr;
+          detr += ar[j] * Cr - ai[j] * Ci;
+          deti += ar[j] * Ci + ai[j] * Cr;
         }
-        Tr += Cr * kr[3 * i + j] - Ci * ki[3 * i + j];
-        Ti += Cr * ki[3 * i + j] + Ci * kr[3 * i + j];
+        Tr += Cr * xr[3 * i + j] - Ci * xi[3 * i + j];
+        Ti += Cr * xi[3 * i + j] + Ci * xr[3 * i + j];
       }
     }
-    const double idd = fast_rcp(detr * detr + deti * deti);
-    const double sr = 0.5 * ((Tr * detr + Ti * deti) * idd);
-    const double si = 0.5 * ((Ti * detr - Tr * deti) * idd);
-    double ka[4];
-    ka[0] = sr * a[0] - si * a[1];
-    ka[1] = sr * a[1] + si * a[0];
-    ka[2] = isS ? sr * a[2] - si * a[3] : 0.0;
-    ka[3] = isS ? sr * a[3] + si * a[2] : 0.0;
+    const double idd = (1.0 / 12.0) * fast_rcp(detr * detr + deti * deti);
+    s_r = (Tr * detr + Ti * deti) * idd;
+    s_i = (Ti * detr - Tr * deti) * idd;
+  }
+
+  // where a step of 6 h6 takes Q
+  __device__ __forceinline__ void move(const double *Q, double h6, double q[3]) const
+  {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      acc[t] += wacc * ka[t];
-      a[t] = a0[t] + cnext * ka[t];
+    for (int j = 0; j < 3; ++j) q[j] = Q[j] + h6 * xq[j];
+  }
+
+  // dzQ and the amplitudes a[4] = (re, im) of a_P or of (a_SV, a_SH) over a step dt
+  template <class ZP> __device__ __forceinline__ void step(double a[4], bool isS, double dt, const ZP &zp)
+  {
+    const double h2 = 0.5 * dt, h6 = dt / 6.0;
+    double mr, mi;
+    trace(zp, 0.5 * h6, mr, mi);
+    double kr = sr, ki = si;  // the stages' derivatives for a = 1
+    double gr = kr, gi = ki;
+#pragma unroll
+    for (int st = 1; st < 3; ++st) {
+      const double ur = 1.0 + h2 * kr, ui = h2 * ki;
+      kr = mr * ur - mi * ui;
+      ki = mr * ui + mi * ur;
+      gr += 2.0 * kr;
+      gi += 2.0 * ki;
+    }
+#pragma unroll
+    for (int o = 0; o < 9; ++o) {
+      qr[o] += h6 * xr[o];
+      qi[o] += h6 * xi[o];
+    }
+    trace(zp, 0.0, sr, si);
+    const double ur = 1.0 + dt * kr, ui = dt * ki;
+    gr = h6 * (gr + (sr * ur - si * ui));
+    gi = h6 * (gi + (sr * ui + si * ur));
+    const double a0 = a[0], a1 = a[1];
+    a[0] += gr * a0 - gi * a1;
+    a[1] += gr * a1 + gi * a0;
+    if (isS) {
+      const double a2 = a[2], a3 = a[3];
+      a[2] += gr * a2 - gi * a3;
+      a[3] += gr * a3 + gi * a2;
     }
   }
+
+  __device__ __forceinline__ void store(double *y) const
+  {
 #pragma unroll
-  for (int t = 0; t < 4; ++t) a0[t] += h6 * acc[t];
-}
+    for (int o = 0; o < 9; ++o) {
+      y[IZQR + o] = qr[o];
+      y[IZQI + o] = qi[o];
+    }
+  }
+};
+
+// dzP in the state y
+struct ZpOf {
+  const double *y;
+  __device__ __forceinline__ double re(int o) const { return y[IZPR + o]; }
+  __device__ __forceinline__ double im(int o) const { return y[IZPI + o]; }
+  __device__ __forceinline__ void again() const {}
+};
+
+// dzP of the wavefront's beams in LDS, [9][64] of (re, im): the registers it would
+// take through the steps are what keeps a second wavefront off the SIMD
+struct ZpLds {
+  double2 *lds;
+  // returns whether all are finite
+  __device__ __forceinline__ bool put(const double *y) const
+  {
+    bool finite = true;
+#pragma unroll
+    for (int o = 0; o < 9; ++o) {
+      lds[o * 64 + threadIdx.x] = double2{y[IZPR + o], y[IZPI + o]};
+      finite = finite && isfinite(y[IZPR + o]) && isfinite(y[IZPI + o]);
+    }
+    return finite;
+  }
+  __device__ __forceinline__ double re(int o) const { return lds[o * 64 + threadIdx.x].x; }
+  __device__ __forceinline__ double im(int o) const { return lds[o * 64 + threadIdx.x].y; }
+  // what follows reads LDS (and does not keep what was read or written before)
+  __device__ __forceinline__ void again() const { asm volatile("" ::: "memory"); }
+};
 
 // One classic RK4 step of the whole state y where grad c = 0, in place.
 template <int MK>
@@ -396,23 +453,15 @@ __device__ __forceinline__ void rk4_step_pc(const DevMedium &med, int sp, int la
 {
   double c, g[3], H6[6];
   medium_eval<MK>(med, sp, layer, y + IQ, c, g, H6);
-  double kQ[3], ph[3], ci, kr[9], ki[9], z0r[9], z0i[9];
-  pc_ray_rates(c, sg, y + IP, kQ, ph, ci);
-  pc_jac_rates(ph, ci, y + IZPR, y + IZPI, kr, ki);
+  ConstRates r;
+  const ZpOf zp{y};
+  r.init(c, sg, y, zp);
+  double q[3];
+  r.move(y + IQ, dt / 6.0, q);
+  r.step(y + IA, isS, dt, zp);
 #pragma unroll
-  for (int o = 0; o < 9; ++o) {
-    z0r[o] = y[IZQR + o] - y[IZPI + o];
-    z0i[o] = y[IZQI + o] + y[IZPR + o];
-  }
-  pc_amplitude(z0r, z0i, kr, ki, isS, y + IA, dt);
-  const double h6 = dt / 6.0;
-#pragma unroll
-  for (int j = 0; j < 3; ++j) y[IQ + j] = rk4_const(y[IQ + j], kQ[j], h6);
-#pragma unroll
-  for (int o = 0; o < 9; ++o) {
-    y[IZQR + o] = rk4_const(y[IZQR + o], kr[o], h6);
-    y[IZQI + o] = rk4_const(y[IZQI + o], ki[o], h6);
-  }
+  for (int j = 0; j < 3; ++j) y[IQ + j] = q[j];
+  r.store(y);
 }
 
 }  // namespace rk
