@@ -54,7 +54,7 @@ HBM_PEAK = 8.0e12
 TRAFFIC = {
     "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "a1599d8314b21260",
                    "beams": 33044152, "bytes_per_launch": 2.1306e10},
-    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "50803b4afaf933bc",
+    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "da85add85787c6fb",
                   "beams": 33044152, "bytes_per_launch": 9.0501e9},
 }
 

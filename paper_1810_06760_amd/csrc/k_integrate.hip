@@ -361,6 +361,7 @@ __device__ __forceinline__ void layered_body(const DevMedium &med, const Integra
   __shared__ double2 zp_lds[GRAD ? 1 : 9 * 64];
   const ZpLds zp{zp_lds};
   ConstRates rates;
+  Layer lay;
   int layer = 0, sp = 0;
   bool isS = false, live = alive, cross = false, s_finite = false, zp_finite = true;
   double sg = 0.0, wabs = 0.0, Wr = 0.0, Wi = 0.0;
@@ -389,9 +390,10 @@ __device__ __forceinline__ void layered_body(const DevMedium &med, const Integra
       flags = FGA_FLAG_QUARANTINED;
       quar = 1;
     }
+    if (LAYERS) lay = layer_of(med, sp, layer);
     if constexpr (!GRAD) {
       zp_finite = zp.put(y);
-      rates.init(LAYERS ? (isS ? med.csl[layer] : med.cpl[layer]) : (isS ? med.cs : med.cp), sg, y, zp);
+      rates.init(LAYERS ? lay.c0 : (isS ? med.cs : med.cp), sg, y, zp);
     }
   }
   for (int s = 0; s < a.nsteps; ++s) {
@@ -403,7 +405,7 @@ __device__ __forceinline__ void layered_body(const DevMedium &med, const Integra
           for (int t = 0; t < 4; ++t) A0[t] = y[IA + t];
           if (isS) frame_to_vector(y, e);
         }
-        cross = rk4_step<MK_LAYERED, SV, true, true>(med, sp, layer, sg, isS, e, y, dt);
+        cross = rk4_step<MK_LAYERED, SV, true, true>(med, sp, layer, sg, isS, e, y, dt, nullptr, nullptr, &lay);
         if (SV && cross) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) y[IA + t] = A0[t];
@@ -415,8 +417,7 @@ __device__ __forceinline__ void layered_body(const DevMedium &med, const Integra
       } else {
         double q[3];
         rates.move(y + IQ, dt / 6.0, q);
-        int iface, nl;
-        if (LAYERS) cross = layer_exit(med, layer, q, iface, nl);
+        if (LAYERS) cross = leaves_layer(lay, q);
         if (!cross) {
 #pragma unroll
           for (int d = 0; d < 3; ++d) y[IQ + d] = q[d];

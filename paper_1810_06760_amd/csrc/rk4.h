@@ -40,7 +40,8 @@ template <int MK, int SV = 0, bool LAST = false, bool EXIT = false>
 __device__ __forceinline__ bool stage(const DevMedium &med, int sp, int layer, double sg, bool isS,
                                       const double e[3], double *__restrict__ y, double *__restrict__ yt,
                                       double *__restrict__ acc, int st, double dt,
-                                      const MedBlock *blk = nullptr, CellCache *cells = nullptr)
+                                      const MedBlock *blk = nullptr, CellCache *cells = nullptr,
+                                      const Layer *lay = nullptr)
 {
   const double h2 = 0.5 * dt, h6 = dt / 6.0;
   const double wacc = (st == 0 || st == 3) ? 1.0 : 2.0;
@@ -63,6 +64,8 @@ __device__ __forceinline__ bool stage(const DevMedium &med, int sp, int layer, d
     for (int k = 0; k < 3; ++k) g[k] = scale * v[1 + k];
 #pragma unroll
     for (int k = 0; k < 6; ++k) H6[k] = scale * v[4 + k];
+  } else if (MK == MK_LAYERED && lay) {
+    layer_eval(*lay, yt + IQ, c, g, H6);
   } else {
     medium_eval<MK>(med, sp, layer, yt + IQ, c, g, H6, blk);
   }
@@ -80,8 +83,7 @@ __device__ __forceinline__ bool stage(const DevMedium &med, int sp, int layer, d
     double q[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) q[j] = y[IQ + j] + h6 * (acc[IQ + j] + sc * ph[j]);
-    int iface, nl;
-    if (layer_exit(med, layer, q, iface, nl)) return true;
+    if (leaves_layer(*lay, q)) return true;
 #pragma unroll
     for (int j = 0; j < 3; ++j) y[IQ + j] = q[j];
   } else {
@@ -243,12 +245,12 @@ __device__ __forceinline__ void reframe_s(double *y, double e[3]) { reframe_s(y 
 // 12.0 ms as a loop of four, 11.5 peeled).  All four in a row are 65 KB of code,
 // as much as the instruction cache holds for two compute units: 16.9 ms.  Callers
 // with many steps in a row of code (the interface step) keep the loop.
-// EXIT (layered media, with PEEL): a step that would leave the beam's layer is
+// EXIT (layered media, with PEEL and the beam's layer): a step that would leave the beam's layer is
 // not taken: y stays as it was and the result is true.
 template <int MK, int SV = 0, bool PEEL = false, bool EXIT = false>
 __device__ __forceinline__ bool rk4_step(const DevMedium &med, int sp, int layer, double sg, bool isS,
                                          const double e[3], double *y, double dt, const MedBlock *blk = nullptr,
-                                         CellCache *cells = nullptr)
+                                         CellCache *cells = nullptr, const Layer *lay = nullptr)
 {
   constexpr int N = nstate<SV>();
   double acc[N], yt[N];
@@ -257,11 +259,11 @@ __device__ __forceinline__ bool rk4_step(const DevMedium &med, int sp, int layer
 #pragma nounroll
   for (int st = 0; st < (PEEL ? 3 : 4); ++st) {
     if (MK == MK_GRID && cells) cells->wait();
-    stage<MK, SV>(med, sp, layer, sg, isS, e, y, yt, acc, st, dt, blk, cells);
+    stage<MK, SV>(med, sp, layer, sg, isS, e, y, yt, acc, st, dt, blk, cells, lay);
   }
   if constexpr (PEEL) {
     if (MK == MK_GRID && cells) cells->wait();
-    if (stage<MK, SV, true, EXIT>(med, sp, layer, sg, isS, e, y, yt, acc, 3, dt, blk, cells)) return true;
+    if (stage<MK, SV, true, EXIT>(med, sp, layer, sg, isS, e, y, yt, acc, 3, dt, blk, cells, lay)) return true;
   } else {
     const double h6 = dt / 6.0;
 #pragma unroll
