@@ -845,7 +845,8 @@ namespace {
 // array's name as a device address: the address of each device's copy comes
 // from hipGetSymbolAddress, taken once per device with that device current.
 constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
-__attribute__((used)) static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+// (behind it the counters of the one-launch sum, zero between calls)
+__attribute__((used)) static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + 4 * MAX_SMALL];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -919,6 +920,30 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
   hipStream_t st = (hipStream_t)stream;
   Arena ar(base, kNoAllocScratchBytes);
   unsigned long long *ctr = ar.take<unsigned long long>(1);
+  const int small = points_small_blocks(nb, n);
+  double *rows = small ? ar.take<double>((size_t)small * n * 6) : nullptr;
+  if (rows) {
+    if (evals) {
+      hipLaunchKernelGGL(k_zero_u64, 1, 64, 0, st, ctr, 1);
+      FGA_HIP(hipGetLastError());
+    }
+    PointsArgs pa{};
+    pa.xyz = xyz;
+    pa.n = n;
+    pa.eps = eps;
+    pa.tau = tau;
+    pa.partial = rows;
+    pa.evals = evals ? ctr : nullptr;
+    pa.precision = precision;
+    FGA_HIP(launch_points_small(beams, pa, out, reinterpret_cast<unsigned *>(base + kNoAllocScratchBytes), st));
+    if (evals) {
+      unsigned long long h = 0;
+      FGA_HIP(hipMemcpyAsync(&h, ctr, sizeof h, hipMemcpyDeviceToHost, st));
+      FGA_HIP(hipStreamSynchronize(st));
+      *evals = (int64_t)h;
+    }
+    return FGA_OK;
+  }
   double *emit = ar.take<double>((size_t)12 * batch);
   const int bpb = points_beams_per_block(batch, n, 1, 64);
   double *partial = ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);

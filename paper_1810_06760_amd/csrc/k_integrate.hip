@@ -16,76 +16,25 @@
 // 517 us (182 without gathers).  With each lane's cell kept in LDS and the next
 // one fetched a stage ahead (CellCache) they take 11.5 ms and 235 us.
 #include "fastmath.h"
-#include "rk4.h"
+#include "record.h"
 
 namespace fga {
 namespace {
 
 using namespace rk;
 
-// Emission record of the current state: Q (3), P 128/(pi eps) (3), B = W A (3 complex),
-// W = w e^{iS/eps} (S does not change, so W is formed once per launch).
-// SV = 1: an S beam's state holds A itself (frame-free form).
-// Returns whether the record is a live one.
+// Writes the record of the current state (beam_record) as beam j's; one with a
+// non-finite entry is written as a dead one.  Returns whether it is a live one.
 template <int SV = 0>
 __device__ __forceinline__ bool emit_record(double *__restrict__ out, int64_t nb, int64_t j,
                                             const double *y, const double e[3], double Wr, double Wi,
                                             bool isS, double ieps)
 {
-  double A[6];
-  if (SV && isS) {
-    A[0] = y[IA];
-    A[1] = y[IA + 1];
-    A[2] = y[IA + 2];
-    A[3] = y[IA + 3];
-    A[4] = y[IAZ];
-    A[5] = y[IAZ + 1];
-  } else if (!isS) {
-    const double inp = fast_rsqrt(y[IP] * y[IP] + y[IP + 1] * y[IP + 1] + y[IP + 2] * y[IP + 2]);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const double nh = y[IP + c] * inp;
-      A[2 * c] = y[IA] * nh;
-      A[2 * c + 1] = y[IA + 1] * nh;
-    }
-  } else {
-    double nsh[3], nsv[3];
-    s_frame(y + IP, e, nsh, nsv);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      A[2 * c] = y[IA] * nsv[c] + y[IA + 2] * nsh[c];
-      A[2 * c + 1] = y[IA + 1] * nsv[c] + y[IA + 3] * nsh[c];
-    }
-  }
-  const double pscale = ieps * INV_PI_128;
   double r[12];
-#pragma unroll
-  for (int f = 0; f < 3; ++f) {
-    r[f] = y[IQ + f];
-    r[3 + f] = y[IP + f] * pscale;  // the phase (P/eps).(x - Q) in units of pi/128
-  }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    r[6 + 2 * c] = Wr * A[2 * c] - Wi * A[2 * c + 1];
-    r[7 + 2 * c] = Wr * A[2 * c + 1] + Wi * A[2 * c];
-  }
-  // a record with a non-finite entry is written as a dead one: it never
-  // enters a window, so no sum takes a NaN from it
-  bool finite = true;
-#pragma unroll
-  for (int f = 0; f < 12; ++f) finite = finite && isfinite(r[f]);
+  const bool finite = beam_record<SV>(y, e, Wr, Wi, isS, ieps, r);
 #pragma unroll
   for (int f = 0; f < 12; ++f) out[f * nb + j] = finite ? r[f] : (f < 3 ? -1.0e300 : 0.0);
   return finite;
-}
-
-// W = w e^{iS/eps}
-__device__ __forceinline__ void emit_weight(double wr, double wi, double S, double ieps, double &Wr, double &Wi)
-{
-  double sn, cs;
-  sincos(S * ieps, &sn, &cs);
-  Wr = wr * cs - wi * sn;
-  Wi = wr * sn + wi * cs;
 }
 
 __device__ __forceinline__ void emit_dead(double *__restrict__ out, int64_t nb, int64_t j)

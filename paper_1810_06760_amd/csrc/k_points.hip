@@ -16,6 +16,7 @@
 
 #include "device_common.h"
 #include "fastmath.h"
+#include "record.h"
 
 namespace fga {
 namespace {
@@ -359,7 +360,163 @@ __global__ __launch_bounds__(64 * RG) void k_reduce_points(const double *__restr
   }
 }
 
+// A small sum in one launch, out[r][c] over all beams.  Each wavefront forms the
+// records of one 64-beam tile and sums them at four points; the wavefronts of a
+// workgroup take neighbouring tiles, whose sums are added in LDS; the last
+// workgroup of a point group to finish (arrived counts them, and is left at 0)
+// adds the groups' sums in order, so the result does not depend on who is last.
+// The sums pass the L2s of the eight XCDs by device-scope stores and loads: a
+// device-scope fence in each workgroup writes a whole L2 back (204 workgroups:
+// 21 us).
+// Such a sum is bound by launches and latencies: 3000 beams at 65 points take
+// 8.2 us a call, 13.8 as records, sums and their reduction in three launches.
+constexpr int SMALL_TILES = 4, SMALL_POINTS = 4;
+template <int MODE>
+__global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double *__restrict__ F,
+                                                                   const int32_t *__restrict__ I, int64_t cap,
+                                                                   int64_t nb, double ieps, PointsArgs a, int groups,
+                                                                   int nblk, double *__restrict__ out,
+                                                                   unsigned *__restrict__ arrived)
+{
+  using Acc = typename std::conditional<MODE == SUM_MIXED32, float, double>::type;
+  constexpr bool MIXED = MODE == SUM_MIXED || MODE == SUM_MIXED32;
+  constexpr int OUT = 6 * SMALL_POINTS, SEG = 64 * SMALL_TILES / OUT;
+  __shared__ ScaledTables tab;
+  __shared__ double part[SEG > SMALL_TILES ? SEG : SMALL_TILES][OUT];
+  __shared__ bool last;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pg = blockIdx.x % groups, blk = blockIdx.x / groups;
+  const int64_t i = ((int64_t)blk * SMALL_TILES + w) * 64 + lane;
+  const int64_t ii = i < nb ? i : nb - 1;
+  const bool alive = i < nb && (I[FGA_FLAGS * cap + ii] & FGA_FLAG_ALIVE);
+  const bool isS = I[FGA_BRANCH * cap + ii] != 0;
+  double y[rk::NS];
+#pragma unroll
+  for (int f = 0; f < rk::NS; ++f)
+    if (f < rk::IZQR || f >= rk::IA) y[f] = F[f * cap + ii];
+  const double e[3] = {F[(FGA_E + 0) * cap + ii], F[(FGA_E + 1) * cap + ii], F[(FGA_E + 2) * cap + ii]};
+  const double wr = F[FGA_W_RE * cap + ii], wi = F[FGA_W_IM * cap + ii];
+  const int64_t r0 = (int64_t)pg * SMALL_POINTS;
+  double xr[SMALL_POINTS][3];
+#pragma unroll
+  for (int k = 0; k < SMALL_POINTS; ++k)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) xr[k][d] = r0 + k < a.n ? a.xyz[3 * (r0 + k) + d] : 1.0e30;
+  if constexpr (!MIXED) fill_tables(tab);
+  double Wr, Wi, r[12];
+  emit_weight(wr, wi, y[rk::IS], ieps, Wr, Wi);
+  const bool mine = beam_record(y, e, Wr, Wi, isS, ieps, r) && alive;
+  double q[3], pe[3];
+  Acc B[6];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    q[d] = mine ? r[d] : 0.0;
+    pe[d] = mine ? r[3 + d] : 0.0;
+    if (MIXED) pe[d] *= 1.0 / 256.0;  // exact: from units of pi/128 to revolutions
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) B[c] = (Acc)(mine ? r[6 + c] : 0.0);
+  if constexpr (!MIXED) __syncthreads();
+  const double R = sqrt(2.0 * a.tau * a.eps);
+  const double hieps = 0.5 / a.eps;
+  const double nc = -hieps * (MIXED ? LOG2E : INV_LN2_256);
+  const double tmax = MAX_EXPONENT / hieps;
+  const ScaledCoeffs K;
+  unsigned long long cnt = 0;
+  double all[OUT], tot[6];
+#pragma unroll
+  for (int k = 0; k < SMALL_POINTS; ++k) {
+    Acc u[6];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) u[c] = (Acc)0;
+    double dd[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) dd[d] = xr[k][d] - q[d];
+    const bool in = mine & (fabs(dd[0]) <= R) & (fabs(dd[1]) <= R) & (fabs(dd[2]) <= R);
+    const uint64_t bal = __ballot(in);
+    if (bal) {
+      cnt += __popcll(bal);
+      Acc er, ei;
+      point_term<MODE>(tab, K, dd, pe, nc, tmax, in, er, ei);
+      accumulate_term(u, B, er, ei);
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) all[k * 6 + c] = (double)u[c];
+  }
+  reduce24(all, tot);
+  const int g = lane >> 4, c = lane & 15;
+  double v = tot[0];
+#pragma unroll
+  for (int k = 1; k < 6; ++k) v = c == k ? tot[k] : v;
+  if (c < 6) part[w][g * 6 + c] = v;
+  if (a.evals && lane == 0 && cnt) atomicAdd(a.evals, cnt);
+  __syncthreads();
+  const int t = threadIdx.x;
+  const bool valid = t < OUT && r0 + t / 6 < a.n;
+  double *P = a.partial + r0 * 6 + t;
+  if (valid) {
+    double s = part[0][t];
+#pragma unroll
+    for (int k = 1; k < SMALL_TILES; ++k) s += part[k][t];
+    if (nblk > 1) __hip_atomic_store(P + (int64_t)blk * a.n * 6, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else out[r0 * 6 + t] = s;
+  }
+  if (nblk == 1) return;
+  // wavefront 0 wrote the row, past the L2s: it waits for those stores and counts
+  if (w == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    if (t == 0)
+      last = __hip_atomic_fetch_add(arrived + pg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  const int seg = t / OUT, o = t % OUT;
+  if (seg < SEG) {
+    double s = 0.0;
+    if (r0 + o / 6 < a.n) {
+      double *Q = a.partial + r0 * 6 + o;
+#pragma unroll 8
+      for (int b = seg; b < nblk; b += SEG)
+        s += __hip_atomic_load(Q + (int64_t)b * a.n * 6, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    part[seg][o] = s;
+  }
+  __syncthreads();
+  if (valid) {
+    double s = part[0][t];
+#pragma unroll
+    for (int k = 1; k < SEG; ++k) s += part[k][t];
+    out[r0 * 6 + t] = s;
+  }
+  if (t == 0) arrived[pg] = 0;
+}
+
 }  // namespace
+
+int points_small_blocks(int64_t nb, int64_t n)
+{
+  const int64_t blocks = (nb + 64 * SMALL_TILES - 1) / (64 * SMALL_TILES);
+  const int64_t groups = (n + SMALL_POINTS - 1) / SMALL_POINTS;
+  return nb > 0 && n > 0 && groups <= MAX_SMALL && blocks <= MAX_SMALL && blocks * groups <= MAX_SMALL ? (int)blocks : 0;
+}
+
+hipError_t launch_points_small(const fga_beams *b, const PointsArgs &a, double *out, unsigned *arrived, hipStream_t st)
+{
+  const int nblk = points_small_blocks(b->count, a.n);
+  if (nblk == 0) return hipErrorInvalidValue;
+  const int groups = (int)((a.n + SMALL_POINTS - 1) / SMALL_POINTS);
+  ProfScope prof(FGA_K_SUM_POINTS, st);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, (unsigned)(nblk * groups), 64 * SMALL_TILES, 0, st, b->f64, b->i32, b->capacity, b->count,
+                       1.0 / a.eps, a, groups, nblk, out, arrived);
+  };
+  if (a.precision == FGA_FP32) go(k_points_small<SUM_MIXED>);
+  else if (a.precision == FGA_FP32_ACC32) go(k_points_small<SUM_MIXED32>);
+  else if (3.0 * a.tau > MAX_EXPONENT - 1.0) go(k_points_small<SUM_FP64_WIDE>);
+  else go(k_points_small<SUM_FP64>);
+  return hipGetLastError();
+}
 
 int points_beams_per_block(int64_t nb, int64_t n, int m, int least)
 {
