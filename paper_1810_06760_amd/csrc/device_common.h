@@ -157,6 +157,9 @@ struct CellCache {
     int i0[3];
     grid_cell(m, x, i0, t);
     if (i0[0] == cell[0] && i0[1] == cell[1] && i0[2] == cell[2]) return;
+    // pieces arrive in LDS on their own time, not in the order of the wavefront's LDS
+    // instructions: what is still to be read of the column is waited for first
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const char *tab = reinterpret_cast<const char *>(m.table + (sp && m.two_fields ? m.field_stride : 0));
     int i1[3];
 #pragma unroll
