@@ -491,7 +491,7 @@ size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_
   if (rec && rec->stride < 1) return 0;
   const EvolvePlan p = evolve_plan(beams, nsteps, opts, rec);
   Arena ar(nullptr, 0);
-  evolve_layout(p, rec, beams->capacity, ar);
+  const EvolveBufs wb = evolve_layout(p, rec, beams->capacity, ar);
   // the re-sort and the compaction work behind the evolution's buffers (the
   // counters among them stay intact), sized for a full beam set: interface
   // splitting can grow it up to capacity
@@ -502,7 +502,7 @@ size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_
   if (p.resort > 0) {
     Arena sa(nullptr, 0);
     size_t ns = 0;
-    sort_beams_spatial(&bb, sa, nullptr, 0, nullptr, true, &ns);
+    sort_beams_spatial(&bb, sa, nullptr, wb.idle_bytes, nullptr, true, &ns);
     need = need > base + ns ? need : base + ns;
   }
   if (opts && opts->compact) {

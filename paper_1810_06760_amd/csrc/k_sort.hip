@@ -210,8 +210,13 @@ struct SortBufs {
   int64_t *alive;
   void *sort_tmp;
   size_t sort_bytes;
-  size_t free_bytes;  // from k1 on: free once the keys are sorted and the live beams counted
+  size_t free_bytes;  // from k1 to the workspace's end: free once the keys are sorted and the live beams counted
 };
+
+// Beams of a set for whose sort a workspace is sized with a slot for every plane
+// (at most 113 MB) unless the caller has memory to lend, as its launches cost more than its bytes: 98 k beams without
+// receivers' buffers to borrow took 30 launches of 5 us for the planes, now two.
+constexpr int64_t SMALL_SET = 1 << 18;
 
 SortBufs sort_layout(int64_t n, Arena &ar)
 {
@@ -231,7 +236,7 @@ SortBufs sort_layout(int64_t n, Arena &ar)
   (void)hipcub::DeviceRadixSort::SortPairs(nullptr, b.sort_bytes, b.k1, b.k2, b.v1, b.v2, (int)(n > 0 ? n : 1), 0,
                                            32);
   b.sort_tmp = ar.take<char>(b.sort_bytes + 1);
-  b.free_bytes = ar.used - keep;
+  b.free_bytes = ar.size > keep ? ar.size - keep : 0;  // and the rest of the workspace
   return b;
 }
 
@@ -243,6 +248,7 @@ fga_status sort_beams_spatial(fga_beams *b, Arena &ar, void *scratch, size_t scr
   const int64_t n = b->count;
   SortBufs s = sort_layout(n, ar);
   if (size_only) {
+    if (scratch_bytes < (size_t)NPLANE * 8 * n && n <= SMALL_SET) ar.take<double>((size_t)NPLANE * ((n + 31) & ~(int64_t)31));
     *need = ar.used;
     return FGA_OK;
   }
