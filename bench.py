@@ -52,10 +52,10 @@ HBM_PEAK = 8.0e12
 # scaled by a 1 GiB copy calibration; valid only while the kernel's source is
 # unchanged (sha256 prefix) and the beam set is the one profiled, else null
 TRAFFIC = {
-    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "49552a4d0a0adf6a",
-                   "beams": 33044152, "bytes_per_launch": 2.1177e10},
+    "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "3628f6082e5958f1",
+                   "beams": 33044152, "bytes_per_launch": 2.1852e10},
     "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "9a935f7a3af2a5b0",
-                  "beams": 33044152, "bytes_per_launch": 9.0510e9},
+                  "beams": 33044152, "bytes_per_launch": 9.0507e9},
 }
 
 

@@ -436,7 +436,25 @@ EvolvePlan evolve_plan(const fga_beams *b, int nsteps, const fga_evolve_opts *o,
   return p;
 }
 
+int64_t sum_evals(const unsigned long long *slots)
+{
+  unsigned long long n = 0;
+  for (int k = 0; k < EVAL_SLOTS; ++k) n += slots[k * EVAL_STRIDE];
+  return (int64_t)n;
+}
+
+// *evals = the sum of the device's counters; synchronises st
+fga_status read_evals(const unsigned long long *slots, hipStream_t st, int64_t *evals)
+{
+  unsigned long long h[EVAL_WORDS];
+  FGA_HIP(hipMemcpyAsync(h, slots, sizeof h, hipMemcpyDeviceToHost, st));
+  FGA_HIP(hipStreamSynchronize(st));
+  *evals = sum_evals(h);
+  return FGA_OK;
+}
+
 struct EvolveBufs {
+  // [0] beam-steps, [1] culled, [2] quarantined, [4..6] interface counters, from [8] on the term counters
   unsigned long long *ctr = nullptr;
   double *emit = nullptr, *partial = nullptr, *xs = nullptr, *box = nullptr, *xc = nullptr;
   int32_t *perm = nullptr;
@@ -454,7 +472,7 @@ struct EvolveBufs {
 static EvolveBufs evolve_layout(const EvolvePlan &p, const fga_receivers *r, int64_t cap, Arena &ar)
 {
   EvolveBufs b;
-  b.ctr = ar.take<unsigned long long>(8);
+  b.ctr = ar.take<unsigned long long>(8 + EVAL_WORDS);
   const int64_t nblk_all = (cap + 255) / 256 + 1;
   b.blk_extra = ar.take<int64_t>(nblk_all);
   b.blk_off = ar.take<int64_t>(nblk_all);
@@ -553,7 +571,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
     return fail(FGA_ENOMEM, "evolve workspace too small (%zu bytes given, %zu needed)", workspace_bytes, ar.used);
   const size_t sort_base = Arena::need(ar.used);  // re-sort and compaction work here, behind the counters
   const size_t sub_bytes = workspace_bytes > sort_base ? workspace_bytes - sort_base : 0;
-  FGA_HIP(hipMemsetAsync(ctr, 0, 8 * sizeof(unsigned long long), st));
+  FGA_HIP(hipMemsetAsync(ctr, 0, (8 + EVAL_WORDS) * sizeof(unsigned long long), st));
   if (rec && rec->n > 0) {
     const double *xyz = rec->xyz;
     if (rec->coords == FGA_COORDS_SPHERICAL) {
@@ -668,7 +686,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
           pa.tau = rec->tau;
           pa.partial = partial;
           pa.beams_per_block = p.bpb;
-          pa.evals = ctr + 3;
+          pa.evals = ctr + 8;
           pa.tile_box = wb.box;
           pa.ntiles = (pa.nb + 63) / 64;
           pa.precision = rec->precision;
@@ -724,7 +742,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
         pa.tau = rec->tau;
         pa.partial = partial;
         pa.beams_per_block = p.bpb;
-        pa.evals = ctr + 3;
+        pa.evals = ctr + 8;
         pa.tile_box = wb.box;
         pa.ntiles = (pa.nb + 63) / 64;
         pa.precision = rec->precision;
@@ -743,14 +761,14 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
     if ((s = compact_beams(beams, a2, st, false, &need)) != FGA_OK) return s;
   }
   if (stats || (cutoff > 0 && nsteps > 0)) {
-    unsigned long long h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    unsigned long long h[8 + EVAL_WORDS];
     FGA_HIP(hipMemcpyAsync(h, ctr, sizeof h, hipMemcpyDeviceToHost, st));
     FGA_HIP(hipStreamSynchronize(st));
     if (stats) {
       stats->beam_steps = (int64_t)h[0];
       stats->culled = (int64_t)h[1];
       stats->quarantined = (int64_t)h[2];
-      stats->evals = (int64_t)h[3];
+      stats->evals = sum_evals(h + 8);
       stats->crossings = (int64_t)h[4];
       stats->spawned = (int64_t)h[5];
       stats->capped = (int64_t)h[6];
@@ -766,7 +784,7 @@ size_t fga_reconstruct_points_workspace_bytes(const fga_beams *beams, int64_t n)
   if (check_beams(beams) != FGA_OK || n < 0) return 0;
   const int64_t batch = beams->count < ((int64_t)1 << 22) ? (beams->count > 0 ? beams->count : 1) : ((int64_t)1 << 22);
   Arena ar(nullptr, 0);
-  ar.take<unsigned long long>(1);
+  ar.take<unsigned long long>(EVAL_WORDS);
   ar.take<double>((size_t)12 * batch);
   const int bpb = points_beams_per_block(batch, n, 1, 64);
   ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
@@ -790,7 +808,7 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
   const int64_t nb = beams->count;
   const int64_t batch = nb < ((int64_t)1 << 22) ? (nb > 0 ? nb : 1) : ((int64_t)1 << 22);
   Arena ar(workspace, workspace_bytes);
-  unsigned long long *ctr = ar.take<unsigned long long>(1);
+  unsigned long long *ctr = ar.take<unsigned long long>(EVAL_WORDS);
   double *emit = ar.take<double>((size_t)12 * batch);
   const int bpb = points_beams_per_block(batch, n, 1, 64);
   double *partial = ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
@@ -800,7 +818,7 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
   if (!ctr || !emit || !partial || !box || !xs || !perm)
     return fail(FGA_ENOMEM, "reconstruct workspace too small (%zu bytes given, %zu needed)", workspace_bytes, ar.used);
   if (n > 0x7fffffff) return fail(FGA_EUNSUPPORTED, "more than 2^31 points");
-  if (evals) FGA_HIP(hipMemsetAsync(ctr, 0, sizeof(unsigned long long), st));
+  if (evals) FGA_HIP(hipMemsetAsync(ctr, 0, EVAL_WORDS * sizeof(unsigned long long), st));
   if (n > 0 && (s = sort_points(xyz, n, xs, perm, st)) != FGA_OK) return s;
   if (nb == 0) FGA_HIP(launch_reduce_points(partial, 0, 1, n, nullptr, out, 1, 0, 0, st));
   for (int64_t b0 = 0; b0 < nb; b0 += batch) {
@@ -825,13 +843,7 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
     FGA_HIP(launch_sum_points(pa, &nblk, st));
     FGA_HIP(launch_reduce_points(partial, nblk, 1, n, perm, out, 1, 0, b0 > 0 ? 1 : 0, st));
   }
-  if (evals) {
-    unsigned long long h = 0;
-    FGA_HIP(hipMemcpyAsync(&h, ctr, sizeof h, hipMemcpyDeviceToHost, st));
-    FGA_HIP(hipStreamSynchronize(st));
-    *evals = (int64_t)h;
-  }
-  return FGA_OK;
+  return evals ? read_evals(ctr, st, evals) : FGA_OK;
 }
 
 // ------------------------------------------ points without allocation --
@@ -845,8 +857,8 @@ namespace {
 // array's name as a device address: the address of each device's copy comes
 // from hipGetSymbolAddress, taken once per device with that device current.
 constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
-// (behind it the counters of the one-launch sum, zero between calls)
-__attribute__((used)) static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + 4 * MAX_SMALL];
+// (behind it the term counters, and those of the one-launch sum, which are zero between calls)
+__attribute__((used)) static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + 8 * EVAL_WORDS + 4 * MAX_SMALL];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -918,41 +930,32 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
   char *base = nullptr;
   if ((s = scratch_of_current_device(&base)) != FGA_OK) return s;
   hipStream_t st = (hipStream_t)stream;
+  unsigned long long *slots = reinterpret_cast<unsigned long long *>(base + kNoAllocScratchBytes);
+  if (evals) {
+    hipLaunchKernelGGL(k_zero_u64, 1, EVAL_WORDS, 0, st, slots, EVAL_WORDS);
+    FGA_HIP(hipGetLastError());
+  }
   Arena ar(base, kNoAllocScratchBytes);
-  unsigned long long *ctr = ar.take<unsigned long long>(1);
+  ar.take<unsigned long long>(1);
   const int small = points_small_blocks(nb, n);
   double *rows = small ? ar.take<double>((size_t)small * n * 6) : nullptr;
   if (rows) {
-    if (evals) {
-      hipLaunchKernelGGL(k_zero_u64, 1, 64, 0, st, ctr, 1);
-      FGA_HIP(hipGetLastError());
-    }
     PointsArgs pa{};
     pa.xyz = xyz;
     pa.n = n;
     pa.eps = eps;
     pa.tau = tau;
     pa.partial = rows;
-    pa.evals = evals ? ctr : nullptr;
+    pa.evals = evals ? slots : nullptr;
     pa.precision = precision;
-    FGA_HIP(launch_points_small(beams, pa, out, reinterpret_cast<unsigned *>(base + kNoAllocScratchBytes), st));
-    if (evals) {
-      unsigned long long h = 0;
-      FGA_HIP(hipMemcpyAsync(&h, ctr, sizeof h, hipMemcpyDeviceToHost, st));
-      FGA_HIP(hipStreamSynchronize(st));
-      *evals = (int64_t)h;
-    }
-    return FGA_OK;
+    FGA_HIP(launch_points_small(beams, pa, out, reinterpret_cast<unsigned *>(slots + EVAL_WORDS), st));
+    return evals ? read_evals(slots, st, evals) : FGA_OK;
   }
   double *emit = ar.take<double>((size_t)12 * batch);
   const int bpb = points_beams_per_block(batch, n, 1, 64);
   double *partial = ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
   double *box = ar.take<double>((size_t)((batch + 63) / 64) * 6);
-  if (!ctr || !emit || !partial || !box) return fail(FGA_ENOMEM, "scratch layout does not fit");
-  if (evals) {
-    hipLaunchKernelGGL(k_zero_u64, 1, 64, 0, st, ctr, 1);
-    FGA_HIP(hipGetLastError());
-  }
+  if (!emit || !partial || !box) return fail(FGA_ENOMEM, "scratch layout does not fit");
   if (nb == 0) FGA_HIP(launch_reduce_points(partial, 0, 1, n, nullptr, out, 1, 0, 0, st));
   for (int64_t b0 = 0; b0 < nb; b0 += batch) {
     const int64_t b1 = b0 + batch < nb ? b0 + batch : nb;
@@ -967,7 +970,7 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
     pa.tau = tau;
     pa.partial = partial;
     pa.beams_per_block = bpb;
-    pa.evals = evals ? ctr : nullptr;
+    pa.evals = evals ? slots : nullptr;
     pa.tile_box = box;
     pa.ntiles = (pa.nb + 63) / 64;
     pa.boxes_ready = 1;
@@ -976,13 +979,7 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
     FGA_HIP(launch_sum_points(pa, &nblk, st));
     FGA_HIP(launch_reduce_points(partial, nblk, 1, n, nullptr, out, 1, 0, b0 > 0 ? 1 : 0, st));
   }
-  if (evals) {
-    unsigned long long h = 0;
-    FGA_HIP(hipMemcpyAsync(&h, ctr, sizeof h, hipMemcpyDeviceToHost, st));
-    FGA_HIP(hipStreamSynchronize(st));
-    *evals = (int64_t)h;
-  }
-  return FGA_OK;
+  return evals ? read_evals(slots, st, evals) : FGA_OK;
 }
 
 size_t fga_reconstruct_grid_workspace_bytes(const fga_beams *beams, const int n[3], double eps, double tau,

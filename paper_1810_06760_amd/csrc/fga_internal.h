@@ -122,6 +122,11 @@ enum { FLAG_BORN = 0x80, RESUME_SHIFT = 8, FLAG_MASK = 0x7f };
 constexpr int MAX_LAYERED_CHUNK = 65535;  // samples that one launch of the sums takes
 hipError_t launch_integrate(const DevMedium &m, const IntegrateArgs &a, hipStream_t st);
 
+// A sum's term counter: workgroups add to one of EVAL_SLOTS words, a cache line
+// apart, and the host adds them up.  One word takes an addition every 10 ns or so,
+// which a small sum with many workgroups waited for (2190 beams at 349 points,
+// FP32: 42 us with one word, 9.3 so).
+constexpr int EVAL_SLOTS = 64, EVAL_STRIDE = 8, EVAL_WORDS = EVAL_SLOTS * EVAL_STRIDE;
 struct PointsArgs {
   const double *emit;        // [m][12][ld] records
   int64_t nb;                // beams in the batch
@@ -132,7 +137,7 @@ struct PointsArgs {
   double eps, tau;
   double *partial;           // [nblk][m][n][6]
   int beams_per_block;
-  unsigned long long *evals;
+  unsigned long long *evals; // NULL, or EVAL_WORDS counters whose sum takes the in-window terms
   double *tile_box;          // scratch [m][ntiles][6], ntiles = ceil(nb / 64)
   int64_t ntiles;
   int boxes_ready;           // tile_box already holds the boxes (written with the records)

@@ -302,7 +302,7 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
     for (int i = 1; i < 6; ++i) v = c == i ? tot[i] : v;
     if (c < 6 && r0 + h + g < a.n) a.partial[((wk.blk * a.m + s) * a.n + r0 + h + g) * 6 + c] = v;
   }
-  if (a.evals && lane == 0 && cnt) atomicAdd(a.evals, (unsigned long long)cnt);
+  if (a.evals && lane == 0 && cnt) atomicAdd(a.evals + blockIdx.x % EVAL_SLOTS * EVAL_STRIDE, (unsigned long long)cnt);
 }
 
 // Per sample and 64-beam tile: bounding box of the live beams' centres Q
@@ -344,6 +344,7 @@ __global__ __launch_bounds__(64 * RG) void k_reduce_points(const double *__restr
   const int64_t row = (int64_t)m * n * 6;  // doubles per block
   double v = 0.0;
   if (id < total)
+#pragma unroll 8  // loads of eight rows in flight, added in order (1498 rows of 78 outputs: 15 us one by one)
     for (int b = w; b < nblk; b += RG) v += partial[(int64_t)b * row + id];
   part[w][lane] = v;
   __syncthreads();
@@ -449,7 +450,7 @@ __global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double 
 #pragma unroll
   for (int k = 1; k < 6; ++k) v = c == k ? tot[k] : v;
   if (c < 6) part[w][g * 6 + c] = v;
-  if (a.evals && lane == 0 && cnt) atomicAdd(a.evals, cnt);
+  if (a.evals && lane == 0 && cnt) atomicAdd(a.evals + blockIdx.x % EVAL_SLOTS * EVAL_STRIDE, cnt);
   __syncthreads();
   const int t = threadIdx.x;
   const bool valid = t < OUT && r0 + t / 6 < a.n;
