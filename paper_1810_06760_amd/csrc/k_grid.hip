@@ -40,11 +40,11 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int T = 16;       // tile edge (points)
 constexpr int NB = 16;      // beams per LDS batch
 constexpr int MAXR = 1024;  // max candidate runs per tile: (2 reach + 1)^2
-// Work items per launch beyond one per tile: eight per tile up to MAX_SEG, and at
-// least MIN_SEG, so that a grid of few tiles still fills the chip (512 workgroups
-// at two wavefronts per SIMD) with a round to spare; 32^3 points (8 tiles) and
-// 98 k beams took 3.30 ms in 72 items.
+// Work items per launch beyond one per tile that the workspace holds: eight per
+// tile up to MAX_SEG, and at least MIN_SEG, so that a grid of few tiles still fills
+// the chip; 32^3 points (8 tiles) and 98 k beams took 3.30 ms in 72 items.
 constexpr int MAX_SEG = 4096, MIN_SEG = 512, SEG_BEAMS = 64;  // SEG_BEAMS: shortest item
+constexpr int RESIDENT = 512;  // workgroups at once
 
 struct GridGeom {
   int n[3], nt[3], nc[3], reach[3];
@@ -732,6 +732,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   Pol::store(acc, partial + item * (3 * T * T * T * 2), ws, half);
 }
 
+// Candidates per work item.  A grid of many tiles takes eight items a tile, at
+// most MAX_SEG in all; one of few takes shorter ones, so that they still fill the
+// chip.  In FP64 workgroups share a compute unit's matrix cores and gain little
+// from company: MIN_SEG items, up to where eight a tile are more than one for each
+// compute unit anyway (18 tiles, 1 M beams: 58.5 -> 35.6 ms; 36 tiles, 883 k: 75.8
+// -> 58.5; 48 tiles, 468 k: 40.9 -> 46.6).  The mixed modes' items are sized to be
+// at once just as many as are resident (52 tiles, 911 k beams: 15.9 ms in 512
+// items, 17.5 in eight a tile, 21.3 in 564; 20 tiles: 18.3 and 32.6; 60 tiles: 6.1
+// and 5.9).
+int64_t item_length(const std::vector<int64_t> &count, int max_items, bool fp64)
+{
+  const int ntile = (int)count.size();
+  auto round_up = [](int64_t v) { return std::max<int64_t>((v + NB - 1) / NB * NB, SEG_BEAMS); };
+  int64_t total = 0;
+  for (int64_t c : count) total += c;
+  if (fp64 || ntile > 56) {
+    const int nseg = fp64 && ntile <= 36 ? max_items - ntile : std::min(MAX_SEG, 8 * ntile);
+    return round_up((total + nseg - 1) / nseg);
+  }
+  const int lim = std::min(RESIDENT, max_items);
+  int64_t seg = round_up((total + lim - 1) / lim);
+  for (;;) {  // ends: from the longest count on there is one item a tile, and ntile < lim
+    int64_t items = 0;
+    for (int64_t c : count) items += (c + seg - 1) / seg;
+    if (items <= lim) return seg;
+    seg = round_up(seg + seg / 32 + 1);
+  }
+}
+
 // out[c][z][y][x] = sum of the tile's partials (fixed item order), added to
 // the previous contents with `add`; points outside the grid of a ragged tile
 // are skipped.
@@ -850,11 +879,7 @@ fga_status grid_sum_impl(const fga_beams *b, double eps, double tau, const int n
   FGA_HIP(hipStreamSynchronize(st));
   if (evals_out) *evals_out = (int64_t)hev;
 
-  int64_t total = 0;
-  for (int t = 0; t < ntile; ++t) total += hc[t];
-  int64_t seg = (total + nseg - 1) / nseg;
-  if (seg < SEG_BEAMS) seg = SEG_BEAMS;
-  seg = (seg + NB - 1) / NB * NB;
+  const int64_t seg = item_length(hc, max_items, precision == FGA_FP64);
   std::vector<Item> hi;
   std::vector<int32_t> hf(ntile), hn(ntile);
   for (int t = 0; t < ntile; ++t) {
