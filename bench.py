@@ -54,7 +54,7 @@ HBM_PEAK = 8.0e12
 TRAFFIC = {
     "sum_points": {"source": "paper_1810_06760_amd/csrc/k_points.hip", "sha256": "3628f6082e5958f1",
                    "beams": 33044152, "bytes_per_launch": 2.1852e10},
-    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "9a935f7a3af2a5b0",
+    "integrate": {"source": "paper_1810_06760_amd/csrc/k_integrate.hip", "sha256": "16339db77d2c65ae",
                   "beams": 33044152, "bytes_per_launch": 9.0507e9},
 }
 

@@ -105,8 +105,9 @@ __device__ __forceinline__ double iface_level(const DevMedium &m, int iface)
 // (xx, yy, zz, xy, xz, yz).  Grid media interpolate the ten precomputed node
 // fields trilinearly (periodic); each node is one 128-byte record.
 // Cubic media: a block of MEDBLK3^3 spline coefficients per node field held in LDS
-// by a workgroup, the c_S field (two_fields) MEDBLK3^3 doubles after the c_P field.
-constexpr int MEDBLK3 = 16;
+// by a workgroup, the c_S field (two_fields) after the c_P field; rows and planes at
+// odd strides, so that neighbouring cells' reads meet on few banks.
+constexpr int MEDBLK3 = 16, MEDROW = 17, MEDPLANE = 277;
 struct MedBlock {
   const double *lds;  // NULL: no block
   int o[3];
@@ -233,25 +234,40 @@ __device__ __forceinline__ void bspline_weights(double t, double ih, double w[4]
 
 // Tensor-product sum of the 4x4x4 coefficients ld(a, b, c) (x, y, z offsets)
 // giving c, grad c and the Hessian (xx, yy, zz, xy, xz, yz) in v[10]: the x
-// sums first (value, first, second derivative per row), then y, then z.
+// sums first (value, first, second derivative per row), then y, then z.  Two
+// rows are read while the two before are summed (and kept there by the
+// scheduling barriers): left alone the compiler reads each pair of
+// coefficients where it is used, and one wavefront per SIMD waits for it
+// (532 k beams x 16 steps of a point source 2.60 ms, so 2.13).
 template <class Load>
 __device__ __forceinline__ void bspline_sum(const double w[3][4], const double d1[3][4], const double d2[3][4],
                                             Load ld, double v[10])
 {
 #pragma unroll
   for (int k = 0; k < 10; ++k) v[k] = 0.0;
+  double q[2][2][4];
+  auto rows = [&](int g, double (&to)[2][4]) {
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    double y00 = 0.0, y10 = 0.0, y01 = 0.0, y20 = 0.0, y11 = 0.0, y02 = 0.0;
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+      for (int a = 0; a < 4; ++a) to[h][a] = ld(a, 2 * (g & 1) + h, g >> 1);
+  };
+  rows(0, q[0]);
+  double y00 = 0.0, y10 = 0.0, y01 = 0.0, y20 = 0.0, y11 = 0.0, y02 = 0.0;
+#pragma unroll
+  for (int g = 0; g < 8; ++g) {
+    if (g < 7) rows(g + 1, q[(g + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if ((g & 1) == 0) y00 = y10 = y01 = y20 = y11 = y02 = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int b = 2 * (g & 1) + h;
       double x0 = 0.0, x1 = 0.0, x2 = 0.0;
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        const double q = ld(a, b, c);
-        x0 += w[0][a] * q;
-        x1 += d1[0][a] * q;
-        x2 += d2[0][a] * q;
+        x0 += w[0][a] * q[g & 1][h][a];
+        x1 += d1[0][a] * q[g & 1][h][a];
+        x2 += d2[0][a] * q[g & 1][h][a];
       }
       y00 += w[1][b] * x0;
       y10 += w[1][b] * x1;
@@ -260,16 +276,19 @@ __device__ __forceinline__ void bspline_sum(const double w[3][4], const double d
       y11 += d1[1][b] * x1;
       y02 += d2[1][b] * x0;
     }
-    v[0] += w[2][c] * y00;
-    v[1] += w[2][c] * y10;
-    v[2] += w[2][c] * y01;
-    v[3] += d1[2][c] * y00;
-    v[4] += w[2][c] * y20;
-    v[5] += w[2][c] * y02;
-    v[6] += d2[2][c] * y00;
-    v[7] += w[2][c] * y11;
-    v[8] += d1[2][c] * y10;
-    v[9] += d1[2][c] * y01;
+    if (g & 1) {
+      const int c = g >> 1;
+      v[0] += w[2][c] * y00;
+      v[1] += w[2][c] * y10;
+      v[2] += w[2][c] * y01;
+      v[3] += d1[2][c] * y00;
+      v[4] += w[2][c] * y20;
+      v[5] += w[2][c] * y02;
+      v[6] += d2[2][c] * y00;
+      v[7] += w[2][c] * y11;
+      v[8] += d1[2][c] * y10;
+      v[9] += d1[2][c] * y01;
+    }
   }
 }
 
@@ -401,9 +420,8 @@ __device__ __forceinline__ void medium_eval(const DevMedium &m, int sp, int laye
     }
     double v[10];
     if (__all(inblk)) {
-      const double *b0 = blk->lds + ((sp && m.two_fields) ? MEDBLK3 * MEDBLK3 * MEDBLK3 : 0) +
-                         (l[2] * MEDBLK3 + l[1]) * MEDBLK3 + l[0];
-      bspline_sum(w, d1, d2, [&](int ia, int ib, int ic) { return b0[(ic * MEDBLK3 + ib) * MEDBLK3 + ia]; }, v);
+      const double *b0 = blk->lds + ((sp && m.two_fields) ? MEDBLK3 * MEDPLANE : 0) + l[2] * MEDPLANE + l[1] * MEDROW + l[0];
+      bspline_sum(w, d1, d2, [&](int ia, int ib, int ic) { return b0[ic * MEDPLANE + ib * MEDROW + ia]; }, v);
     } else {
       int ix[4], iy[4], iz[4];
 #pragma unroll

@@ -114,7 +114,7 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
     // there are two) is staged in LDS once and the 4x4x4 stencils read it (stencils
     // outside it fall back to global memory).
     constexpr int B3 = MEDBLK3 * MEDBLK3 * MEDBLK3;
-    __shared__ double lds_cf[2 * B3];
+    __shared__ double lds_cf[2 * MEDBLK3 * MEDPLANE];
     __shared__ int bb[6];
     if (threadIdx.x < 3) {
       bb[threadIdx.x] = 0x7fffffff;
@@ -143,7 +143,7 @@ __device__ __forceinline__ void integrate_body(const DevMedium &med, const Integ
         const int f = idx / B3, r = idx - f * B3;
         const int lx = r % MEDBLK3, ly = (r / MEDBLK3) % MEDBLK3, lz = r / (MEDBLK3 * MEDBLK3);
         const int nx = (o[0] + lx) % med.n[0], ny = (o[1] + ly) % med.n[1], nz = (o[2] + lz) % med.n[2];
-        lds_cf[idx] = med.coef[f * med.coef_stride + ((int64_t)nz * med.n[1] + ny) * med.n[0] + nx];
+        lds_cf[f * MEDBLK3 * MEDPLANE + lz * MEDPLANE + ly * MEDROW + lx] = med.coef[f * med.coef_stride + ((int64_t)nz * med.n[1] + ny) * med.n[0] + nx];
       }
       __syncthreads();
       blk.lds = lds_cf;
