@@ -166,6 +166,14 @@ fga_status make_dev_medium(const fga_medium *m, DevMedium *o)
 
 fga_status sort_points(const double *xyz, int64_t n, double *xyz_sorted, int32_t *perm, hipStream_t st)
 {
+  if (n <= MAX_RANKED) {
+    int64_t *bad = reinterpret_cast<int64_t *>(xyz_sorted + 3 * n), first = n;
+    FGA_HIP(launch_rank_points(xyz, (int)n, xyz_sorted, perm, bad, st));
+    FGA_HIP(hipMemcpyAsync(&first, bad, sizeof first, hipMemcpyDeviceToHost, st));
+    FGA_HIP(hipStreamSynchronize(st));
+    if (first < n) return fail(FGA_EINVAL, "point %lld is not finite", (long long)first);
+    return FGA_OK;
+  }
   std::vector<double> h((size_t)3 * n);
   FGA_HIP(hipMemcpyAsync(h.data(), xyz, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   FGA_HIP(hipStreamSynchronize(st));

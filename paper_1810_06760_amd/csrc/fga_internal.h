@@ -162,7 +162,10 @@ hipError_t launch_reduce_points(const double *partial, int nblk, int m, int64_t 
                                 double *out, int64_t out_samples, int s0, int accumulate, hipStream_t st);
 // Copies n points (device [n][3]) into xyz_sorted in Morton order of their
 // positions and sets perm[k] = original index of sorted point k.  Synchronises st.
+// xyz_sorted holds 3 n + 1 doubles (the last for the check of the points).
 fga_status sort_points(const double *xyz, int64_t n, double *xyz_sorted, int32_t *perm, hipStream_t st);
+constexpr int MAX_RANKED = 1024;
+hipError_t launch_rank_points(const double *xyz, int n, double *sorted, int32_t *perm, int64_t *bad, hipStream_t st);
 // rtp (device [n][3]: radius, longitude, latitude) -> xyz (device [n][3])
 hipError_t launch_spherical_to_cartesian(const double *rtp, int64_t n, double *xyz, hipStream_t st);
 
