@@ -174,12 +174,14 @@ struct ScaledCoeffs {
 };
 
 // in ? exp(-C t ln2/256) (cos(v pi/128) + i sin(v pi/128)) : 0 for nc = -C,
-// t >= 0 and C t < 1022 * 256 (the exponent must stay normal), |v| < 2^51 where
-// in is true; where it is false t >= 0 and v may be any finite values.  The same
-// reductions and polynomials as cexp_neg_units with both arguments in table
-// units: the remainders r = -C t - k (one FMA, exact in t) and w = v - n are in
-// units of ln2/256 and pi/128, which the coefficients carry, and k goes into
-// the exponent by one shift-and-add on the table's high word.
+// t >= 0 and C t < 1022 * 256 (the exponent must stay normal; WIDE: C t < 2^31),
+// |v| < 2^51 where in is true; where it is false t >= 0 and v may be any finite
+// values.  The same reductions and polynomials as cexp_neg_units with both
+// arguments in table units: the remainders r = -C t - k (one FMA, exact in t) and
+// w = v - n are in units of ln2/256 and pi/128, which the coefficients carry, and
+// k goes into the exponent by one shift-and-add on the table's high word.  WIDE
+// scales by ldexp instead: below the normal range the values are subnormal, then 0.
+template <bool WIDE>
 __device__ __forceinline__ void cexp_scaled(const ScaledTables &tab, const ScaledCoeffs &K, double t, double nc,
                                             double v, bool in, double &re, double &im)
 {
@@ -204,8 +206,11 @@ __device__ __forceinline__ void cexp_scaled(const ScaledTables &tab, const Scale
   const double su = w * sp;
   const double cu = fma(w2, cp, 1.0);
   q = q * r;  // e^{rL} - 1
-  const double tj = __hiloint2double((int)(((unsigned)k << 12) + e.y), (int)e.x);
-  const double ex = in ? fma(tj, q, tj) : 0.0;
+  const unsigned up = (unsigned)(WIDE ? k & (TRIG_N - 1) : k) << 12;
+  const double tj = __hiloint2double((int)(up + e.y), (int)e.x);
+  double ex = fma(tj, q, tj);
+  if (WIDE) ex = ldexp(ex, k >> 8);
+  ex = in ? ex : 0.0;
   const double sphi = fma(su, scn.y, cu * scn.x);
   const double cphi = fma(cu, scn.y, -(su * scn.x));
   re = ex * cphi;

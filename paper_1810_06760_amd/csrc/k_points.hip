@@ -55,9 +55,11 @@ constexpr double LOG2E = 1.4426950408889634;
 // Summation modes: FP64 throughout; MIXED (FP32 exp / sin / cos, FP64
 // products and sums); MIXED32 (FP32 exp / sin / cos, products and per-lane
 // sums, the lane and block reductions in FP64).  FP64_WIDE: FP64 for windows
-// so wide that exp(-3 tau) leaves the normal range; such exponents are clamped.
+// so wide that exp(-3 tau) leaves the normal range; its magnitudes go on through
+// the subnormal numbers to 0.
 enum { SUM_FP64 = 0, SUM_MIXED = 1, SUM_MIXED32 = 2, SUM_FP64_WIDE = 3 };
-constexpr double MAX_EXPONENT = 700.0;  // the magnitude stays normal up to here
+constexpr double MAX_EXPONENT = 700.0;   // the magnitude stays normal up to here
+constexpr double ZERO_EXPONENT = 800.0;  // and is 0 from here on (the smallest subnormal is e^-744.4)
 
 // Points per wavefront.  FP64 sums take 12 registers a point: four points fit
 // four wavefronts per SIMD (122 registers); eight fit three and lose what the
@@ -87,7 +89,7 @@ __device__ __forceinline__ void point_term(const ScaledTables &tab, const Scaled
     ei = (T)(amp * __builtin_amdgcn_sinf(r));
   } else {
     if constexpr (MODE == SUM_FP64_WIDE) t = fmin(t, tmax);
-    cexp_scaled(tab, K, t, nc, v, in, er, ei);
+    cexp_scaled<MODE == SUM_FP64_WIDE>(tab, K, t, nc, v, in, er, ei);
   }
 }
 
@@ -182,7 +184,7 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
   const double R = sqrt(2.0 * a.tau * a.eps);
   const double hieps = 0.5 / a.eps;
   const double nc = -hieps * (MIXED ? LOG2E : INV_LN2_256);
-  const double tmax = MAX_EXPONENT / hieps;
+  const double tmax = ZERO_EXPONENT / hieps;
   const int64_t b0 = wk.blk * a.beams_per_block;
   const int64_t b1 = b0 + a.beams_per_block < a.nb ? b0 + a.beams_per_block : a.nb;
   const int s = wk.s;
@@ -421,7 +423,7 @@ __global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double 
   const double R = sqrt(2.0 * a.tau * a.eps);
   const double hieps = 0.5 / a.eps;
   const double nc = -hieps * (MIXED ? LOG2E : INV_LN2_256);
-  const double tmax = MAX_EXPONENT / hieps;
+  const double tmax = ZERO_EXPONENT / hieps;
   const ScaledCoeffs K;
   unsigned long long cnt = 0;
   double all[OUT], tot[6];
