@@ -135,6 +135,7 @@ struct PointsArgs {
   const double *xyz;         // [n][3]
   int64_t n;
   double eps, tau;
+  double nc, ncl;            // set by the launch: minus the exponent's scale for |x - Q|^2, and what its rounding left
   double *partial;           // [nblk][m][n][6]
   int beams_per_block;
   unsigned long long *evals; // NULL, or EVAL_WORDS counters whose sum takes the in-window terms
@@ -143,7 +144,7 @@ struct PointsArgs {
   int boxes_ready;           // tile_box already holds the boxes (written with the records)
   int precision;             // FGA_FP64, or FGA_FP32: FP32 exp/sin/cos of FP64-reduced arguments
 };
-hipError_t launch_sum_points(const PointsArgs &a, int *nblk_out, hipStream_t st);
+hipError_t launch_sum_points(PointsArgs a, int *nblk_out, hipStream_t st);
 // beams walked by one point-sum workgroup for nb beams, n points and m samples
 // per launch (a multiple of 64 in [least, 8192], least itself a multiple of 64
 // up to 1024); partial holds ceil(nb / that) * m * n * 6 doubles
@@ -156,7 +157,7 @@ int points_beams_per_block(int64_t nb, int64_t n, int m, int least);
 // so at 1975 (20,000 by 100) the two are even (22.8, 23.6), at 5925 it is 45 against 34.
 constexpr int MAX_SMALL = 1024;
 int points_small_blocks(int64_t nb, int64_t n);
-hipError_t launch_points_small(const fga_beams *b, const PointsArgs &a, double *out, unsigned *arrived, hipStream_t st);
+hipError_t launch_points_small(const fga_beams *b, PointsArgs a, double *out, unsigned *arrived, hipStream_t st);
 // seis[perm[r]][s0 + s][c] (+)= sum_blk partial[blk][s][r][c]   (perm NULL: identity)
 hipError_t launch_reduce_points(const double *partial, int nblk, int m, int64_t n, const int32_t *perm,
                                 double *out, int64_t out_samples, int s0, int accumulate, hipStream_t st);

@@ -50,8 +50,6 @@ __device__ __forceinline__ PointsWork points_work(int64_t id, int groups, int64_
   return w;
 }
 
-constexpr double LOG2E = 1.4426950408889634;
-
 // Summation modes: FP64 throughout; MIXED (FP32 exp / sin / cos, FP64
 // products and sums); MIXED32 (FP32 exp / sin / cos, products and per-lane
 // sums, the lane and block reductions in FP64).  FP64_WIDE: FP64 for windows
@@ -73,12 +71,14 @@ constexpr int points_per_wave(int mode) { return mode == SUM_MIXED32 ? 8 : 4; }
 // window (in false); v: the phase in units of pi/128 (FP64 sums) or of 2 pi.  Mixed
 // modes: the exponent and the phase (reduced to [-1/2, 1/2] revolutions) are
 // formed in FP64, then exp2 / sin / cos run on the FP32 transcendental unit.
-// FP64: the table-driven exponential.  nc: minus the exponent's scale for |d|^2
-// in the units that the exponential takes (ln2/256, or ln2 for the mixed modes).
+// FP64: the table-driven exponential.  nc + ncl: minus the exponent's scale for
+// |d|^2 in the units that the exponential takes (ln2/256, or ln2 for the mixed
+// modes, to which ncl is nothing).
 // T is the accumulation type (float only for MIXED32).
 template <int MODE, typename T>
 __device__ __forceinline__ void point_term(const ScaledTables &tab, const ScaledCoeffs &K, const double (&dd)[3],
-                                           const double (&pe)[3], double nc, double tmax, bool in, T &er, T &ei)
+                                           const double (&pe)[3], double nc, double ncl, double tmax, bool in, T &er,
+                                           T &ei)
 {
   double t = dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2];
   const double v = pe[0] * dd[0] + pe[1] * dd[1] + pe[2] * dd[2];
@@ -89,7 +89,7 @@ __device__ __forceinline__ void point_term(const ScaledTables &tab, const Scaled
     ei = (T)(amp * __builtin_amdgcn_sinf(r));
   } else {
     if constexpr (MODE == SUM_FP64_WIDE) t = fmin(t, tmax);
-    cexp_scaled<MODE == SUM_FP64_WIDE>(tab, K, t, nc, v, in, er, ei);
+    cexp_scaled<MODE == SUM_FP64_WIDE>(tab, K, t, nc, ncl, v, in, er, ei);
   }
 }
 
@@ -182,9 +182,8 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
     for (int d = 0; d < 3; ++d) xr[k][d] = r0 + k < a.n ? a.xyz[3 * (r0 + k) + d] : 1.0e30;
   const double R = sqrt(2.0 * a.tau * a.eps);
-  const double hieps = 0.5 / a.eps;
-  const double nc = -hieps * (MIXED ? LOG2E : INV_LN2_256);
-  const double tmax = ZERO_EXPONENT / hieps;
+  const double nc = a.nc, ncl = a.ncl;
+  const double tmax = 2.0 * ZERO_EXPONENT * a.eps;
   const int64_t b0 = wk.blk * a.beams_per_block;
   const int64_t b1 = b0 + a.beams_per_block < a.nb ? b0 + a.beams_per_block : a.nb;
   const int s = wk.s;
@@ -275,14 +274,14 @@ __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) v
         for (int d = 0; d < 3; ++d) dd[d] = xr[k][d] - q[d];
         Acc er, ei;
         if ((whole[k] >> bit) & 1) {
-          point_term<MODE>(tab, K, dd, pe, nc, tmax, true, er, ei);
+          point_term<MODE>(tab, K, dd, pe, nc, ncl, tmax, true, er, ei);
           cnt += __popcll(live);
         } else {
           const bool in = (fabs(dd[0]) <= R) & (fabs(dd[1]) <= R) & (fabs(dd[2]) <= R);
           const uint64_t bal = __ballot(in) & live;
           if (!bal) continue;
           cnt += __popcll(bal);
-          point_term<MODE>(tab, K, dd, pe, nc, tmax, in, er, ei);
+          point_term<MODE>(tab, K, dd, pe, nc, ncl, tmax, in, er, ei);
         }
         accumulate_term(u[k], B, er, ei);
       }
@@ -421,9 +420,8 @@ __global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double 
   for (int c = 0; c < 6; ++c) B[c] = (Acc)(mine ? r[6 + c] : 0.0);
   if constexpr (!MIXED) __syncthreads();
   const double R = sqrt(2.0 * a.tau * a.eps);
-  const double hieps = 0.5 / a.eps;
-  const double nc = -hieps * (MIXED ? LOG2E : INV_LN2_256);
-  const double tmax = ZERO_EXPONENT / hieps;
+  const double nc = a.nc, ncl = a.ncl;
+  const double tmax = 2.0 * ZERO_EXPONENT * a.eps;
   const ScaledCoeffs K;
   unsigned long long cnt = 0;
   double all[OUT], tot[6];
@@ -440,7 +438,7 @@ __global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double 
     if (bal) {
       cnt += __popcll(bal);
       Acc er, ei;
-      point_term<MODE>(tab, K, dd, pe, nc, tmax, in, er, ei);
+      point_term<MODE>(tab, K, dd, pe, nc, ncl, tmax, in, er, ei);
       accumulate_term(u, B, er, ei);
     }
 #pragma unroll
@@ -497,6 +495,15 @@ __global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double 
 
 }  // namespace
 
+// The exponent -|d|^2/(2 eps) in units of ln2/256 (mixed modes: of ln2) is (nc + ncl) |d|^2.
+static void exponent_scale(PointsArgs &a)
+{
+  const bool mixed = a.precision == FGA_FP32 || a.precision == FGA_FP32_ACC32;
+  const long double c = -(mixed ? 1.0L : 256.0L) * 0.72134752044448170367996234050094L / (long double)a.eps;  // 1/(2 ln2)
+  a.nc = (double)c;
+  a.ncl = (double)(c - (long double)a.nc);
+}
+
 int points_small_blocks(int64_t nb, int64_t n)
 {
   const int64_t blocks = (nb + 64 * SMALL_TILES - 1) / (64 * SMALL_TILES);
@@ -504,10 +511,11 @@ int points_small_blocks(int64_t nb, int64_t n)
   return nb > 0 && n > 0 && groups <= MAX_SMALL && blocks <= MAX_SMALL && blocks * groups <= MAX_SMALL ? (int)blocks : 0;
 }
 
-hipError_t launch_points_small(const fga_beams *b, const PointsArgs &a, double *out, unsigned *arrived, hipStream_t st)
+hipError_t launch_points_small(const fga_beams *b, PointsArgs a, double *out, unsigned *arrived, hipStream_t st)
 {
   const int nblk = points_small_blocks(b->count, a.n);
   if (nblk == 0) return hipErrorInvalidValue;
+  exponent_scale(a);
   const int groups = (int)((a.n + SMALL_POINTS - 1) / SMALL_POINTS);
   ProfScope prof(FGA_K_SUM_POINTS, st);
   auto go = [&](auto kernel) {
@@ -543,8 +551,9 @@ int points_beams_per_block(int64_t nb, int64_t n, int m, int least)
   return (int)bpb;
 }
 
-hipError_t launch_sum_points(const PointsArgs &a, int *nblk_out, hipStream_t st)
+hipError_t launch_sum_points(PointsArgs a, int *nblk_out, hipStream_t st)
 {
+  exponent_scale(a);
   const int64_t nblk = (a.nb + a.beams_per_block - 1) / a.beams_per_block;
   *nblk_out = (int)nblk;
   if (a.nb == 0 || a.n == 0 || a.m == 0) return hipSuccess;
