@@ -1,6 +1,5 @@
 // C ABI of the gfx950 FGA library: argument validation, workspace layout and
 // the host-side sequencing of the kernels.  See include/fga.h.
-#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -867,11 +866,10 @@ namespace {
 // from hipGetSymbolAddress, taken once per device with that device current.
 constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
 // (behind it the term counters, and those of the one-launch sum, which are zero
-// between calls: each call takes the next of SMALL_SETS, so that calls which
-// overlap, against the rule, spoil their own results and no later call's)
-constexpr int SMALL_SETS = 64;
-std::atomic<unsigned> g_small_calls{0};
-__attribute__((used)) static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + 8 * EVAL_WORDS + 4 * SMALL_SETS * MAX_SMALL];
+// between calls, also after calls that overlapped, against the rule, and spoilt
+// each other's results)
+__attribute__((used)) static __device__ __align__(256) unsigned char
+    scratch[kNoAllocScratchBytes + 8 * EVAL_WORDS + 4 * SMALL_COUNTERS];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -961,9 +959,7 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
     pa.partial = rows;
     pa.evals = evals ? slots : nullptr;
     pa.precision = precision;
-    unsigned *arrived = reinterpret_cast<unsigned *>(slots + EVAL_WORDS) +
-                        (size_t)(g_small_calls.fetch_add(1, std::memory_order_relaxed) % SMALL_SETS) * MAX_SMALL;
-    FGA_HIP(launch_points_small(beams, pa, out, arrived, st));
+    FGA_HIP(launch_points_small(beams, pa, out, reinterpret_cast<unsigned *>(slots + EVAL_WORDS), st));
     return evals ? read_evals(slots, st, evals) : FGA_OK;
   }
   double *emit = ar.take<double>((size_t)12 * batch);

@@ -150,14 +150,15 @@ hipError_t launch_sum_points(PointsArgs a, int *nblk_out, hipStream_t st);
 // up to 1024); partial holds ceil(nb / that) * m * n * 6 doubles
 int points_beams_per_block(int64_t nb, int64_t n, int m, int least);
 // A sum small enough for one launch: the rows of partial it takes, else 0.
-// partial: [that][n][6]; arrived: MAX_SMALL counters at 0, which are 0 again afterwards.
+// partial: [that][n][6]; counters: SMALL_COUNTERS words at 0, which are 0 again
+// when no launch that uses them is on its way.
 // Up to MAX_SMALL workgroups (256 beams by 4 points), about what the chip holds at
 // once: 1016 (65,000 beams, 16 points) take 19.7 us against 35.3 in three launches,
 // 1000 (10,000 by 100) 14.1 against 20.2.  Each four points form the records anew,
 // so at 1975 (20,000 by 100) the two are even (22.8, 23.6), at 5925 it is 45 against 34.
-constexpr int MAX_SMALL = 1024;
+constexpr int MAX_SMALL = 1024, SMALL_COUNTERS = 32 * MAX_SMALL + (MAX_SMALL + 1) * 32;
 int points_small_blocks(int64_t nb, int64_t n);
-hipError_t launch_points_small(const fga_beams *b, PointsArgs a, double *out, unsigned *arrived, hipStream_t st);
+hipError_t launch_points_small(const fga_beams *b, PointsArgs a, double *out, unsigned *counters, hipStream_t st);
 // seis[perm[r]][s0 + s][c] (+)= sum_blk partial[blk][s][r][c]   (perm NULL: identity)
 hipError_t launch_reduce_points(const double *partial, int nblk, int m, int64_t n, const int32_t *perm,
                                 double *out, int64_t out_samples, int s0, int accumulate, hipStream_t st);

@@ -365,8 +365,10 @@ __global__ __launch_bounds__(64 * RG) void k_reduce_points(const double *__restr
 // A small sum in one launch, out[r][c] over all beams.  Each wavefront forms the
 // records of one 64-beam tile and sums them at four points; the wavefronts of a
 // workgroup take neighbouring tiles, whose sums are added in LDS; the last
-// workgroup of a point group to finish (arrived counts them, and is left at 0)
-// adds the groups' sums in order, so the result does not depend on who is last.
+// workgroup of a point group to finish adds the groups' sums in order, so the
+// result does not depend on who is last.  arrived counts them modulo their number:
+// a launch leaves a counter as it found it, and so do launches that overlap,
+// since all that use one have the same number (small_counters).
 // The sums pass the L2s of the eight XCDs by device-scope stores and loads: a
 // device-scope fence in each workgroup writes a whole L2 back (204 workgroups:
 // 21 us).
@@ -468,7 +470,7 @@ __global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);
     if (t == 0)
-      last = __hip_atomic_fetch_add(arrived + pg, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nblk - 1;
+      last = atomicInc(arrived + pg, (unsigned)nblk - 1) == (unsigned)nblk - 1;
   }
   __syncthreads();
   if (!last) return;
@@ -490,7 +492,6 @@ __global__ __launch_bounds__(64 * SMALL_TILES) void k_points_small(const double 
     for (int k = 1; k < SEG; ++k) s += part[k][t];
     out[r0 * 6 + t] = s;
   }
-  if (t == 0) arrived[pg] = 0;
 }
 
 }  // namespace
@@ -511,10 +512,17 @@ int points_small_blocks(int64_t nb, int64_t n)
   return nb > 0 && n > 0 && groups <= MAX_SMALL && blocks <= MAX_SMALL && blocks * groups <= MAX_SMALL ? (int)blocks : 0;
 }
 
-hipError_t launch_points_small(const fga_beams *b, PointsArgs a, double *out, unsigned *arrived, hipStream_t st)
+// The first of the counters of a sum of nblk rows.  Counters are by (nblk, point
+// group): 1024 groups for each nblk below 32, and 32 above, as nblk times the
+// groups is at most MAX_SMALL.
+static int small_counters(int nblk) { return nblk < 32 ? nblk * MAX_SMALL : 32 * MAX_SMALL + nblk * 32; }
+static_assert(MAX_SMALL == 1024 && SMALL_COUNTERS == 32 * MAX_SMALL + (MAX_SMALL + 1) * 32, "counters cover every sum");
+
+hipError_t launch_points_small(const fga_beams *b, PointsArgs a, double *out, unsigned *counters, hipStream_t st)
 {
   const int nblk = points_small_blocks(b->count, a.n);
   if (nblk == 0) return hipErrorInvalidValue;
+  unsigned *arrived = counters + small_counters(nblk);
   exponent_scale(a);
   const int groups = (int)((a.n + SMALL_POINTS - 1) / SMALL_POINTS);
   ProfScope prof(FGA_K_SUM_POINTS, st);
