@@ -415,6 +415,10 @@ typedef struct {
   int64_t capped;          /* beams retired at an interface at the generation cap      */
 } fga_evolve_stats;
 
+/* For sets of up to 2^18 slots whose receiver buffers are small (no receivers,
+ * or few samples a chunk) the size includes room, up to 122 MB, to re-order all
+ * planes of the set in two launches.  fga_evolve also runs in a workspace that
+ * is smaller by that room, with more launches and the same results. */
 size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_evolve_opts *opts,
                                   const fga_receivers *rec);
 

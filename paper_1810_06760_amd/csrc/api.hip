@@ -462,8 +462,10 @@ fga_status read_evals(const unsigned long long *slots, hipStream_t st, int64_t *
 }
 
 struct EvolveBufs {
-  // [0] beam-steps, [1] culled, [2] quarantined, [4..6] interface counters, from [8] on the term counters
+  // [0] beam-steps, [1] culled, [2] quarantined, [4..6] interface counters, from [8] on the term counters (with
+  // receivers)
   unsigned long long *ctr = nullptr;
+  int ctr_words = 0;
   double *emit = nullptr, *partial = nullptr, *xs = nullptr, *box = nullptr, *xc = nullptr;
   int32_t *perm = nullptr;
   int64_t *blk_extra = nullptr, *blk_off = nullptr, *total = nullptr;  // interface step
@@ -480,7 +482,8 @@ struct EvolveBufs {
 static EvolveBufs evolve_layout(const EvolvePlan &p, const fga_receivers *r, int64_t cap, Arena &ar)
 {
   EvolveBufs b;
-  b.ctr = ar.take<unsigned long long>(8 + EVAL_WORDS);
+  b.ctr_words = 8 + (r ? EVAL_WORDS : 0);
+  b.ctr = ar.take<unsigned long long>(b.ctr_words);
   const int64_t nblk_all = (cap + 255) / 256 + 1;
   b.blk_extra = ar.take<int64_t>(nblk_all);
   b.blk_off = ar.take<int64_t>(nblk_all);
@@ -508,10 +511,10 @@ static EvolveBufs evolve_layout(const EvolvePlan &p, const fga_receivers *r, int
   return b;
 }
 
-}  // namespace
-
-size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_evolve_opts *opts,
-                                  const fga_receivers *rec)
+// The workspace of an evolution: the least it runs in, or one that re-orders a
+// small set in the fewest launches.
+size_t evolve_bytes(const fga_beams *beams, int nsteps, const fga_evolve_opts *opts, const fga_receivers *rec,
+                    bool least)
 {
   if (check_beams(beams) != FGA_OK || nsteps < 0) return 0;
   if (rec && rec->stride < 1) return 0;
@@ -528,7 +531,7 @@ size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_
   if (p.resort > 0) {
     Arena sa(nullptr, 0);
     size_t ns = 0;
-    sort_beams_spatial(&bb, sa, nullptr, wb.idle_bytes, nullptr, true, &ns);
+    sort_beams_spatial(&bb, sa, nullptr, wb.idle_bytes, nullptr, true, &ns, least);
     need = need > base + ns ? need : base + ns;
   }
   if (opts && opts->compact) {
@@ -538,6 +541,23 @@ size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_
     need = need > base + n2 ? need : base + n2;
   }
   return need;
+}
+
+}  // namespace
+
+}  // extern "C"
+
+size_t fga::evolve_least_bytes(const fga_beams *beams, int nsteps, const fga_evolve_opts *opts, const fga_receivers *rec)
+{
+  return evolve_bytes(beams, nsteps, opts, rec, true);
+}
+
+extern "C" {
+
+size_t fga_evolve_workspace_bytes(const fga_beams *beams, int nsteps, const fga_evolve_opts *opts,
+                                  const fga_receivers *rec)
+{
+  return evolve_bytes(beams, nsteps, opts, rec, false);
 }
 
 fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int nsteps, const fga_evolve_opts *opts,
@@ -579,7 +599,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
     return fail(FGA_ENOMEM, "evolve workspace too small (%zu bytes given, %zu needed)", workspace_bytes, ar.used);
   const size_t sort_base = Arena::need(ar.used);  // re-sort and compaction work here, behind the counters
   const size_t sub_bytes = workspace_bytes > sort_base ? workspace_bytes - sort_base : 0;
-  FGA_HIP(hipMemsetAsync(ctr, 0, (8 + EVAL_WORDS) * sizeof(unsigned long long), st));
+  FGA_HIP(hipMemsetAsync(ctr, 0, wb.ctr_words * sizeof(unsigned long long), st));
   if (rec && rec->n > 0) {
     const double *xyz = rec->xyz;
     if (rec->coords == FGA_COORDS_SPHERICAL) {
@@ -770,13 +790,13 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
   }
   if (stats || (cutoff > 0 && nsteps > 0)) {
     unsigned long long h[8 + EVAL_WORDS];
-    FGA_HIP(hipMemcpyAsync(h, ctr, sizeof h, hipMemcpyDeviceToHost, st));
+    FGA_HIP(hipMemcpyAsync(h, ctr, wb.ctr_words * sizeof *h, hipMemcpyDeviceToHost, st));
     FGA_HIP(hipStreamSynchronize(st));
     if (stats) {
       stats->beam_steps = (int64_t)h[0];
       stats->culled = (int64_t)h[1];
       stats->quarantined = (int64_t)h[2];
-      stats->evals = sum_evals(h + 8);
+      stats->evals = rec ? sum_evals(h + 8) : 0;
       stats->crossings = (int64_t)h[4];
       stats->spawned = (int64_t)h[5];
       stats->capped = (int64_t)h[6];

@@ -227,8 +227,11 @@ hipError_t launch_scan(const int64_t *in, int64_t *out, int64_t n, int64_t *tota
 // Morton-order the beam set by Q (dead beams dropped; count updated; synchronises st).
 // scratch (256-byte aligned, may be NULL): memory free during the call beside the
 // arena's; the more planes it holds the fewer launches the re-ordering takes
+// (least: the size is what the call takes at least)
 fga_status sort_beams_spatial(fga_beams *b, Arena &ar, void *scratch, size_t scratch_bytes, hipStream_t st,
-                              bool size_only, size_t *need);
+                              bool size_only, size_t *need, bool least = false);
+// The least workspace fga_evolve takes; its query gives more for small sets.
+size_t evolve_least_bytes(const fga_beams *beams, int nsteps, const fga_evolve_opts *opts, const fga_receivers *rec);
 
 // stable compaction of the beam set by FLAGS & ALIVE
 fga_status compact_beams(fga_beams *b, Arena &ar, hipStream_t st, bool size_only, size_t *need);

@@ -285,9 +285,10 @@ struct SortBufs {
   size_t free_bytes;  // from k1 to the workspace's end: free once the keys are sorted and the live beams counted
 };
 
-// Beams of a set for whose sort a workspace is sized with a slot for every plane
-// (at most 113 MB) unless the caller has memory to lend, as its launches cost more than its bytes: 98 k beams without
-// receivers' buffers to borrow took 30 launches of 5 us for the planes, now two.
+// Beams of a set for whose sort a workspace query counts a slot for every plane
+// (at most 122 MB) unless the caller has memory to lend, as its launches cost more
+// than its bytes: 98 k beams without receivers' buffers to borrow took 30 launches
+// of 5 us for the planes, now two.  The call takes less, down to a query without them.
 constexpr int64_t SMALL_SET = 1 << 18;
 
 SortBufs sort_layout(int64_t n, Arena &ar)
@@ -322,12 +323,13 @@ hipError_t launch_rank_points(const double *xyz, int n, double *sorted, int32_t 
 }
 
 fga_status sort_beams_spatial(fga_beams *b, Arena &ar, void *scratch, size_t scratch_bytes, hipStream_t st,
-                              bool size_only, size_t *need)
+                              bool size_only, size_t *need, bool least)
 {
   const int64_t n = b->count;
   SortBufs s = sort_layout(n, ar);
   if (size_only) {
-    if (scratch_bytes < (size_t)NPLANE * 8 * n && n <= SMALL_SET) ar.take<double>((size_t)NPLANE * ((n + 31) & ~(int64_t)31));
+    if (!least && scratch_bytes < (size_t)NPLANE * 8 * n && n <= SMALL_SET)
+      ar.take<double>((size_t)NPLANE * ((n + 31) & ~(int64_t)31));
     *need = ar.used;
     return FGA_OK;
   }

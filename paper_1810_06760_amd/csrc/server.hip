@@ -66,7 +66,8 @@ bool request_sizes(const fga_request *r, Sizes *z)
   rc.coords = r->receiver_coords;
   const size_t wd = r->point_source ? fga_decompose_point_source_workspace_bytes(&r->source)
                                     : fga_decompose_workspace_bytes(&r->mesh, 0);
-  const size_t we = fga_evolve_workspace_bytes(&b, r->nsteps, nullptr, r->n_receivers > 0 ? &rc : nullptr);
+  // the least: what a request holds decides whether it is taken and how many run
+  const size_t we = fga::evolve_least_bytes(&b, r->nsteps, nullptr, r->n_receivers > 0 ? &rc : nullptr);
   z->ws = align256(wd > we ? wd : we);
   z->total = z->beams + z->f + z->rec + z->seis + z->ws;
   return wd > 0 && we > 0;
