@@ -469,7 +469,8 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
  * a_SV N_SV + a_SH N_SH.  xyz: device [n][3]; out: device complex [n][3]
  * (overwritten).  precision: FGA_FP64, FGA_FP32 or FGA_FP32_ACC32 (as in
  * fga_receivers); * others give FGA_EUNSUPPORTED.  evals (host, may be NULL): number of
- * in-window terms; the call synchronises `stream` when evals != NULL. */
+ * in-window terms; the call synchronises `stream` when evals != NULL.  A
+ * workspace of the query's size also serves fewer beams or fewer points. */
 size_t fga_reconstruct_points_workspace_bytes(const fga_beams *beams, int64_t n);
 fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau, int64_t n,
                                   const double *xyz, int precision, double *out,

@@ -814,8 +814,7 @@ size_t fga_reconstruct_points_workspace_bytes(const fga_beams *beams, int64_t n)
   Arena ar(nullptr, 0);
   ar.take<unsigned long long>(EVAL_WORDS);
   ar.take<double>((size_t)12 * batch);
-  const int bpb = points_beams_per_block(batch, n, 1, 64);
-  ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
+  ar.take<double>(points_partial_most(batch, n));
   ar.take<double>((size_t)((batch + 63) / 64) * 6);
   ar.take<double>((size_t)3 * n + 1);
   ar.take<int32_t>((size_t)n + 1);

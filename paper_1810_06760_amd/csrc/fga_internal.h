@@ -149,6 +149,8 @@ hipError_t launch_sum_points(PointsArgs a, int *nblk_out, hipStream_t st);
 // per launch (a multiple of 64 in [least, 8192], least itself a multiple of 64
 // up to 1024); partial holds ceil(nb / that) * m * n * 6 doubles
 int points_beams_per_block(int64_t nb, int64_t n, int m, int least);
+// The doubles of partial that sums of at most nb beams at at most n points take (m 1, least 64).
+size_t points_partial_most(int64_t nb, int64_t n);
 // A sum small enough for one launch: the rows of partial it takes, else 0.
 // partial: [that][n][6]; counters: SMALL_COUNTERS words at 0, which are 0 again
 // when no launch that uses them is on its way.

@@ -12,6 +12,7 @@
 // are reduced over the lanes in a fixed order and written once per wavefront;
 // per-workgroup partials are then reduced in a fixed order, so the sums are
 // bitwise reproducible and need no atomics.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -537,6 +538,12 @@ hipError_t launch_points_small(const fga_beams *b, PointsArgs a, double *out, un
   return hipGetLastError();
 }
 
+namespace {
+constexpr int RANGE_GROUP = 4 * WPW;  // the FP64 sums' points per workgroup, for every mode
+constexpr int64_t MANY_RANGES = 8192, FILL_RANGES = 2048;
+constexpr int LONG_RANGE = 1024, MAX_RANGE = 8192;
+}  // namespace
+
 int points_beams_per_block(int64_t nb, int64_t n, int m, int least)
 {
   // enough workgroups (about 8192) that the last partial round of resident
@@ -545,18 +552,29 @@ int points_beams_per_block(int64_t nb, int64_t n, int m, int least)
   // `least`, until the chip holds one workgroup per slot (about 2048): beyond
   // that a workgroup's tables and final reduction (about 500 instructions, against
   // 200 for a tile) outweigh what the extra workgroups give.
-  constexpr int PG = 4 * WPW;  // the FP64 sums' points per workgroup, for every mode
-  const int64_t groups = (n + PG - 1) / PG;
+  const int64_t groups = (n + RANGE_GROUP - 1) / RANGE_GROUP;
   const int64_t pairs = nb * groups * (m > 0 ? m : 1);
-  int64_t bpb = (pairs + 8191) / 8192;
-  if (bpb < 1024) {
-    const int64_t fill = (pairs + 2047) / 2048 < 1024 ? (pairs + 2047) / 2048 : 1024;
-    bpb = fill > bpb ? fill : bpb;
+  int64_t bpb = (pairs + MANY_RANGES - 1) / MANY_RANGES;
+  if (bpb < LONG_RANGE) {
+    const int64_t fill = (pairs + FILL_RANGES - 1) / FILL_RANGES;
+    bpb = std::max(bpb, std::min<int64_t>(fill, LONG_RANGE));
   }
   bpb = (bpb + 63) / 64 * 64;
   if (bpb < least) bpb = least;
-  if (bpb > 8192) bpb = 8192;
+  if (bpb > MAX_RANGE) bpb = MAX_RANGE;
   return (int)bpb;
+}
+
+size_t points_partial_most(int64_t nb, int64_t n)
+{
+  // A sum takes at most F / groups + 1 rows of n points, so fewer than F groups' points
+  // and a row, for F = FILL_RANGES (ranges of 64 beams or more) or F = MANY_RANGES
+  // (LONG_RANGE or more), or ranges of MAX_RANGE.  The rows themselves go down where
+  // the range grows by a tile (14,561 beams at 65 points: 228, 14,568: 114).
+  auto rows = [nb](int64_t range) { return (nb + range - 1) / range; };
+  const int64_t fill = std::min(rows(64) * n, FILL_RANGES * RANGE_GROUP + n);
+  const int64_t many = std::min(rows(LONG_RANGE) * n, MANY_RANGES * RANGE_GROUP + n);
+  return (size_t)6 * std::max(std::max(fill, many), rows(MAX_RANGE) * n);
 }
 
 hipError_t launch_sum_points(PointsArgs a, int *nblk_out, hipStream_t st)
