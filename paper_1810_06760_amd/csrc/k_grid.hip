@@ -732,23 +732,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   Pol::store(acc, partial + item * (3 * T * T * T * 2), ws, half);
 }
 
-// Candidates per work item.  A grid of many tiles takes eight items a tile, at
-// most MAX_SEG in all; one of few takes shorter ones, so that they still fill the
-// chip.  In FP64 workgroups share a compute unit's matrix cores and gain little
-// from company: MIN_SEG items, up to where eight a tile are more than one for each
-// compute unit anyway (18 tiles, 1 M beams: 58.5 -> 35.6 ms; 36 tiles, 883 k: 75.8
-// -> 58.5; 48 tiles, 468 k: 40.9 -> 46.6).  The mixed modes' items are sized to be
-// at once just as many as are resident (52 tiles, 911 k beams: 15.9 ms in 512
-// items, 17.5 in eight a tile, 21.3 in 564; 20 tiles: 18.3 and 32.6; 60 tiles: 6.1
-// and 5.9).
+// Candidates per work item.  A grid of many tiles takes eight items a tile, at most
+// MAX_SEG in all.  Few tiles take shorter items, as many as RESIDENT: in the mixed
+// modes as many workgroups as are resident, in FP64, two workgroups an item, four
+// for each compute unit, whose matrix cores they share; one item more and the last
+// turn is nearly empty (FP64, 27 tiles, 300 k beams: 15.3 ms in at most 512 items,
+// 17.7 in up to 539, 17.3 in eight a tile; mixed, 52 tiles: 15.9 in 512, 21.3 in
+// 564).  The lines lie where eight a tile fill their own turns as well: FP64 at 60
+// and 300 k beams, eight a tile against this: 36 tiles 1.34, 40 1.11 to 1.17, 44
+// 1.04 to 1.06, 45 1.01 to 1.06, 48 0.92 to 0.95; FP16X3: 48 tiles 1.16 to 1.19,
+// 56 1.06 to 1.09, 60 0.96 to 1.01.
+constexpr int FEW_TILES_FP64 = 45, FEW_TILES_MIXED = 56;
 int64_t item_length(const std::vector<int64_t> &count, int max_items, bool fp64)
 {
   const int ntile = (int)count.size();
   auto round_up = [](int64_t v) { return std::max<int64_t>((v + NB - 1) / NB * NB, SEG_BEAMS); };
   int64_t total = 0;
   for (int64_t c : count) total += c;
-  if (fp64 || ntile > 56) {
-    const int nseg = fp64 && ntile <= 36 ? max_items - ntile : std::min(MAX_SEG, 8 * ntile);
+  if (ntile > (fp64 ? FEW_TILES_FP64 : FEW_TILES_MIXED)) {
+    const int nseg = std::min(MAX_SEG, 8 * ntile);
     return round_up((total + nseg - 1) / nseg);
   }
   const int lim = std::min(RESIDENT, max_items);
