@@ -504,7 +504,11 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
  * FGA_FP32, FGA_BF16X3 or FGA_FP16X3 (split hi+lo factors, FP32 accumulation;
  * FGA_FP16X2: the Khatri-Rao rows in single FP16, the other factor split hi+lo;
  * phases reduced modulo 2 pi in FP64 before the cast).  evals (host, may be
- * NULL): algorithmic in-window (beam, point) terms. */
+ * NULL): algorithmic in-window (beam, point) terms.  For grids of up to 56 tiles
+ * the query counts up to 512 partial tiles of 196,608 bytes (101 MB), which fill
+ * the chip; the call also takes a workspace that holds fewer, down to nine a tile,
+ * and is slower in it.  The order of the sums, so their rounding, goes by the
+ * number of partial tiles held. */
 size_t fga_reconstruct_grid_workspace_bytes(const fga_beams *beams, const int n[3], double eps,
                                             double tau, const double h[3]);
 fga_status fga_reconstruct_grid(const fga_beams *beams, double eps, double tau, const int n[3],

@@ -40,11 +40,12 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int T = 16;       // tile edge (points)
 constexpr int NB = 16;      // beams per LDS batch
 constexpr int MAXR = 1024;  // max candidate runs per tile: (2 reach + 1)^2
-// Work items per launch beyond one per tile that the workspace holds: eight per
-// tile up to MAX_SEG, and at least MIN_SEG, so that a grid of few tiles still fills
-// the chip; 32^3 points (8 tiles) and 98 k beams took 3.30 ms in 72 items.
-constexpr int MAX_SEG = 4096, MIN_SEG = 512, SEG_BEAMS = 64;  // SEG_BEAMS: shortest item
+// Work items per launch: eight per tile up to MAX_SEG and one per tile more, or, so
+// that a grid of few tiles still fills the chip, as many as RESIDENT (item_length);
+// 32^3 points (8 tiles) and 98 k beams took 3.30 ms in 72 items.
+constexpr int MAX_SEG = 4096, SEG_BEAMS = 64;  // SEG_BEAMS: shortest item
 constexpr int RESIDENT = 512;  // workgroups at once
+constexpr int TILE_DOUBLES = 3 * T * T * T * 2;  // a partial tile
 
 struct GridGeom {
   int n[3], nt[3], nc[3], reach[3];
@@ -729,7 +730,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   if (tid == 0 && half == 0 && executed && nexec) atomicAdd(executed, nexec);
   // partial tile [c][l][j][i] complex
-  Pol::store(acc, partial + item * (3 * T * T * T * 2), ws, half);
+  Pol::store(acc, partial + item * TILE_DOUBLES, ws, half);
 }
 
 // Candidates per work item.  A grid of many tiles takes eight items a tile, at most
@@ -782,7 +783,7 @@ __global__ __launch_bounds__(256) void k_grid_reduce(GridGeom g, const int32_t *
   double re = 0.0, im = 0.0;
   const int f = first[t];
   for (int k = 0; k < nitems[t]; ++k) {
-    const double *P = partial + (int64_t)(f + k) * (3 * T * T * T * 2) + ((((int64_t)c * T + l) * T + j) * T + i) * 2;
+    const double *P = partial + (int64_t)(f + k) * TILE_DOUBLES + ((((int64_t)c * T + l) * T + j) * T + i) * 2;
     re += P[0];
     im += P[1];
   }
@@ -827,29 +828,47 @@ fga_status grid_sum_impl(const fga_beams *b, double eps, double tau, const int n
   const int ntile = g.nt[0] * g.nt[1] * g.nt[2];
   const int64_t ncells = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
   if (ncells >= 0x7fffffff) return fail(FGA_EUNSUPPORTED, "too many cells");
-  const int64_t most = (int64_t)ntile * ((nb + SEG_BEAMS - 1) / SEG_BEAMS);  // no item shorter than SEG_BEAMS
-  const int nseg = (int)std::min<int64_t>(std::min(MAX_SEG, std::max(MIN_SEG, 8 * ntile)), std::max<int64_t>(most, 1));
-  const int max_items = nseg + ntile;
-
-  int32_t *keys = ar.take<int32_t>(nb + 1), *keys2 = ar.take<int32_t>(nb + 1);
-  int32_t *vals = ar.take<int32_t>(nb + 1), *vals2 = ar.take<int32_t>(nb + 1);
-  int64_t *start = ar.take<int64_t>(ncells + 1);
-  int64_t *tcount = ar.take<int64_t>(ntile);
-  Item *items = ar.take<Item>(max_items);
-  int32_t *sched = ar.take<int32_t>(max_items);
-  int32_t *first = ar.take<int32_t>(ntile), *nitems = ar.take<int32_t>(ntile);
-  unsigned long long *ev = ar.take<unsigned long long>(3);  // evals, executed, max |W| bits
-  double *partial = ar.take<double>((size_t)max_items * 3 * T * T * T * 2);
-  double *rec = ar.take<double>((size_t)12 * (nb + 1));
   size_t sort_bytes = 0;
-  if (hipcub::DeviceRadixSort::SortPairs(nullptr, sort_bytes, keys, keys2, vals, vals2, (int)nb, 0, 31, st) !=
-      hipSuccess)
+  if (hipcub::DeviceRadixSort::SortPairs(nullptr, sort_bytes, (int32_t *)nullptr, (int32_t *)nullptr,
+                                         (int32_t *)nullptr, (int32_t *)nullptr, (int)nb, 0, 31, st) != hipSuccess)
     return fail(FGA_EDEVICE, "radix sort size query failed");
-  void *sort_tmp = ar.take<char>(sort_bytes);
+  // Partial tiles: what the items of item_length can take, no item being shorter than
+  // SEG_BEAMS; in a workspace that holds fewer, longer items of few tiles, down to
+  // eight a tile and one.
+  const int64_t most = std::max<int64_t>((int64_t)ntile * ((nb + SEG_BEAMS - 1) / SEG_BEAMS), ntile);
+  const int eight = (int)std::min<int64_t>(std::min(MAX_SEG, 8 * ntile) + ntile, most);
+  int max_items = ntile > FEW_TILES_MIXED ? eight : (int)std::min<int64_t>(RESIDENT, most);
+  const int least_items = std::min(eight, max_items);
+
+  int32_t *keys, *keys2, *vals, *vals2, *sched, *first, *nitems;
+  int64_t *start, *tcount;
+  Item *items;
+  unsigned long long *ev;  // evals, executed, max |W| bits
+  double *partial, *rec;
+  void *sort_tmp;
+  auto layout = [&](Arena &a) {
+    keys = a.take<int32_t>(nb + 1), keys2 = a.take<int32_t>(nb + 1);
+    vals = a.take<int32_t>(nb + 1), vals2 = a.take<int32_t>(nb + 1);
+    start = a.take<int64_t>(ncells + 1);
+    tcount = a.take<int64_t>(ntile);
+    items = a.take<Item>(max_items);
+    sched = a.take<int32_t>(max_items);
+    first = a.take<int32_t>(ntile), nitems = a.take<int32_t>(ntile);
+    ev = a.take<unsigned long long>(3);
+    partial = a.take<double>((size_t)max_items * TILE_DOUBLES);
+    rec = a.take<double>((size_t)12 * (nb + 1));
+    sort_tmp = a.take<char>(sort_bytes);
+    return a.used;
+  };
   if (size_only) {
-    *need = ar.used;
+    *need = layout(ar);
     return FGA_OK;
   }
+  for (; max_items > least_items; --max_items) {
+    Arena dry(nullptr, 0);
+    if (layout(dry) <= ar.size) break;
+  }
+  layout(ar);
   if (!keys || !keys2 || !vals || !vals2 || !start || !tcount || !items || !sched || !first || !nitems || !ev || !partial ||
       !sort_tmp || !rec)
     return fail(FGA_ENOMEM, "grid summation workspace too small (%zu bytes given)", ar.size);
