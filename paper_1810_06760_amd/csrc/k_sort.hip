@@ -213,7 +213,7 @@ hipError_t permute_planes(const PlaneSet &ps, const int32_t *perm, int64_t n, co
 __global__ __launch_bounds__(256) void k_rank_points(const double *__restrict__ xyz, int n, double *__restrict__ sorted,
                                                      int32_t *__restrict__ perm, int64_t *__restrict__ bad)
 {
-  __shared__ uint32_t key[MAX_RANKED];
+  __shared__ alignas(16) uint32_t key[MAX_RANKED];  // read four at a time
   __shared__ double red[4][6];
   __shared__ int first_bad;
   const int t = threadIdx.x;
