@@ -462,7 +462,7 @@ fga_status read_evals(const unsigned long long *slots, hipStream_t st, int64_t *
 }
 
 struct EvolveBufs {
-  // [0] beam-steps, [1] culled, [2] quarantined, [4..6] interface counters, from [8] on the term counters (with
+  // [0] beam-steps, [1] culled, [2] quarantined, [3..5] interface counters, from [8] on the term counters (with
   // receivers)
   unsigned long long *ctr = nullptr;
   int ctr_words = 0;
@@ -681,7 +681,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
           ia.child_cut = child_cut;
           ia.blk_extra = wb.blk_extra;
           ia.blk_off = wb.blk_off;
-          ia.counters = ctr + 4;
+          ia.counters = ctr + 3;
           ia.list = wb.cross_sorted;  // in slot order: the children's slots do not depend on the order of arrival
           ia.nlist = ncross;
           ia.ncross = wb.cross_count;
@@ -797,9 +797,9 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
       stats->culled = (int64_t)h[1];
       stats->quarantined = (int64_t)h[2];
       stats->evals = rec ? sum_evals(h + 8) : 0;
-      stats->crossings = (int64_t)h[4];
-      stats->spawned = (int64_t)h[5];
-      stats->capped = (int64_t)h[6];
+      stats->crossings = (int64_t)h[3];
+      stats->spawned = (int64_t)h[4];
+      stats->capped = (int64_t)h[5];
     }
   }
   return FGA_OK;
@@ -884,6 +884,7 @@ namespace {
 // array's name as a device address: the address of each device's copy comes
 // from hipGetSymbolAddress, taken once per device with that device current.
 constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;
+constexpr size_t kNoAllocHead = 8;  // unused, and part of what decides the most points a call takes
 // (behind it the term counters, and those of the one-launch sum, which are zero
 // between calls, also after calls that overlapped, against the rule, and spoilt
 // each other's results)
@@ -923,7 +924,7 @@ __global__ void k_zero_u64(unsigned long long *p, int n)
 size_t noalloc_bytes(int64_t batch, int64_t n)
 {
   Arena ar(nullptr, 0);
-  ar.take<unsigned long long>(1);
+  ar.take<char>(kNoAllocHead);
   ar.take<double>((size_t)12 * batch);
   const int bpb = points_beams_per_block(batch, n, 1, 64);
   ar.take<double>((size_t)((batch + bpb - 1) / bpb) * n * 6);
@@ -966,7 +967,7 @@ fga_status fga_reconstruct_points_noalloc(const fga_beams *beams, double eps, do
     FGA_HIP(hipGetLastError());
   }
   Arena ar(base, kNoAllocScratchBytes);
-  ar.take<unsigned long long>(1);
+  ar.take<char>(kNoAllocHead);
   const int small = points_small_blocks(nb, n);
   double *rows = small ? ar.take<double>((size_t)small * n * 6) : nullptr;
   if (rows) {

@@ -173,29 +173,26 @@ __global__ __launch_bounds__(256) void k_permute(PlaneSet ps, const int32_t *__r
   }
 }
 
-// The permutation of all planes in as few launches as the scratch allows:
-// with NPLANE slots one gather and one copy; with fewer, groups of half the
-// slots, each launch gathering one group while it copies the group before
-// back (a single slot alternates).
+// The permutation of all planes in as few launches as the scratch allows: with
+// NPLANE slots one gather and one copy; with fewer, groups of half the slots, each
+// launch gathering one group while it copies the group before back.  The sort's own
+// buffers always give two slots.
 hipError_t permute_planes(const PlaneSet &ps, const int32_t *perm, int64_t n, const Slots &sl, hipStream_t st)
 {
   const int slots = sl.na + sl.nb;
-  if (slots < 1) return hipErrorInvalidValue;
-  const int per = slots >= NPLANE ? NPLANE : (slots >= 2 ? slots / 2 : 1);
+  if (slots < 2) return hipErrorInvalidValue;
+  const int per = slots >= NPLANE ? NPLANE : slots / 2;
   const unsigned nblk = (unsigned)((n + 255) / 256);
   auto launch = [&](int g0, int g1, int gs, int c0, int c1, int cs) {
     const int y = (g1 - g0 + G - 1) / G + (c1 - c0 + G - 1) / G;
     hipLaunchKernelGGL(k_permute, dim3(nblk, (unsigned)y), 256, 0, st, ps, perm, n, sl, g0, g1, gs, c0, c1, cs);
     return hipGetLastError();
   };
-  const bool overlap = slots >= 2 * per;
   int prev0 = 0, prev1 = 0, prevs = 0;
   for (int g0 = 0, k = 0; g0 < NPLANE; g0 += per, ++k) {
-    const int g1 = g0 + per < NPLANE ? g0 + per : NPLANE;
-    const int gs = overlap ? (k & 1) * per : 0;
-    hipError_t e;
-    if (!overlap && prev1 > prev0 && (e = launch(0, 0, 0, prev0, prev1, prevs)) != hipSuccess) return e;
-    if ((e = overlap ? launch(g0, g1, gs, prev0, prev1, prevs) : launch(g0, g1, gs, 0, 0, 0)) != hipSuccess) return e;
+    const int g1 = g0 + per < NPLANE ? g0 + per : NPLANE, gs = (k & 1) * per;
+    hipError_t e = launch(g0, g1, gs, prev0, prev1, prevs);
+    if (e != hipSuccess) return e;
     prev0 = g0;
     prev1 = g1;
     prevs = gs;
@@ -278,7 +275,8 @@ __global__ __launch_bounds__(256) void k_rank_points(const double *__restrict__ 
 struct SortBufs {
   uint32_t *k1, *k2;
   int32_t *v1, *v2;
-  double *part, *box, *tmp;
+  double *part, *box;
+  double *room;  // nothing of its own: with it the free bytes hold two planes
   int64_t *alive;
   void *sort_tmp;
   size_t sort_bytes;
@@ -303,7 +301,7 @@ SortBufs sort_layout(int64_t n, Arena &ar)
   b.k1 = ar.take<uint32_t>(n + 1);
   b.k2 = ar.take<uint32_t>(n + 1);
   b.v1 = ar.take<int32_t>(n + 1);
-  b.tmp = ar.take<double>(n + 1);
+  b.room = ar.take<double>(n + 1);
   b.sort_bytes = 0;
   // size query only (no device work): the bytes come back in sort_bytes
   (void)hipcub::DeviceRadixSort::SortPairs(nullptr, b.sort_bytes, b.k1, b.k2, b.v1, b.v2, (int)(n > 0 ? n : 1), 0,
@@ -333,7 +331,7 @@ fga_status sort_beams_spatial(fga_beams *b, Arena &ar, void *scratch, size_t scr
     *need = ar.used;
     return FGA_OK;
   }
-  if (!s.k1 || !s.k2 || !s.v1 || !s.v2 || !s.part || !s.box || !s.tmp || !s.alive || !s.sort_tmp)
+  if (!s.k1 || !s.k2 || !s.v1 || !s.v2 || !s.part || !s.box || !s.room || !s.alive || !s.sort_tmp)
     return fail(FGA_ENOMEM, "beam sort workspace too small (%zu bytes given)", ar.size);
   if (n == 0) return FGA_OK;
   if (n > 0x7fffffff) return fail(FGA_EUNSUPPORTED, "more than 2^31 beams in one sort");
