@@ -107,7 +107,7 @@ __device__ __forceinline__ void fill_tables(ScaledTables &t)
 
 // Coefficients of cexp_scaled's polynomials, held in registers over a loop:
 // the compiler otherwise moves each into a fresh register pair at every use
-// (7 moves in a term of 48 instructions).  An FMA takes one scalar operand, so
+// (7 moves in a term of 49 instructions).  An FMA takes one scalar operand, so
 // the first step of each polynomial has its addend in a vector register.
 struct ScaledCoeffs {
   double e4, e3, e2, e1;  // L^4/24, L^3/6, L^2/2, L with L = ln2/256

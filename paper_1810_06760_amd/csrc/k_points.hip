@@ -151,14 +151,16 @@ __device__ __forceinline__ void reduce24(const double (&v)[24], double (&out)[6]
 // MODE: one of the SUM_ modes (the term and its sum as stated at point_term;
 // MIXED32 holds the tile's records B and the sums in FP32).
 //
-// Bound by vector issue (busy in 79 % of the cycles on 66 k beams x 16 samples
-// x 512 points): a term inside the window costs 48 instructions, 12 of them the
-// accumulation, and reads 24 bytes of tables.  What a term does not need is
-// decided per tile by one lane each, 64 tiles at a time: a point whose window the
-// tile's box misses is not visited, and one whose window holds the whole box is
-// summed without the window test and mask.  With 63 instructions a term and the
-// test on every beam the same launch took 1.36 ms; it takes 1.14 ms, and one over
-// 4.1 M beams x 16 samples x 256 points 25.3 ms in place of 29.9.
+// Bound by vector issue where tiles lie wholly in windows (busy in 82 % of the
+// cycles on 66 k beams x 16 samples x 512 points): a term inside the window costs 49
+// instructions, 12 of them the accumulation, and reads 24 bytes of tables.  What a
+// term does not need is decided per tile by one lane each, 64 tiles at a time: a
+// point whose window the tile's box misses is not visited, and one whose window holds
+// the whole box is summed without the window test and mask.  With 63 instructions a
+// term and the test on every beam the same launch took 1.36 ms; it takes 1.17 ms, and
+// one over 4.1 M beams x 16 samples x 256 points 25.8 ms in place of 29.9.  There the
+// vector unit is busy in 77 % of the cycles, 3.3 of four wavefronts are resident and
+// wait 37 % of their time, on a tile's twelve record loads among others.
 template <int MODE>
 __global__ __launch_bounds__(64 * WPW) __attribute__((amdgpu_waves_per_eu(4))) void k_sum_points(PointsArgs a, int groups, int64_t nblk)
 {
