@@ -468,7 +468,7 @@ fga_status fga_evolve(const fga_medium *med, fga_beams *beams, double dt, int ns
  * over the beams with max_d |x_d - Q_d| <= sqrt(2 tau eps), A_b = a_P P/|P| or
  * a_SV N_SV + a_SH N_SH.  xyz: device [n][3]; out: device complex [n][3]
  * (overwritten).  precision: FGA_FP64, FGA_FP32 or FGA_FP32_ACC32 (as in
- * fga_receivers); * others give FGA_EUNSUPPORTED.  evals (host, may be NULL): number of
+ * fga_receivers); others give FGA_EUNSUPPORTED.  evals (host, may be NULL): number of
  * in-window terms; the call synchronises `stream` when evals != NULL.  A
  * workspace of the query's size also serves fewer beams or fewer points. */
 size_t fga_reconstruct_points_workspace_bytes(const fga_beams *beams, int64_t n);
@@ -482,14 +482,15 @@ fga_status fga_reconstruct_points(const fga_beams *beams, double eps, double tau
  * forbid hipMalloc): the same arguments without a workspace.  Its records,
  * tile boxes, partial sums and term counter live in a fixed scratch array
  * that the library holds on each device it runs on until the process ends
- * (fga_reconstruct_points_noalloc_max_bytes() bytes, 64 MiB); the call itself
- * allocates nothing.  Beams are taken in batches of whole 64-beam tiles sized
- * so that records and partial sums fit; the points are used in the order
- * given (fga_reconstruct_points first sorts them by position, which only
- * speeds up the sum), and must be finite (not checked).  Every call on a
- * device shares that device's scratch: calls that overlap on one device (on
- * different streams or host threads) race and give wrong results.  The
- * counter is cleared by a kernel, not a memset.
+ * (fga_reconstruct_points_noalloc_max_bytes() bytes, 64 MiB, and 0.3 MB of
+ * counters behind them); the call itself allocates nothing.  Beams are taken in
+ * batches of whole 64-beam tiles sized so that records and partial sums fit;
+ * the points are used in the order given (fga_reconstruct_points first sorts
+ * them by position, which only speeds up the sum), and must be finite (not
+ * checked).  Every call on a device shares that device's scratch: calls that
+ * overlap on one device (on different streams or host threads) race and give
+ * wrong results (later calls do not).  The counter is cleared by a kernel, not
+ * a memset.
  * Errors: as fga_reconstruct_points; FGA_ENOMEM when n points need more
  * scratch than the array holds even for one tile (about 1.3 million points). */
 size_t fga_reconstruct_points_noalloc_max_bytes(void);
